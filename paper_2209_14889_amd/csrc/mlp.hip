@@ -2,9 +2,8 @@
 // C ABI declared in include/lb_mlp.h.
 //
 // Products run on the matrix cores: v_mfma_f32_16x16x16_bf16 with BF16 operands rounded (nearest
-// even) from FP32 while a 64x64 output tile's operands are staged through LDS, FP32 accumulation,
-// and fused epilogues (bias, tanh, tanh derivative).  Master weights, gradients and Adam moments
-// are FP32.
+// even) from FP32 as they are staged, FP32 accumulation in the order of k, and fused epilogues (bias,
+// tanh, tanh derivative).  Master weights, gradients and Adam moments are FP32.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,64 +23,104 @@ namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 hw_bf16x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ short bf16_rne(float x) {
-    unsigned u = __float_as_uint(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (short)(u >> 16);   // inf / nan kept
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (short)(u >> 16);
+// four values rounded to BF16 (nearest even; the conversion instruction of the target)
+__device__ __forceinline__ bf16x4 bf16_rne4(f32x4 v) {
+    return __builtin_bit_cast(bf16x4, __builtin_convertvector(v, hw_bf16x4));
 }
 
 enum Epi { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_TANH = 2, EPI_TANH_GRAD = 3 };
 
-constexpr int TM = 64, TN = 64, TK = 16;
+constexpr int TM = 64, TN = 64, TK = 64;
+constexpr int LDK = TK + 8;   // LDS row stride in BF16 values: 36 words, so the 16 rows of an operand
+                              // read start at 16 different multiples of four banks
 
-// D(m, n) = epilogue( sum_k A(m, k) B(k, n) ) with A(m, k) = A[m*sam + k*sak] and
-// B(k, n) = B[k*sbk + n*sbn] (strides express transposes).  Epilogues: + bias[n]; tanh(+ bias);
-// times (1 - aux(m, n)^2) with aux row-major M x N (the tanh derivative from stored activations).
-// Block: 256 threads = 4 waves, 64x64 tile; each wave owns 32x32 = 2x2 MFMA tiles of 16x16.
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long sam, long sak, const float *__restrict__ B,
-                                              long sbk, long sbn, float *__restrict__ D, int M, int N, int K,
+// One thread's share of a 64 x 64 operand tile, as the four float4 it loads.  KC: the operand is
+// contiguous along k (element (r, k) at p[r * ld + k]) and the thread takes k4 .. k4+3 of rows
+// r0, r0+16, r0+32, r0+48.  Otherwise it is contiguous along the rows (element at p[k * ld + r]) and
+// the thread takes the 4 x 4 block of rows r0 .. r0+3 and k4 .. k4+3, v[i] holding k4 + i.
+// vec: ld and p allow 16-byte loads.  Values outside R x K are zero.
+template <bool KC>
+__device__ __forceinline__ void tile_load(f32x4 v[4], const float *__restrict__ p, long ld, int R, int K, int row, int k0,
+                                          bool vec) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = KC ? row + (t >> 4) + 16 * i : row + (t & 15) * 4;
+        const int k = KC ? k0 + (t & 15) * 4 : k0 + (t >> 4) * 4 + i;
+        const int n = KC ? (r < R ? K - k : 0) : (k < K ? R - r : 0);   // values left along the contiguous direction
+        const float *q = KC ? p + (long)r * ld + k : p + (long)k * ld + r;
+        if (vec && n >= 4) {
+            v[i] = *reinterpret_cast<const f32x4 *>(q);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[i][j] = j < n ? q[j] : 0.f;
+        }
+    }
+}
+template <bool KC> __device__ __forceinline__ void tile_store(short (*S)[LDK], const f32x4 v[4]) {
+    const int t = threadIdx.x;
+    if (KC) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<bf16x4 *>(&S[(t >> 4) + 16 * i][(t & 15) * 4]) = bf16_rne4(v[i]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<bf16x4 *>(&S[(t & 15) * 4 + j][(t >> 4) * 4]) =
+                bf16_rne4(f32x4{v[0][j], v[1][j], v[2][j], v[3][j]});
+    }
+}
+
+// D(m, n) = epilogue( sum_k A(m, k) B(k, n) ), operands rounded to BF16 while staged through LDS, FP32
+// accumulation in steps of 16 in the order of k.  AK / BK: A / B is contiguous along k (leading
+// dimension lda / ldb between rows m / columns n), else along m / n (leading dimension between k).
+// Epilogues: + bias[n]; tanh(+ bias); times (1 - aux(m, n)^2) with aux row-major M x N (the tanh
+// derivative from stored activations).
+// Block: 256 threads = 4 waves, 64 x 64 tile; each wave owns 32 x 32 = 2 x 2 MFMA tiles of 16 x 16.
+// These products are small (K of a few hundred, some tens of blocks), so a block's time is its chain
+// of dependent loads, not arithmetic or bandwidth: a trip takes 64 of k with eight 16-byte loads per
+// thread, issued before the previous trip's products, and one barrier (two LDS buffers).  Against a
+// trip of 16 of k with scalar loads and two barriers, same results bit for bit: the four products of
+// a 512-row forward pass of the 256-wide network 104 -> 31 us, one of 1000 x 1000 x 1000 78-152 -> about
+// 30 us.
+template <int EPI, bool AK, bool BK>
+__global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long lda, bool veca, const float *__restrict__ B,
+                                              long ldb, bool vecb, float *__restrict__ D, int M, int N, int K,
                                               const float *__restrict__ bias, const float *__restrict__ aux) {
-    __shared__ short As[TM][TK + 4];
-    __shared__ short Bs[TK][TN + 4];
+    __shared__ __align__(16) short As[2][TM][LDK];
+    __shared__ __align__(16) short Bs[2][TN][LDK];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
     const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
     f32x4 acc[2][2];
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += TK) {
-        // stage 64x16 of A and 16x64 of B as BF16 (4 elements per thread each), zero outside
-        for (int e = tid; e < TM * TK; e += 256) {
-            int mm = e / TK, kk = e % TK;
-            int m = m0 + mm, k = k0 + kk;
-            float v = (m < M && k < K) ? A[(long)m * sam + (long)k * sak] : 0.f;
-            As[mm][kk] = bf16_rne(v);
-        }
-        for (int e = tid; e < TK * TN; e += 256) {
-            int kk = e / TN, nn = e % TN;
-            int k = k0 + kk, n = n0 + nn;
-            float v = (k < K && n < N) ? B[(long)k * sbk + (long)n * sbn] : 0.f;
-            Bs[kk][nn] = bf16_rne(v);
-        }
+    f32x4 va[4], vb[4];
+    tile_load<AK>(va, A, lda, M, K, m0, 0, veca);
+    tile_load<BK>(vb, B, ldb, N, K, n0, 0, vecb);
+    for (int k0 = 0, s = 0; k0 < K; k0 += TK, s ^= 1) {
+        // buffer s was last read two trips ago, before the previous trip's barrier
+        tile_store<AK>(As[s], va);
+        tile_store<BK>(Bs[s], vb);
         __syncthreads();
+        if (k0 + TK < K) {
+            tile_load<AK>(va, A, lda, M, K, m0, k0 + TK, veca);
+            tile_load<BK>(vb, B, ldb, N, K, n0, k0 + TK, vecb);
+        }
         // operand layout of the 16x16x16 BF16 MFMA: lane l holds A(l%16, 4*(l/16)+0..3) and
         // B(4*(l/16)+0..3, l%16)
         const int r = lane & 15, kq = (lane >> 4) * 4;
-        bf16x4 a[2], b[2];
-        for (int i = 0; i < 2; ++i) {
-            const short *ap = &As[wm + 16 * i + r][kq];
-            a[i] = bf16x4{ap[0], ap[1], ap[2], ap[3]};
+#pragma unroll
+        for (int kk = 0; kk < TK; kk += 16) {
+            if (k0 + kk >= K) break;
+            bf16x4 a[2], b[2];
+            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x4 *>(&As[s][wm + 16 * i + r][kk + kq]);
+            for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const bf16x4 *>(&Bs[s][wn + 16 * j + r][kk + kq]);
+            for (int i = 0; i < 2; ++i)
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
         }
-        for (int j = 0; j < 2; ++j) {
-            const int c = wn + 16 * j + r;
-            b[j] = bf16x4{Bs[kq][c], Bs[kq + 1][c], Bs[kq + 2][c], Bs[kq + 3][c]};
-        }
-        for (int i = 0; i < 2; ++i)
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
-        __syncthreads();
     }
     // result layout: lane l holds D(4*(l/16)+q, l%16), q = 0..3
     const int c = lane & 15, rq = (lane >> 4) * 4;
@@ -104,7 +143,6 @@ __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long 
         }
 }
 
-// db[n] = sum over rows of dZ(m, n); one block per 64 columns, fixed summation order
 // zero n bytes (n a multiple of 4, 4-byte aligned): a kernel rather than a memset node, so a caller
 // may capture the calls that clear state into a graph
 __global__ __launch_bounds__(256) void k_zero(unsigned *__restrict__ p, size_t n_words) {
@@ -119,6 +157,7 @@ static hipError_t zero_async(void *p, size_t bytes, hipStream_t st) {
     return hipGetLastError();
 }
 
+// db[n] = sum over rows of dZ(m, n); one block per 64 columns, fixed summation order
 __global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ dZ, int M, int N, float *__restrict__ db) {
     __shared__ float part[4][64];
     const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
@@ -268,16 +307,21 @@ struct lb_mlp {
 
 namespace {
 
-hipError_t gemm(int epi, const float *A, long sam, long sak, const float *B, long sbk, long sbn, float *D, int M, int N,
-                int K, const float *bias, const float *aux, hipStream_t st) {
+template <int EPI, bool AK, bool BK>
+hipError_t gemm(const float *A, long lda, const float *B, long ldb, float *D, int M, int N, int K, const float *bias,
+                const float *aux, hipStream_t st) {
+    // 16-byte loads where every row (or k) of the operand starts on 16 bytes
+    auto vec = [](const float *p, long ld) { return ((uintptr_t)p & 15) == 0 && (ld & 3) == 0; };
     dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
-    switch (epi) {
-    case EPI_STORE: k_gemm<EPI_STORE><<<grid, 256, 0, st>>>(A, sam, sak, B, sbk, sbn, D, M, N, K, bias, aux); break;
-    case EPI_BIAS: k_gemm<EPI_BIAS><<<grid, 256, 0, st>>>(A, sam, sak, B, sbk, sbn, D, M, N, K, bias, aux); break;
-    case EPI_BIAS_TANH: k_gemm<EPI_BIAS_TANH><<<grid, 256, 0, st>>>(A, sam, sak, B, sbk, sbn, D, M, N, K, bias, aux); break;
-    default: k_gemm<EPI_TANH_GRAD><<<grid, 256, 0, st>>>(A, sam, sak, B, sbk, sbn, D, M, N, K, bias, aux); break;
-    }
+    k_gemm<EPI, AK, BK><<<grid, 256, 0, st>>>(A, lda, vec(A, lda), B, ldb, vec(B, ldb), D, M, N, K, bias, aux);
     return hipGetLastError();
+}
+
+// Z = in W^T + b over a batch (in: B x K, W: N x K, both row-major), tanh unless it is the last layer
+hipError_t layer_forward(bool last, const float *in, const float *W, const float *b, float *out, int B, int N, int K,
+                         hipStream_t st) {
+    return last ? gemm<EPI_BIAS, true, true>(in, K, W, K, out, B, N, K, b, nullptr, st)
+                : gemm<EPI_BIAS_TANH, true, true>(in, K, W, K, out, B, N, K, b, nullptr, st);
 }
 
 // ---- forward pass without allocation ------------------------------------------------------
@@ -313,8 +357,7 @@ int forward(lb_mlp *m, const float *X, int B) {
     for (int l = 0; l < lo.L; ++l) {
         const int K = lo.w[l], N = lo.w[l + 1];
         const float *W = m->P() + lo.oW[l], *b = m->P() + lo.oB[l];
-        // Z = A_prev W^T + b: A_prev(m, k) = in[m*K + k], B(k, n) = W[n*K + k]
-        HIPCHK(gemm(l + 1 < lo.L ? EPI_BIAS_TANH : EPI_BIAS, in, K, 1, W, 1, K, m->act(l), B, N, K, b, nullptr, m->stream));
+        HIPCHK(layer_forward(l + 1 == lo.L, in, W, b, m->act(l), B, N, K, m->stream));
         in = m->act(l);
     }
     return LB_OK;
@@ -334,13 +377,13 @@ int backward(lb_mlp *m, const float *X, const float *Y, int B) {
         const float *Aprev = l > 0 ? m->act(l - 1) : X;
         float *gW = m->G() + lo.oW[l], *gb = m->G() + lo.oB[l];
         // dW = dZ^T A_prev: A(m=n_out, k=row) = dZ[row*N + n_out], B(k=row, n=in) = Aprev[row*K + in]
-        HIPCHK(gemm(EPI_STORE, dZ, 1, N, Aprev, K, 1, gW, N, K, B, nullptr, nullptr, m->stream));
+        HIPCHK((gemm<EPI_STORE, false, false>(dZ, N, Aprev, K, gW, N, K, B, nullptr, nullptr, m->stream)));
         k_colsum<<<(N + 63) / 64, 256, 0, m->stream>>>(dZ, B, N, gb);
         HIPCHK(hipGetLastError());
         if (l > 0) {
             // dZ_prev = (dZ W) * (1 - A_prev^2): A(m=row, k=out) = dZ[row*N + out], B(k=out, n=in) = W[out*K + in]
             const float *W = m->P() + lo.oW[l];
-            HIPCHK(gemm(EPI_TANH_GRAD, dZ, N, 1, W, K, 1, dA, B, K, N, nullptr, Aprev, m->stream));
+            HIPCHK((gemm<EPI_TANH_GRAD, true, false>(dZ, N, W, K, dA, B, K, N, nullptr, Aprev, m->stream)));
             std::swap(dA, dZ);
         }
     }
@@ -486,7 +529,7 @@ int lb_mlp_forward_noalloc(const lb_mlp_config *cfg, const float *params, const 
         const float *W = params + off, *b = params + off + (size_t)N * K;
         off += (size_t)N * K + N;
         float *out = l + 1 < L ? buf + (size_t)(l & 1) * (kScratchFloats / 2) : Y;
-        HIPCHK(gemm(l + 1 < L ? EPI_BIAS_TANH : EPI_BIAS, in, K, 1, W, 1, K, out, batch, N, K, b, nullptr, st));
+        HIPCHK(layer_forward(l + 1 == L, in, W, b, out, batch, N, K, st));
         in = out;
     }
     return LB_OK;
@@ -495,7 +538,7 @@ int lb_mlp_forward_noalloc(const lb_mlp_config *cfg, const float *params, const 
 int lb_mlp_gemm_bf16(const float *A, const float *B, float *D, int32_t M, int32_t N, int32_t K, void *stream) {
     if (!A || !B || !D) return fail(LB_EINVAL, "NULL argument");
     if (M < 1 || N < 1 || K < 1) return fail(LB_EINVAL, "sizes must be positive");
-    HIPCHK(gemm(EPI_STORE, A, K, 1, B, N, 1, D, M, N, K, nullptr, nullptr, static_cast<hipStream_t>(stream)));
+    HIPCHK((gemm<EPI_STORE, true, false>(A, K, B, N, D, M, N, K, nullptr, nullptr, static_cast<hipStream_t>(stream))));
     return LB_OK;
 }
 

@@ -49,6 +49,30 @@ def test_gemm_bf16_matches_rounded_product(M, N, K):
     assert np.all(np.abs(D.cpu().numpy() - ref) <= K * 2.0 ** -24 * scale + 1e-30)
 
 
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 64), (65, 63, 65), (63, 66, 61), (128, 64, 129), (1, 1, 1), (130, 68, 192)])
+def test_gemm_bf16_tile_edges(M, N, K, offset):
+    """Sizes at and beside the 64 x 64 x 64 tile, from operands on a 16-byte boundary and 4 bytes past
+    one (which takes the scalar loads), against the product of the rounded operands."""
+    import torch
+    from paper_2209_14889_amd import mlp
+    rng = np.random.default_rng(M * 11 + N * 5 + K)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    B = rng.standard_normal((K, N)).astype(np.float32)
+
+    def dev(a):
+        buf = torch.empty(a.size + offset, dtype=torch.float32, device="cuda")
+        v = buf[offset:].view(*a.shape)
+        v.copy_(torch.from_numpy(a))
+        return v
+
+    D = mlp.gemm_bf16(dev(A), dev(B))
+    torch.cuda.synchronize()
+    scale = np.abs(bf16(A)) @ np.abs(bf16(B))
+    # FP32 accumulation of K exact BF16 x BF16 products: error <= K 2^-24 sum |a b|
+    assert np.all(np.abs(D.cpu().numpy() - bf16(A) @ bf16(B)) <= K * 2.0 ** -24 * scale + 1e-30)
+
+
 def _net(params, B=512):
     from paper_2209_14889_amd import mlp
     net = mlp.MLP(WIDTHS, B)
