@@ -36,26 +36,44 @@ constexpr int TM = 64, TN = 64, TK = 64;
 constexpr int LDK = TK + 8;   // LDS row stride in BF16 values: 36 words, so the 16 rows of an operand
                               // read start at 16 different multiples of four banks
 
+// Loads through a buffer resource return zero for an offset beyond its range, so what lies outside an
+// operand is loaded with kOut as its offset instead of being branched around: the loads of a trip
+// then issue back to back and stay in flight until their own values are used.
+constexpr unsigned kOut = 0xfffffff0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const float *p) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, 0x7fffffff, 0x00020000);
+}
+__device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+
 // One thread's share of a 64 x 64 operand tile, as the four float4 it loads.  KC: the operand is
 // contiguous along k (element (r, k) at p[r * ld + k]) and the thread takes k4 .. k4+3 of rows
 // r0, r0+16, r0+32, r0+48.  Otherwise it is contiguous along the rows (element at p[k * ld + r]) and
 // the thread takes the 4 x 4 block of rows r0 .. r0+3 and k4 .. k4+3, v[i] holding k4 + i.
-// vec: ld and p allow 16-byte loads.  Values outside R x K are zero.
-template <bool KC>
-__device__ __forceinline__ void tile_load(f32x4 v[4], const float *__restrict__ p, long ld, int R, int K, int row, int k0,
-                                          bool vec) {
+// VEC: p and ld, and with ld the extent along the contiguous direction, are multiples of four
+// floats.  Values outside R x K are zero.
+template <bool KC, bool VEC>
+__device__ __forceinline__ void tile_load(f32x4 v[4], const float *__restrict__ p, long ld, int R, int K, int row, int k0) {
     const int t = threadIdx.x;
+    // offsets are taken from the tile's corner: at most 64 rows (or k) of ld <= 4096 floats in the
+    // network, and of ld < 2^23 in lb_mlp_gemm_bf16
+    const __amdgpu_buffer_rsrc_t src = operand_rsrc(KC ? p + (long)row * ld + k0 : p + (long)k0 * ld + row);
+    const unsigned l = (unsigned)ld;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int r = KC ? row + (t >> 4) + 16 * i : row + (t & 15) * 4;
-        const int k = KC ? k0 + (t & 15) * 4 : k0 + (t >> 4) * 4 + i;
-        const int n = KC ? (r < R ? K - k : 0) : (k < K ? R - r : 0);   // values left along the contiguous direction
-        const float *q = KC ? p + (long)r * ld + k : p + (long)k * ld + r;
-        if (vec && n >= 4) {
-            v[i] = *reinterpret_cast<const f32x4 *>(q);
+        const int r = KC ? (t >> 4) + 16 * i : (t & 15) * 4;
+        const int k = KC ? (t & 15) * 4 : (t >> 4) * 4 + i;
+        const int n = KC ? (row + r < R ? K - k0 - k : 0) : (k0 + k < K ? R - row - r : 0);   // values left
+        const unsigned o = 4u * (KC ? (unsigned)r * l + (unsigned)k : (unsigned)k * l + (unsigned)r);
+        if (VEC) {
+            v[i] = load4(src, n > 0 ? o : kOut);
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[i][j] = j < n ? q[j] : 0.f;
+            for (int j = 0; j < 4; ++j) v[i][j] = load1(src, j < n ? o + 4u * j : kOut);
         }
     }
 }
@@ -84,9 +102,9 @@ template <bool KC> __device__ __forceinline__ void tile_store(short (*S)[LDK], c
 // trip of 16 of k with scalar loads and two barriers, same results bit for bit: the four products of
 // a 512-row forward pass of the 256-wide network 104 -> 31 us, one of 1000 x 1000 x 1000 78-152 -> about
 // 30 us.
-template <int EPI, bool AK, bool BK>
-__global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long lda, bool veca, const float *__restrict__ B,
-                                              long ldb, bool vecb, float *__restrict__ D, int M, int N, int K,
+template <int EPI, bool AK, bool BK, bool VEC>
+__global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long lda, const float *__restrict__ B, long ldb,
+                                              float *__restrict__ D, int M, int N, int K,
                                               const float *__restrict__ bias, const float *__restrict__ aux) {
     __shared__ __align__(16) short As[2][TM][LDK];
     __shared__ __align__(16) short Bs[2][TN][LDK];
@@ -97,16 +115,16 @@ __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long 
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 va[4], vb[4];
-    tile_load<AK>(va, A, lda, M, K, m0, 0, veca);
-    tile_load<BK>(vb, B, ldb, N, K, n0, 0, vecb);
+    tile_load<AK, VEC>(va, A, lda, M, K, m0, 0);
+    tile_load<BK, VEC>(vb, B, ldb, N, K, n0, 0);
     for (int k0 = 0, s = 0; k0 < K; k0 += TK, s ^= 1) {
         // buffer s was last read two trips ago, before the previous trip's barrier
         tile_store<AK>(As[s], va);
         tile_store<BK>(Bs[s], vb);
         __syncthreads();
         if (k0 + TK < K) {
-            tile_load<AK>(va, A, lda, M, K, m0, k0 + TK, veca);
-            tile_load<BK>(vb, B, ldb, N, K, n0, k0 + TK, vecb);
+            tile_load<AK, VEC>(va, A, lda, M, K, m0, k0 + TK);
+            tile_load<BK, VEC>(vb, B, ldb, N, K, n0, k0 + TK);
         }
         // operand layout of the 16x16x16 BF16 MFMA: lane l holds A(l%16, 4*(l/16)+0..3) and
         // B(4*(l/16)+0..3, l%16)
@@ -141,6 +159,166 @@ __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long 
                 D[(long)m * N + n] = v;
             }
         }
+}
+
+// ---- narrow networks: the whole pass in one launch --------------------------------------------
+// Networks whose layers are all at most kNarrow wide keep a block of rows' activations in LDS from
+// the first layer to the last.
+constexpr int kNarrow = 512;
+
+// LDS row stride in BF16 values for rows of n: 8 words more than a multiple of 64, so that the 16 rows
+// of an operand read spread over all banks
+constexpr __host__ __device__ int row_stride(int n) { return ((n + 127) & ~127) + 16; }
+
+constexpr int kWaves = 16;      // waves of a narrow-network block
+constexpr int kPanel = 128;     // k of the weights that a wave stages at a time
+
+struct Net {
+    int L;
+    int w[9];
+    int oW[8];      // offset of W_l in the parameters (b_l follows it)
+    int stride;     // LDS row stride of the activations in BF16 values (row_stride of the widest layer)
+};
+
+// Y = network(X) for 16 * RT rows per block.  Each of the 16 waves owns every 16th column tile of a
+// layer and stages that tile's weights itself: 16 rows x 128 of k at a time, loaded with 512
+// contiguous bytes per row and put into its own part of LDS as BF16 (the operand layout of the
+// product, 16 rows side by side in consecutive lanes, loaded directly costs four times the cache
+// lookups).  The next panel's loads (also across layers: weights wait for no activation) are in flight
+// during this one's products, and no barrier is needed but one a layer, for the activations, which
+// are handed on through two LDS buffers.  The first layer, whose few inputs need no 16-byte rows, takes
+// single loads.  The products, their order and the epilogues are those of k_gemm, so the results are
+// the same bits.
+// What bounds it: at a few hundred rows a chain of dependent steps (one round of loads per panel, and
+// the fetch of the code itself, which every launch starts cold: the same kernel unrolled to 8.4 KB of
+// code took 16-27 us for 512 rows, this form of 4.2 KB 13), at tens of thousands the tanh (about 40
+// instructions a value).
+// 512 rows of 5-256-256-256-64: 31 -> 13 us against a launch per layer; 65 536 rows 210 -> 90 us.
+template <int RT>
+__global__ __launch_bounds__(64 * kWaves) void k_forward(Net net, const float *__restrict__ P, const float *__restrict__ X,
+                                                         int B, float *__restrict__ Y) {
+    constexpr int LD = row_stride(kPanel), NL = kPanel / 16;   // loads per lane and panel
+    extern __shared__ __align__(16) short sAct[];   // [2][16 RT][stride], then [kWaves][16][LD]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g4 = (lane >> 4) * 4;
+    const int m0 = blockIdx.x * (16 * RT), L = net.L, S = net.stride;
+    short *const sW = sAct + 2 * (16 * RT) * S + wave * (16 * LD);
+
+    // the panels in the order this wave takes them (l == L: none left)
+    struct Panel {
+        int l, nt, kc, K, N;
+        const float *W;
+    };
+    auto first = [&](int l) {
+        while (l < L && 16 * wave >= net.w[l + 1]) ++l;
+        return l < L ? Panel{l, wave, 0, net.w[l], net.w[l + 1], P + net.oW[l]} : Panel{L, 0, 0, 0, 0, P};
+    };
+    auto after = [&](Panel p) {
+        if (p.kc + kPanel < p.K)
+            p.kc += kPanel;
+        else if (16 * (p.nt + kWaves) < p.N)
+            p.nt += kWaves, p.kc = 0;
+        else
+            p = first(p.l + 1);
+        return p;
+    };
+    // a panel of a layer after the first, zero outside it: a wave's load i covers whole rows of the
+    // panel; and the bias of the panel's tile
+    struct Weights {
+        float bias;
+        f32x4 w[NL];
+    };
+    const int row = lane / (kPanel / 4), quad = (lane % (kPanel / 4)) * 4;
+    auto issue = [&](const Panel &p) {
+        Weights b;
+        const __amdgpu_buffer_rsrc_t src = operand_rsrc(p.W + (long)p.nt * 16 * p.K + p.kc);
+        const int rows = p.kc + quad < p.K ? p.N - 16 * p.nt : 0;
+        b.bias = load1(operand_rsrc(p.W + (long)p.N * p.K), 16 * p.nt + r < p.N ? 4u * (unsigned)(16 * p.nt + r) : kOut);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int n = (256 / kPanel) * i + row;
+            b.w[i] = load4(src, n < rows ? 4u * (unsigned)(n * p.K + quad) : kOut);
+        }
+        return b;
+    };
+    Panel now = first(0);             // the panel to multiply next
+    Weights b = issue(first(1));      // in flight: that panel, or the first one after layer 0
+
+    {   // the rows of X as BF16, zero beyond the batch and up to the next multiple of 16 columns
+        const int K = net.w[0], KP = (K + 15) & ~15;
+#pragma unroll 1
+        for (int m = wave * 4 + (lane >> 4); m < 16 * RT; m += 4 * kWaves)
+#pragma unroll 1
+            for (int k = r; k < KP; k += 16) {
+                const float v = m0 + m < B && k < K ? X[(long)(m0 + m) * K + k] : 0.f;
+                sAct[m * S + k] = bf16_rne4(f32x4{v, v, v, v})[0];
+            }
+    }
+    f32x4 acc[RT];
+    int layer = -1;   // every wave has begun this layer
+    while (now.l < L) {
+        const Panel p = now;
+        now = after(p);
+#pragma unroll 1
+        for (; layer < p.l; ++layer) __syncthreads();
+        const short *in = sAct + (p.l & 1) * (16 * RT) * S + p.kc;
+        const int n = p.nt * 16 + r, steps = min(kPanel, p.K - p.kc);
+        float bias;
+        if (p.l == 0) {   // few inputs: single loads
+            const __amdgpu_buffer_rsrc_t src = operand_rsrc(p.W);
+            bias = load1(src, n < p.N ? 4u * (unsigned)(p.N * p.K + n) : kOut);
+#pragma unroll 1
+            for (int j = 0; j < steps; j += 16) {
+                f32x4 w;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    w[q] = load1(src, n < p.N && p.kc + j + g4 + q < p.K ? 4u * (unsigned)(n * p.K + p.kc + j + g4 + q) : kOut);
+                *reinterpret_cast<bf16x4 *>(sW + r * LD + j + g4) = bf16_rne4(w);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+                *reinterpret_cast<bf16x4 *>(sW + ((256 / kPanel) * i + row) * LD + quad) = bf16_rne4(b.w[i]);
+            bias = b.bias;
+            b = issue(now);
+        }
+        if (p.kc == 0)
+#pragma unroll
+            for (int t = 0; t < RT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+        for (int j = 0; j < steps; j += 16) {
+            const bf16x4 w = *reinterpret_cast<const bf16x4 *>(sW + r * LD + j + g4);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                const bf16x4 a = *reinterpret_cast<const bf16x4 *>(in + (16 * t + r) * S + j + g4);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, w, acc[t], 0, 0, 0);
+            }
+        }
+        if (p.kc + kPanel < p.K) continue;
+        if (p.l + 1 == L) {
+            if (n < p.N)
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int m = m0 + 16 * t + g4 + q;
+                        if (m < B) Y[(long)m * p.N + n] = acc[t][q] + bias;
+                    }
+            continue;
+        }
+        short *out = sAct + ((p.l + 1) & 1) * (16 * RT) * S;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            f32x4 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = n < p.N ? tanhf(acc[t][q] + bias) : 0.f;
+            const bf16x4 o = bf16_rne4(v);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out[(16 * t + g4 + q) * S + n] = o[q];
+        }
+    }
+#pragma unroll 1
+    for (; layer < L - 1; ++layer) __syncthreads();   // every wave meets every layer's barrier
 }
 
 // zero n bytes (n a multiple of 4, 4-byte aligned): a kernel rather than a memset node, so a caller
@@ -313,7 +491,10 @@ hipError_t gemm(const float *A, long lda, const float *B, long ldb, float *D, in
     // 16-byte loads where every row (or k) of the operand starts on 16 bytes
     auto vec = [](const float *p, long ld) { return ((uintptr_t)p & 15) == 0 && (ld & 3) == 0; };
     dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
-    k_gemm<EPI, AK, BK><<<grid, 256, 0, st>>>(A, lda, vec(A, lda), B, ldb, vec(B, ldb), D, M, N, K, bias, aux);
+    if (vec(A, lda) && vec(B, ldb))
+        k_gemm<EPI, AK, BK, true><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
+    else
+        k_gemm<EPI, AK, BK, false><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
     return hipGetLastError();
 }
 
@@ -322,6 +503,47 @@ hipError_t layer_forward(bool last, const float *in, const float *W, const float
                          hipStream_t st) {
     return last ? gemm<EPI_BIAS, true, true>(in, K, W, K, out, B, N, K, b, nullptr, st)
                 : gemm<EPI_BIAS_TANH, true, true>(in, K, W, K, out, B, N, K, b, nullptr, st);
+}
+
+// The network as the narrow kernels take it; false if it is not one for them: a layer too wide, or
+// rows of a weight matrix after the first that do not start on 16 bytes.
+bool narrow_net(int L, const int *w, const float *P, Net &net) {
+    if (*std::max_element(w, w + L + 1) > kNarrow) return false;
+    int o = 0;
+    net.L = L;
+    for (int l = 0; l < L; ++l) {
+        if (l > 0 && ((w[l] & 3) != 0 || ((uintptr_t)(P + o) & 15) != 0)) return false;
+        net.w[l] = w[l];
+        net.oW[l] = o;
+        o += w[l + 1] * w[l] + w[l + 1];
+    }
+    net.w[L] = w[L];
+    net.stride = row_stride(*std::max_element(w, w + L + 1));
+    return true;
+}
+
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + nb && y < x + na;
+}
+
+template <int RT> size_t narrow_lds(const Net &net) {
+    return (2 * (16 * RT) * (size_t)net.stride + kWaves * 16 * row_stride(kPanel)) * sizeof(short);
+}
+template <int RT> hipError_t forward_narrow(const Net &net, const float *P, const float *X, int B, float *Y, hipStream_t st) {
+    k_forward<RT><<<(B + 16 * RT - 1) / (16 * RT), 64 * kWaves, narrow_lds<RT>(net), st>>>(net, P, X, B, Y);
+    return hipGetLastError();
+}
+
+// Y = network(X) in one launch.  Rows per block: 16 while the blocks are at most one per compute
+// unit (each block reads every weight, so fewer rows a block only help while units are idle), then 32
+// and, where 64 rows' activations fit the 160 KB of LDS, 64, which halve and quarter the weight
+// traffic: 4096 rows take 14 us with 16 rows a block, 8192 rows 18 with 32 (22 with 64), 65 536 rows
+// 90 with 64 (124 with 32).
+hipError_t forward_narrow(const Net &net, const float *P, const float *X, int B, float *Y, hipStream_t st) {
+    if (B <= 16 * 256) return forward_narrow<1>(net, P, X, B, Y, st);
+    if (B <= 32 * 256 || narrow_lds<4>(net) > 160 * 1024) return forward_narrow<2>(net, P, X, B, Y, st);
+    return forward_narrow<4>(net, P, X, B, Y, st);
 }
 
 // ---- forward pass without allocation ------------------------------------------------------
@@ -460,9 +682,16 @@ int lb_mlp_get_params(lb_mlp *m, float *host) {
 int lb_mlp_forward(lb_mlp *m, const float *X, int32_t batch, float *Y) {
     if (!m || !X || !Y) return fail(LB_EINVAL, "NULL argument");
     if (batch < 1 || batch > m->cfg.max_batch) return fail(LB_ERANGE, "batch out of range");
+    const int NL = m->lo.w[m->lo.L];
+    Net net;
+    // (overlapping X and Y: the layers' own buffers keep Y unwritten until X has been read)
+    if (narrow_net(m->lo.L, m->lo.w.data(), m->P(), net) &&
+        !overlap(X, 4 * (size_t)batch * m->lo.w[0], Y, 4 * (size_t)batch * NL)) {
+        HIPCHK(forward_narrow(net, m->P(), X, batch, Y, m->stream));
+        return LB_OK;
+    }
     int rc = forward(m, X, batch);
     if (rc) return rc;
-    const int NL = m->lo.w[m->lo.L];
     HIPCHK(hipMemcpyAsync(Y, m->act(m->lo.L - 1), 4 * (size_t)batch * NL, hipMemcpyDeviceToDevice, m->stream));
     return LB_OK;
 }
@@ -518,10 +747,19 @@ int lb_mlp_forward_noalloc(const lb_mlp_config *cfg, const float *params, const 
     if ((size_t)batch * (size_t)wmax_hidden > kScratchFloats / 2)
         return fail(LB_ERANGE, "batch %d x hidden width %d exceeds the scratch limit of %zu values", batch, wmax_hidden,
                     kScratchFloats / 2);
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    Net net;
+    size_t n_params = 0;
+    for (int l = 0; l < L; ++l) n_params += (size_t)cfg->widths[l + 1] * (cfg->widths[l] + 1);
+    const size_t nY = 4 * (size_t)batch * cfg->widths[L];
+    if (narrow_net(L, cfg->widths, params, net) && !overlap(X, 4 * (size_t)batch * cfg->widths[0], Y, nY) &&
+        !overlap(params, 4 * n_params, Y, nY)) {
+        HIPCHK(forward_narrow(net, params, X, batch, Y, st));
+        return LB_OK;
+    }
     float *buf = nullptr;
     int rc = scratch_on_current_device(&buf);
     if (rc) return rc;
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const float *in = X;
     size_t off = 0;   // parameter offset of W_l
     for (int l = 0; l < L; ++l) {

@@ -73,6 +73,41 @@ def test_gemm_bf16_tile_edges(M, N, K, offset):
     assert np.all(np.abs(D.cpu().numpy() - bf16(A) @ bf16(B)) <= K * 2.0 ** -24 * scale + 1e-30)
 
 
+@pytest.mark.parametrize("widths,batch", [
+    ([5, 256, 256, 256, 64], 1), ([5, 256, 256, 256, 64], 17), ([5, 256, 256, 256, 64], 4097),
+    ([5, 256, 256, 256, 64], 8193 + 15), ([3, 512, 20, 512, 1], 33), ([130, 4], 5), ([7, 300, 100, 65], 70),
+    ([5, 384, 384, 16], 8200), ([5, 100, 513, 16], 40), ([5, 30, 40, 16], 40)])
+def test_one_launch_forward_is_the_layers_forward(widths, batch):
+    """The forward pass of narrow networks in one launch (both entry points, all three row counts per
+    block, ragged tiles and panels) against the same layers one launch each, which a call whose output
+    overlaps its input takes: the same bits.  The last two networks (a layer too wide, rows not on 16
+    bytes) take the layers in every call."""
+    import torch
+    from paper_2209_14889_amd import lb, mlp
+    params = mlp.init_params(widths, 31)
+    rng, o = np.random.default_rng(batch), 0
+    for a, b in zip(widths[:-1], widths[1:]):
+        o += a * b
+        params[o:o + b] = rng.uniform(-0.1, 0.1, b)
+        o += b
+    X = torch.from_numpy(rng.uniform(-1, 1, (batch, widths[0])).astype(np.float32)).cuda()
+    net = mlp.MLP(widths, batch)
+    net.set_params(params)
+    Y = net.forward(X).cpu().numpy()
+    if batch * max(widths[1:-1], default=0) <= 1 << 19:
+        Yn = torch.empty((batch, widths[-1]), dtype=torch.float32, device="cuda")
+        mlp.forward_noalloc(widths, torch.from_numpy(params).cuda(), X, Yn)
+        torch.cuda.synchronize()
+        assert np.array_equal(Yn.cpu().numpy(), Y)
+    both = torch.empty(batch * max(widths[0], widths[-1]), dtype=torch.float32, device="cuda")
+    both[:X.numel()] = X.flatten()
+    torch.cuda.synchronize()
+    lb.check(mlp.lib().lb_mlp_forward(net.h, mlp._dev(both), batch, mlp._dev(both)))
+    net.stream.synchronize()
+    assert np.array_equal(both[:Y.size].cpu().numpy().reshape(Y.shape), Y)
+    net.close()
+
+
 def _net(params, B=512):
     from paper_2209_14889_amd import mlp
     net = mlp.MLP(WIDTHS, B)
