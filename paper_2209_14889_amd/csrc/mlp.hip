@@ -13,6 +13,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lb.h"
@@ -90,28 +91,27 @@ template <bool KC> __device__ __forceinline__ void tile_store(short (*S)[LDK], c
     }
 }
 
-// D(m, n) = epilogue( sum_k A(m, k) B(k, n) ), operands rounded to BF16 while staged through LDS, FP32
-// accumulation in steps of 16 in the order of k.  AK / BK: A / B is contiguous along k (leading
-// dimension lda / ldb between rows m / columns n), else along m / n (leading dimension between k).
-// Epilogues: + bias[n]; tanh(+ bias); times (1 - aux(m, n)^2) with aux row-major M x N (the tanh
-// derivative from stored activations).
-// Block: 256 threads = 4 waves, 64 x 64 tile; each wave owns 32 x 32 = 2 x 2 MFMA tiles of 16 x 16.
+struct Stage {   // the two LDS buffers of both operands' tiles
+    short a[2][TM][LDK], b[2][TN][LDK];
+};
+
+// acc = this wave's 32 x 32 part of the 64 x 64 tile at (m0, n0) of sum_k A(m, k) B(k, n), operands
+// rounded to BF16 while staged through LDS, FP32 accumulation in steps of 16 in the order of k.
+// AK / BK: A / B is contiguous along k (leading dimension lda / ldb between rows m / columns n), else
+// along m / n (leading dimension between k).
+// Block: 256 threads = 4 waves, each with 2 x 2 MFMA tiles of 16 x 16.
 // These products are small (K of a few hundred, some tens of blocks), so a block's time is its chain
 // of dependent loads, not arithmetic or bandwidth: a trip takes 64 of k with eight 16-byte loads per
 // thread, issued before the previous trip's products, and one barrier (two LDS buffers).  Against a
 // trip of 16 of k with scalar loads and two barriers, same results bit for bit: the four products of
 // a 512-row forward pass of the 256-wide network 104 -> 31 us, one of 1000 x 1000 x 1000 78-152 -> about
 // 30 us.
-template <int EPI, bool AK, bool BK, bool VEC>
-__global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long lda, const float *__restrict__ B, long ldb,
-                                              float *__restrict__ D, int M, int N, int K,
-                                              const float *__restrict__ bias, const float *__restrict__ aux) {
-    __shared__ __align__(16) short As[2][TM][LDK];
-    __shared__ __align__(16) short Bs[2][TN][LDK];
+template <bool AK, bool BK, bool VEC>
+__device__ __forceinline__ void product_tile(Stage &S, f32x4 acc[2][2], const float *__restrict__ A, long lda,
+                                             const float *__restrict__ B, long ldb, int M, int N, int K, int m0,
+                                             int n0) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
     const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-    f32x4 acc[2][2];
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 va[4], vb[4];
@@ -119,8 +119,8 @@ __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long 
     tile_load<BK, VEC>(vb, B, ldb, N, K, n0, 0);
     for (int k0 = 0, s = 0; k0 < K; k0 += TK, s ^= 1) {
         // buffer s was last read two trips ago, before the previous trip's barrier
-        tile_store<AK>(As[s], va);
-        tile_store<BK>(Bs[s], vb);
+        tile_store<AK>(S.a[s], va);
+        tile_store<BK>(S.b[s], vb);
         __syncthreads();
         if (k0 + TK < K) {
             tile_load<AK, VEC>(va, A, lda, M, K, m0, k0 + TK);
@@ -133,21 +133,34 @@ __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long 
         for (int kk = 0; kk < TK; kk += 16) {
             if (k0 + kk >= K) break;
             bf16x4 a[2], b[2];
-            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x4 *>(&As[s][wm + 16 * i + r][kk + kq]);
-            for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const bf16x4 *>(&Bs[s][wn + 16 * j + r][kk + kq]);
+            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x4 *>(&S.a[s][wm + 16 * i + r][kk + kq]);
+            for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const bf16x4 *>(&S.b[s][wn + 16 * j + r][kk + kq]);
             for (int i = 0; i < 2; ++i)
                 for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
         }
     }
+}
+
+// D(m, n) = epilogue(product).  Epilogues: + bias[n]; tanh(+ bias); times (1 - aux(m, n)^2) with aux
+// row-major M x N (the tanh derivative from stored activations).
+template <int EPI, bool AK, bool BK, bool VEC>
+__global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long lda, const float *__restrict__ B, long ldb,
+                                              float *__restrict__ D, int M, int N, int K,
+                                              const float *__restrict__ bias, const float *__restrict__ aux) {
+    __shared__ __align__(16) Stage S;
+    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
+    f32x4 acc[2][2];
+    product_tile<AK, BK, VEC>(S, acc, A, lda, B, ldb, M, N, K, m0, n0);
     // result layout: lane l holds D(4*(l/16)+q, l%16), q = 0..3
-    const int c = lane & 15, rq = (lane >> 4) * 4;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int c = n0 + (wv & 1) * 32 + (lane & 15), rq = m0 + (wv >> 1) * 32 + (lane >> 4) * 4;
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) {
-            const int n = n0 + wn + 16 * j + c;
+            const int n = c + 16 * j;
             if (n >= N) continue;
             for (int q = 0; q < 4; ++q) {
-                const int m = m0 + wm + 16 * i + rq + q;
+                const int m = rq + 16 * i + q;
                 if (m >= M) continue;
                 float v = acc[i][j][q];
                 if (EPI == EPI_BIAS || EPI == EPI_BIAS_TANH) v += bias[n];
@@ -159,6 +172,170 @@ __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long 
                 D[(long)m * N + n] = v;
             }
         }
+}
+
+// ---- weight gradients -----------------------------------------------------------------------
+// One layer's share of k_weights: dW = dZ^T A over the batch and db = column sums of dZ.
+struct LayerGrad {
+    const float *dZ, *A;   // batch x N, batch x K
+    long oW;               // of W and then b in the parameter-shaped arrays
+    int N, K, vec;
+    int tile0, tn;         // first block, and blocks along K
+};
+struct Grads {
+    LayerGrad l[8];
+    int n, blocks;         // layers; blocks of all of them (one more takes the mean loss)
+};
+struct Adam {
+    float *p, *m1, *m2;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam_update(const Adam &o, float gi, float &p, float &m1, float &m2) {
+    float a = o.b1 * m1 + (1.0f - o.b1) * gi;
+    float b = o.b2 * m2 + (1.0f - o.b2) * gi * gi;
+    m1 = a;
+    m2 = b;
+    p -= o.lr * (a / o.c1) / (sqrtf(b / o.c2) + o.eps);
+}
+
+// Every layer's weight and bias gradients in one launch, a 32 x 32 tile of one layer per block, and
+// with STEP the Adam update of the parameters on the spot (the gradients then need no memory); else
+// they go to G.  Half the threads load 4 x 4 blocks of dZ, the other half of A, 64 rows of the batch
+// a trip, transposed in registers; each of the four waves multiplies 16 x 16 in the order of the
+// rows.  The first block along K of each layer also sums its columns of dZ, each thread the values it
+// loads anyway, then the 16 threads of a column in a fixed order.  The last block takes the mean of
+// the rows' losses.
+// Bounded by the chain of loads over the batch and the fetch of its code: hence one small tile a wave
+// (a 64 x 64 tile's 16 values a lane cost 15 KB of unrolled update), and more blocks than units.
+// A training step of 256 rows of the 256-wide network: 134 us in 19 launches -> 39 us in three
+// (k_forward 15, k_backward 13, this 9).
+constexpr int WT = 32;
+template <bool STEP>
+__global__ __launch_bounds__(256) void k_weights(Grads gr, int batch, float *__restrict__ G, Adam adam,
+                                                 const float *__restrict__ rows, float *__restrict__ loss) {
+    __shared__ __align__(16) short S[2][2][WT][LDK];   // [buffer][dZ, A]
+    __shared__ float part[16 * WT];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if ((int)blockIdx.x >= gr.blocks) {
+        float s = 0.f;
+        for (int i = tid; i < batch; i += 256) s += rows[i];
+        part[tid] = s;
+        __syncthreads();
+#pragma unroll 1
+        for (int w = 128; w > 0; w >>= 1) {
+            if (tid < w) part[tid] += part[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) *loss = part[0] / (float)batch;
+        return;
+    }
+    int q = 0;
+#pragma unroll 1
+    while (q + 1 < gr.n && (int)blockIdx.x >= gr.l[q + 1].tile0) ++q;
+    const LayerGrad &l = gr.l[q];
+    const int t = blockIdx.x - l.tile0, N = l.N, K = l.K, m0 = (t / l.tn) * WT, n0 = (t % l.tn) * WT;
+
+    // this wave's operand: dZ (columns from m0) or A (columns from n0)
+    const int half = wv >> 1, u = tid & 127, c4 = (u & 7) * 4, k4 = (u >> 3) * 4;
+    const int ld = half ? K : N, left = ld - (half ? n0 : m0) - c4;
+    const float *src = (half ? l.A + n0 : l.dZ + m0);
+    const int wm = (wv >> 1) * 16, wn = (wv & 1) * 16, r = lane & 15, g4 = (lane >> 4) * 4;
+    f32x4 acc{0.f, 0.f, 0.f, 0.f}, sum{0.f, 0.f, 0.f, 0.f};
+    auto products = [&](auto vec) {
+        f32x4 v[4];
+        auto load = [&](int k0) {
+            const __amdgpu_buffer_rsrc_t b = operand_rsrc(src + (long)k0 * ld);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned o = 4u * ((unsigned)(k4 + i) * (unsigned)ld + (unsigned)c4);
+                const int n = k0 + k4 + i < batch ? left : 0;
+                if (vec) {
+                    v[i] = load4(b, n > 0 ? o : kOut);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[i][j] = load1(b, j < n ? o + 4u * j : kOut);
+                }
+            }
+        };
+        load(0);
+#pragma unroll 1
+        for (int k0 = 0, s = 0; k0 < batch; k0 += TK, s ^= 1) {
+            // buffer s was last read two trips ago, before the previous trip's barrier
+            sum += (v[0] + v[1]) + (v[2] + v[3]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<bf16x4 *>(&S[s][half][c4 + j][k4]) = bf16_rne4(f32x4{v[0][j], v[1][j], v[2][j], v[3][j]});
+            __syncthreads();
+            if (k0 + TK < batch) load(k0 + TK);
+#pragma unroll
+            for (int kk = 0; kk < TK; kk += 16) {
+                if (k0 + kk >= batch) break;
+                const bf16x4 a = *reinterpret_cast<const bf16x4 *>(&S[s][0][wm + r][kk + g4]);
+                const bf16x4 b = *reinterpret_cast<const bf16x4 *>(&S[s][1][wn + r][kk + g4]);
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+            }
+        }
+    };
+    if (l.vec)
+        products(std::true_type{});
+    else
+        products(std::false_type{});
+    float *const out = STEP ? adam.p : G;
+    auto put = [&](const bool in[4], const long at[4], f32x4 g) {
+        if (!STEP) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (in[i]) out[at[i]] = g[i];
+            return;
+        }
+        float p[4], m1[4], m2[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const long o = in[i] ? at[i] : 0;
+            p[i] = adam.p[o];
+            m1[i] = adam.m1[o];
+            m2[i] = adam.m2[o];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            adam_update(adam, g[i], p[i], m1[i], m2[i]);
+            if (in[i]) {
+                adam.p[at[i]] = p[i];
+                adam.m1[at[i]] = m1[i];
+                adam.m2[at[i]] = m2[i];
+            }
+        }
+    };
+    bool in[4];
+    long at[4];
+    f32x4 g = acc;
+#pragma unroll 1
+    for (int pass = 0;; ++pass) {   // the tile's weights, then (first blocks only) its biases
+        if (pass == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = m0 + wm + g4 + i, n = n0 + wn + r;
+                in[i] = m < N && n < K;
+                at[i] = l.oW + (long)m * K + n;
+            }
+        } else {
+            const int m = m0 + (tid & (WT - 1));
+            float s = 0.f;
+#pragma unroll 1
+            for (int k = 0; k < 16; ++k) s += part[k * WT + (tid & (WT - 1))];
+            g = f32x4{s, 0.f, 0.f, 0.f};
+            in[0] = tid < WT && m < N;
+            in[1] = in[2] = in[3] = false;
+            at[0] = l.oW + (long)N * K + m;
+        }
+        put(in, at, g);
+        if (n0 != 0 || pass == 1) break;
+        if (half == 0)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[(u >> 3) * WT + c4 + j] = sum[j];
+        __syncthreads();
+    }
 }
 
 // ---- narrow networks: the whole pass in one launch --------------------------------------------
@@ -194,9 +371,13 @@ struct Net {
 // code took 16-27 us for 512 rows, this form of 4.2 KB 13), at tens of thousands the tanh (about 40
 // instructions a value).
 // 512 rows of 5-256-256-256-64: 31 -> 13 us against a launch per layer; 65 536 rows 210 -> 90 us.
-template <int RT>
+// KEEP: every hidden layer's activations are also stored, in FP32, for the backward pass.
+struct Kept {
+    float *act[8];
+};
+template <int RT, bool KEEP>
 __global__ __launch_bounds__(64 * kWaves) void k_forward(Net net, const float *__restrict__ P, const float *__restrict__ X,
-                                                         int B, float *__restrict__ Y) {
+                                                         int B, float *__restrict__ Y, Kept kept) {
     constexpr int LD = row_stride(kPanel), NL = kPanel / 16;   // loads per lane and panel
     extern __shared__ __align__(16) short sAct[];   // [2][16 RT][stride], then [kWaves][16][LD]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -314,7 +495,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_forward(Net net, const float *_
             for (int q = 0; q < 4; ++q) v[q] = n < p.N ? tanhf(acc[t][q] + bias) : 0.f;
             const bf16x4 o = bf16_rne4(v);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) out[(16 * t + g4 + q) * S + n] = o[q];
+            for (int q = 0; q < 4; ++q) {
+                const int m = 16 * t + g4 + q;
+                out[m * S + n] = o[q];
+                if (KEEP && n < p.N && m0 + m < B) kept.act[p.l][(long)(m0 + m) * p.N + n] = v[q];
+            }
         }
     }
 #pragma unroll 1
@@ -335,23 +520,11 @@ static hipError_t zero_async(void *p, size_t bytes, hipStream_t st) {
     return hipGetLastError();
 }
 
-// db[n] = sum over rows of dZ(m, n); one block per 64 columns, fixed summation order
-__global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ dZ, int M, int N, float *__restrict__ db) {
-    __shared__ float part[4][64];
-    const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + c;
-    float s = 0.f;
-    if (n < N)
-        for (int m = g; m < M; m += 4) s += dZ[(long)m * N + n];
-    part[g][c] = s;
-    __syncthreads();
-    if (g == 0 && n < N) db[n] = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
-}
-
-// per row i: r_i = |yhat_i - y_i|^2 / |y_i|^2; dYhat = 2 (yhat - y) / (|y|^2 batch); row loss out
-__global__ __launch_bounds__(64) void k_rel_loss(const float *__restrict__ Yh, const float *__restrict__ Y, int B, int N,
-                                                 float *__restrict__ dY, float *__restrict__ row_loss) {
-    const int i = blockIdx.x, l = threadIdx.x;
+// one wave, row i: returns r_i = |yhat_i - y_i|^2 / |y_i|^2 and hands put(n, dYhat) the gradient
+// dYhat = 2 (yhat - y) / (|y|^2 batch)
+template <typename Put>
+__device__ __forceinline__ float rel_loss_row(const float *Yh, const float *__restrict__ Y, int i, int B, int N, Put put) {
+    const int l = threadIdx.x & 63;
     float e2 = 0.f, y2 = 0.f;
     for (int n = l; n < N; n += 64) {
         float d = Yh[(long)i * N + n] - Y[(long)i * N + n];
@@ -364,35 +537,138 @@ __global__ __launch_bounds__(64) void k_rel_loss(const float *__restrict__ Yh, c
         y2 += __shfl_xor(y2, o);
     }
     const float inv = 1.0f / fmaxf(y2, 1e-30f);
-    for (int n = l; n < N; n += 64)
-        dY[(long)i * N + n] = 2.0f * (Yh[(long)i * N + n] - Y[(long)i * N + n]) * inv / (float)B;
-    if (l == 0) row_loss[i] = e2 * inv;
+    for (int n = l; n < N; n += 64) put(n, 2.0f * (Yh[(long)i * N + n] - Y[(long)i * N + n]) * inv / (float)B);
+    return e2 * inv;
 }
 
-__global__ __launch_bounds__(256) void k_mean(const float *__restrict__ v, int n, float *__restrict__ out) {
-    __shared__ float part[256];
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n; i += 256) s += v[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
+// dY may be Yh itself
+__global__ __launch_bounds__(64) void k_rel_loss(const float *Yh, const float *__restrict__ Y, int B, int N, float *dY,
+                                                 float *__restrict__ row_loss) {
+    const int i = blockIdx.x;
+    const float r = rel_loss_row(Yh, Y, i, B, N, [&](int n, float v) { dY[(long)i * N + n] = v; });
+    if (threadIdx.x == 0) row_loss[i] = r;
+}
+
+// The gradients of every layer's pre-activations for 16 rows per block, from the stored activations:
+// dZ of the last layer from the loss, then dZ_{l-1} = (dZ_l W_l) (1 - A_{l-1}^2) down to the first,
+// each stored in FP32 for k_weights and handed on in LDS as the next product's BF16 operand.  Built
+// like k_forward (waves, panels, prefetch, barriers); W_l is read along its rows (64 bytes of 16
+// columns per k) and transposed 4 x 4 in registers.
+struct Chain {
+    const float *act[8];   // A_l (batch x w[l+1]), l < L - 1
+    float *dz[8];          // dZ_l (batch x w[l+1]); dz[L-1] holds the network's output on entry
+};
+__global__ __launch_bounds__(64 * kWaves) void k_backward(Net net, Chain ch, const float *__restrict__ P,
+                                                          const float *__restrict__ Y, int B, float *__restrict__ rows) {
+    constexpr int LD = row_stride(kPanel);
+    extern __shared__ __align__(16) short sAct[];   // [2][16][stride], then [kWaves][16][LD]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g4 = (lane >> 4) * 4;
+    const int m0 = blockIdx.x * 16, L = net.L, S = net.stride;
+    short *const sW = sAct + 2 * 16 * S + wave * (16 * LD);
+
+    // the panels in the order this wave takes them: layer l from L-1 down to 1, column tile nt of its
+    // K inputs, 128 of its N outputs (l == 0: none left)
+    struct Panel {
+        int l, nt, kc, K, N;
+        const float *W;
+    };
+    auto first = [&](int l) {
+        while (l > 0 && 16 * wave >= net.w[l]) --l;
+        return l > 0 ? Panel{l, wave, 0, net.w[l], net.w[l + 1], P + net.oW[l]} : Panel{0, 0, 0, 0, 0, P};
+    };
+    auto after = [&](Panel p) {
+        if (p.kc + kPanel < p.N)
+            p.kc += kPanel;
+        else if (16 * (p.nt + kWaves) < p.K)
+            p.nt += kWaves, p.kc = 0;
+        else
+            p = first(p.l - 1);
+        return p;
+    };
+    struct Weights {
+        f32x4 w[8];   // two 4 x 4 blocks: w[4 h + i] row kc + 64 h + 4 (lane / 4) + i, columns 4 (lane % 4) ..
+    };
+    const int k4 = (lane >> 2) * 4, c4 = (lane & 3) * 4;
+    auto issue = [&](const Panel &p) {
+        Weights b;
+        const __amdgpu_buffer_rsrc_t src = operand_rsrc(p.W + (long)p.kc * p.K + 16 * p.nt);
+        const int rowsLeft = 16 * p.nt + c4 < p.K ? p.N - p.kc : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int k = 64 * (i >> 2) + k4 + (i & 3);
+            b.w[i] = load4(src, k < rowsLeft ? 4u * (unsigned)(k * p.K + c4) : kOut);
+        }
+        return b;
+    };
+    Panel now = first(L - 1);
+    Weights b = issue(now);
+
+    {   // one wave a row: the loss and dZ of the last layer, zero beyond the batch and the layer
+        const int N = net.w[L], NP = (N + 15) & ~15, i = m0 + wave;
+        short *o = sAct + ((L - 1) & 1) * 16 * S + wave * S;
+#pragma unroll 1
+        for (int n = lane; n < NP; n += 64) o[n] = 0;
+        if (i < B) {
+            float *dz = ch.dz[L - 1];
+            const float v = rel_loss_row(dz, Y, i, B, N, [&](int n, float g) {
+                dz[(long)i * N + n] = g;
+                o[n] = bf16_rne4(f32x4{g, g, g, g})[0];
+            });
+            if (lane == 0) rows[i] = v;
+        }
     }
-    if (threadIdx.x == 0) *out = part[0] / (float)n;
+    f32x4 acc;
+    int layer = L;   // every wave has begun this layer
+    while (now.l > 0) {
+        const Panel p = now;
+        now = after(p);
+#pragma unroll 1
+        for (; layer > p.l; --layer) __syncthreads();
+        const short *in = sAct + (p.l & 1) * 16 * S + p.kc;
+        const int n = 16 * p.nt + r, steps = min(kPanel, p.N - p.kc);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<bf16x4 *>(sW + (c4 + j) * LD + 64 * h + k4) =
+                    bf16_rne4(f32x4{b.w[4 * h][j], b.w[4 * h + 1][j], b.w[4 * h + 2][j], b.w[4 * h + 3][j]});
+        float a[4];
+        {
+            const __amdgpu_buffer_rsrc_t src = operand_rsrc(ch.act[p.l - 1] + (long)m0 * p.K);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                a[q] = load1(src, n < p.K && m0 + g4 + q < B ? 4u * (unsigned)((g4 + q) * p.K + n) : kOut);
+        }
+        b = issue(now);
+        if (p.kc == 0) acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+        for (int j = 0; j < steps; j += 16) {
+            const bf16x4 w = *reinterpret_cast<const bf16x4 *>(sW + r * LD + j + g4);
+            const bf16x4 d = *reinterpret_cast<const bf16x4 *>(in + r * S + j + g4);
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(d, w, acc, 0, 0, 0);
+        }
+        if (p.kc + kPanel < p.N) continue;
+        f32x4 v;
+        float *dz = ch.dz[p.l - 1];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[q] = acc[q] * (1.0f - a[q] * a[q]);
+            if (n >= p.K) v[q] = 0.f;
+            if (n < p.K && m0 + g4 + q < B) dz[(long)(m0 + g4 + q) * p.K + n] = v[q];
+        }
+        short *out = sAct + ((p.l - 1) & 1) * 16 * S;
+        const bf16x4 o = bf16_rne4(v);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[(g4 + q) * S + n] = o[q];
+    }
+#pragma unroll 1
+    for (; layer > 1; --layer) __syncthreads();   // every wave meets every layer's barrier
 }
 
-__global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m1,
-                                              float *__restrict__ m2, long n, float lr, float b1, float b2, float eps,
-                                              float c1, float c2) {
-    long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float gi = g[i];
-    float a = b1 * m1[i] + (1.0f - b1) * gi;
-    float b = b2 * m2[i] + (1.0f - b2) * gi * gi;
-    m1[i] = a;
-    m2[i] = b;
-    p[i] -= lr * (a / c1) / (sqrtf(b / c2) + eps);
+__global__ __launch_bounds__(256) void k_adam(Adam o, const float *__restrict__ g, long n) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) adam_update(o, g[i], o.p[i], o.m1[i], o.m2[i]);
 }
 
 int fail(int code, const char *fmt, ...) {
@@ -415,7 +691,10 @@ struct Layout {
     std::vector<int> w;
     std::vector<size_t> oW, oB;   // offsets (floats) of W_l and b_l in the parameter array
     size_t n_params = 0, acts = 0;
-    size_t bytes = 0, oP = 0, oG = 0, oM1 = 0, oM2 = 0, oAct = 0, oGrad = 0, oRow = 0, oLoss = 0;
+    size_t bytes = 0;       // of the arena
+    size_t least = 0;       // what an arena needs to be usable at all: two gradient buffers instead of
+                            // one per hidden layer, and so a launch per layer in the backward pass
+    size_t oP = 0, oG = 0, oM1 = 0, oM2 = 0, oAct = 0, oGrad = 0, oRow = 0, oLoss = 0;
 };
 
 int layout(const lb_mlp_config *c, Layout &lo) {
@@ -444,10 +723,12 @@ int layout(const lb_mlp_config *c, Layout &lo) {
     lo.oM2 = o; o += al(4 * off);
     lo.oAct = o; o += al(4 * acts * (size_t)c->max_batch);           // activations of every layer
     size_t wmax = *std::max_element(lo.w.begin(), lo.w.end());
-    lo.oGrad = o; o += al(4 * 2 * wmax * (size_t)c->max_batch);      // two gradient buffers
     lo.oRow = o; o += al(4 * (size_t)c->max_batch);
     lo.oLoss = o; o += al(4);
-    lo.bytes = o + 256;
+    const size_t hidden = acts - (size_t)lo.w[lo.L];
+    lo.oGrad = o;                                                    // gradient buffers
+    lo.least = o + al(4 * 2 * wmax * (size_t)c->max_batch) + 256;
+    lo.bytes = o + al(4 * std::max(2 * wmax, hidden) * (size_t)c->max_batch) + 256;
     return LB_OK;
 }
 
@@ -460,6 +741,7 @@ struct lb_mlp {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     long step = 0;
+    bool room = true;   // a gradient buffer per layer
     // waits for the stream and releases it if the library created it (also when lb_mlp_create
     // fails part way); the arena belongs to the caller
     ~lb_mlp() {
@@ -478,6 +760,12 @@ struct lb_mlp {
     float *grad(int i) {
         size_t wmax = *std::max_element(lo.w.begin(), lo.w.end());
         return reinterpret_cast<float *>(base + lo.oGrad) + (size_t)i * wmax * cfg.max_batch;
+    }
+    // gradient of layer l's pre-activations, with room for one per layer: the last one's takes the place
+    // of the network's output
+    float *dz(int l) {
+        if (l + 1 == lo.L) return act(l);
+        return reinterpret_cast<float *>(base + lo.oGrad) + (act(l) - act(0));
     }
     float *rows() { return reinterpret_cast<float *>(base + lo.oRow); }
     float *loss() { return reinterpret_cast<float *>(base + lo.oLoss); }
@@ -531,7 +819,7 @@ template <int RT> size_t narrow_lds(const Net &net) {
     return (2 * (16 * RT) * (size_t)net.stride + kWaves * 16 * row_stride(kPanel)) * sizeof(short);
 }
 template <int RT> hipError_t forward_narrow(const Net &net, const float *P, const float *X, int B, float *Y, hipStream_t st) {
-    k_forward<RT><<<(B + 16 * RT - 1) / (16 * RT), 64 * kWaves, narrow_lds<RT>(net), st>>>(net, P, X, B, Y);
+    k_forward<RT, false><<<(B + 16 * RT - 1) / (16 * RT), 64 * kWaves, narrow_lds<RT>(net), st>>>(net, P, X, B, Y, Kept{});
     return hipGetLastError();
 }
 
@@ -572,7 +860,7 @@ int scratch_on_current_device(float **out) {
     return LB_OK;
 }
 
-// forward into the activation buffers; returns the output pointer (batch x w[L])
+// forward into the activation buffers, a launch per layer
 int forward(lb_mlp *m, const float *X, int B) {
     const Layout &lo = m->lo;
     const float *in = X;
@@ -585,29 +873,80 @@ int forward(lb_mlp *m, const float *X, int B) {
     return LB_OK;
 }
 
-// gradients of the mean squared relative error into G(); loss of the batch into loss()
-int backward(lb_mlp *m, const float *X, const float *Y, int B) {
+// one layer's entry of k_weights' work, its blocks after those already there
+void add_layer(Grads &g, lb_mlp *m, int l, const float *dZ, const float *A) {
+    const int N = m->lo.w[l + 1], K = m->lo.w[l];
+    auto vec = [](const float *p, int ld) { return ((uintptr_t)p & 15) == 0 && (ld & 3) == 0; };
+    const int tn = (K + WT - 1) / WT;
+    g.l[g.n++] = LayerGrad{dZ, A, (long)m->lo.oW[l], N, K, vec(dZ, N) && vec(A, K), g.blocks, tn};
+    g.blocks += tn * ((N + WT - 1) / WT);
+}
+
+// Forward pass, loss and gradients of the mean squared relative error: with `adam` the update of the
+// parameters, else the gradients in G().  The mean loss goes to `loss`.
+// Narrow networks: three launches (k_forward, k_backward, k_weights).  Others: a launch per layer and
+// direction, then k_weights.  An arena with two gradient buffers only: each layer's weight gradients as
+// soon as its dZ is there, and the update at the end.
+int gradients(lb_mlp *m, const float *X, const float *Y, int B, const Adam *adam, float *loss) {
     const Layout &lo = m->lo;
     const int L = lo.L, NL = lo.w[L];
+    Net net;
+    Grads g{};
+    if (m->room) {
+        if (narrow_net(L, lo.w.data(), m->P(), net)) {
+            Kept kept{};
+            Chain ch{};
+            for (int l = 0; l < L; ++l) {
+                kept.act[l] = m->act(l);
+                ch.act[l] = m->act(l);
+                ch.dz[l] = m->dz(l);
+            }
+            k_forward<1, true><<<(B + 15) / 16, 64 * kWaves, narrow_lds<1>(net), m->stream>>>(net, m->P(), X, B, m->act(L - 1),
+                                                                                            kept);
+            HIPCHK(hipGetLastError());
+            k_backward<<<(B + 15) / 16, 64 * kWaves, narrow_lds<1>(net), m->stream>>>(net, ch, m->P(), Y, B, m->rows());
+            HIPCHK(hipGetLastError());
+        } else {
+            int rc = forward(m, X, B);
+            if (rc) return rc;
+            k_rel_loss<<<B, 64, 0, m->stream>>>(m->act(L - 1), Y, B, NL, m->dz(L - 1), m->rows());
+            HIPCHK(hipGetLastError());
+            for (int l = L - 1; l > 0; --l) {
+                // dZ_prev = (dZ W) * (1 - A_prev^2): A(m=row, k=out) = dZ[row*N + out], B(k=out, n=in) = W[out*K + in]
+                const int K = lo.w[l], N = lo.w[l + 1];
+                HIPCHK((gemm<EPI_TANH_GRAD, true, false>(m->dz(l), N, m->P() + lo.oW[l], K, m->dz(l - 1), B, K, N, nullptr,
+                                                         m->act(l - 1), m->stream)));
+            }
+        }
+        for (int l = 0; l < L; ++l) add_layer(g, m, l, m->dz(l), l > 0 ? m->act(l - 1) : X);
+        if (adam)
+            k_weights<true><<<g.blocks + 1, 256, 0, m->stream>>>(g, B, nullptr, *adam, m->rows(), loss);
+        else
+            k_weights<false><<<g.blocks + 1, 256, 0, m->stream>>>(g, B, m->G(), Adam{}, m->rows(), loss);
+        HIPCHK(hipGetLastError());
+        return LB_OK;
+    }
+    int rc = forward(m, X, B);
+    if (rc) return rc;
     float *dA = m->grad(0), *dZ = m->grad(1);
     k_rel_loss<<<B, 64, 0, m->stream>>>(m->act(L - 1), Y, B, NL, dZ, m->rows());
-    HIPCHK(hipGetLastError());
-    k_mean<<<1, 256, 0, m->stream>>>(m->rows(), B, m->loss());
     HIPCHK(hipGetLastError());
     for (int l = L - 1; l >= 0; --l) {
         const int K = lo.w[l], N = lo.w[l + 1];
         const float *Aprev = l > 0 ? m->act(l - 1) : X;
-        float *gW = m->G() + lo.oW[l], *gb = m->G() + lo.oB[l];
-        // dW = dZ^T A_prev: A(m=n_out, k=row) = dZ[row*N + n_out], B(k=row, n=in) = Aprev[row*K + in]
-        HIPCHK((gemm<EPI_STORE, false, false>(dZ, N, Aprev, K, gW, N, K, B, nullptr, nullptr, m->stream)));
-        k_colsum<<<(N + 63) / 64, 256, 0, m->stream>>>(dZ, B, N, gb);
+        g = Grads{};
+        add_layer(g, m, l, dZ, Aprev);
+        k_weights<false><<<g.blocks + 1, 256, 0, m->stream>>>(g, B, m->G(), Adam{}, m->rows(), loss);
         HIPCHK(hipGetLastError());
         if (l > 0) {
-            // dZ_prev = (dZ W) * (1 - A_prev^2): A(m=row, k=out) = dZ[row*N + out], B(k=out, n=in) = W[out*K + in]
-            const float *W = m->P() + lo.oW[l];
-            HIPCHK((gemm<EPI_TANH_GRAD, true, false>(dZ, N, W, K, dA, B, K, N, nullptr, Aprev, m->stream)));
+            HIPCHK((gemm<EPI_TANH_GRAD, true, false>(dZ, N, m->P() + lo.oW[l], K, dA, B, K, N, nullptr, Aprev, m->stream)));
             std::swap(dA, dZ);
         }
+    }
+    if (adam) {
+        const long n = (long)lo.n_params;
+        k_adam<<<(unsigned)((n + 255) / 256), 256, 0, m->stream>>>(*adam, m->G(), n);
+        HIPCHK(hipGetLastError());
     }
     return LB_OK;
 }
@@ -641,7 +980,8 @@ int lb_mlp_create(const lb_mlp_config *cfg, void *arena, size_t arena_bytes, voi
         std::unique_ptr<lb_mlp> m(new lb_mlp());
         int rc = layout(cfg, m->lo);
         if (rc) return rc;
-        if (arena_bytes < m->lo.bytes) return fail(LB_ENOMEM, "arena too small: %zu < %zu", arena_bytes, m->lo.bytes);
+        if (arena_bytes < m->lo.least) return fail(LB_ENOMEM, "arena too small: %zu < %zu", arena_bytes, m->lo.bytes);
+        m->room = arena_bytes >= m->lo.bytes;
         m->cfg = *cfg;
         if (m->cfg.beta1 == 0.f) m->cfg.beta1 = 0.9f;
         if (m->cfg.beta2 == 0.f) m->cfg.beta2 = 0.999f;
@@ -699,9 +1039,7 @@ int lb_mlp_forward(lb_mlp *m, const float *X, int32_t batch, float *Y) {
 int lb_mlp_gradients(lb_mlp *m, const float *X, const float *Y, int32_t batch, float *host_loss, float *host_grads) {
     if (!m || !X || !Y) return fail(LB_EINVAL, "NULL argument");
     if (batch < 1 || batch > m->cfg.max_batch) return fail(LB_ERANGE, "batch out of range");
-    int rc = forward(m, X, batch);
-    if (rc) return rc;
-    rc = backward(m, X, Y, batch);
+    int rc = gradients(m, X, Y, batch, nullptr, m->loss());
     if (rc) return rc;
     if (host_loss) HIPCHK(hipMemcpyAsync(host_loss, m->loss(), 4, hipMemcpyDeviceToHost, m->stream));
     if (host_grads) HIPCHK(hipMemcpyAsync(host_grads, m->G(), 4 * m->lo.n_params, hipMemcpyDeviceToHost, m->stream));
@@ -712,18 +1050,12 @@ int lb_mlp_gradients(lb_mlp *m, const float *X, const float *Y, int32_t batch, f
 int lb_mlp_train_step(lb_mlp *m, const float *X, const float *Y, int32_t batch, float lr, float *device_loss) {
     if (!m || !X || !Y) return fail(LB_EINVAL, "NULL argument");
     if (batch < 1 || batch > m->cfg.max_batch) return fail(LB_ERANGE, "batch out of range");
-    int rc = forward(m, X, batch);
-    if (rc) return rc;
-    rc = backward(m, X, Y, batch);
+    const float step = (float)(m->step + 1);
+    const Adam adam{m->P(), m->M1(), m->M2(), lr, m->cfg.beta1, m->cfg.beta2, m->cfg.eps,
+                    1.0f - std::pow(m->cfg.beta1, step), 1.0f - std::pow(m->cfg.beta2, step)};
+    int rc = gradients(m, X, Y, batch, &adam, device_loss ? device_loss : m->loss());
     if (rc) return rc;
     m->step += 1;
-    const float c1 = 1.0f - std::pow(m->cfg.beta1, (float)m->step);
-    const float c2 = 1.0f - std::pow(m->cfg.beta2, (float)m->step);
-    const long n = (long)m->lo.n_params;
-    k_adam<<<(unsigned)((n + 255) / 256), 256, 0, m->stream>>>(m->P(), m->G(), m->M1(), m->M2(), n, lr, m->cfg.beta1,
-                                                               m->cfg.beta2, m->cfg.eps, c1, c2);
-    HIPCHK(hipGetLastError());
-    if (device_loss) HIPCHK(hipMemcpyAsync(device_loss, m->loss(), 4, hipMemcpyDeviceToDevice, m->stream));
     return LB_OK;
 }
 

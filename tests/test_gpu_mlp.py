@@ -229,6 +229,54 @@ def test_gradients_match_oracle():
     net.close()
 
 
+@pytest.mark.parametrize("widths,batch", [
+    ([5, 256, 256, 256, 64], 256), ([5, 256, 256, 256, 64], 1), ([5, 64, 64, 64, 16], 65), ([7, 300, 100, 65], 70),
+    ([3, 512, 20, 512, 1], 33), ([130, 36], 17), ([5, 30, 30, 30, 16], 40), ([16, 520, 520, 520, 33], 100)])
+def test_gradients_in_three_launches_and_layer_by_layer(widths, batch):
+    """Gradients and one training step with an arena that holds a gradient buffer per layer (narrow
+    networks: three launches; the last two networks: a launch per layer, then all weight gradients)
+    against an arena of the least accepted size (two gradient buffers, a launch per layer): the same
+    products in the same order, so the same gradients bit for bit; and against the oracle network with
+    the same operand rounding.  The update differs at most by the rounding of about ten operations on
+    a step of size lr, and of the new parameter."""
+    import ctypes
+
+    import torch
+    from paper_2209_14889_amd import lb, mlp
+    params = mlp.init_params(widths, 41)
+    rng = np.random.default_rng(42)
+    X = rng.uniform(-1, 1, (batch, widths[0])).astype(np.float32)
+    Y = rng.uniform(0.5, 1.5, (batch, widths[-1])).astype(np.float32)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    full = mlp.MLP(widths, batch)
+    wmax = max(widths)
+    hidden = sum(widths[1:-1])
+    less = 4 * max(0, hidden - 2 * wmax) * batch // 256 * 256
+    small = mlp.MLP(widths, batch)
+    lb.check(mlp.lib().lb_mlp_destroy(small.h))
+    h = ctypes.c_void_p()
+    lb.check(mlp.lib().lb_mlp_create(ctypes.byref(small.cfg), mlp._dev(small.arena),
+                                     ctypes.c_size_t(small.arena.numel() - less),
+                                     ctypes.c_void_p(small.stream.cuda_stream), ctypes.byref(h)))
+    small.h = h
+    out = []
+    lr = 1e-3
+    for net in (full, small):
+        net.set_params(params)
+        loss, g = net.gradients(Xd, Yd)
+        net.train_step(Xd, Yd, lr)
+        out.append((loss, g, net.get_params()))
+        net.close()
+    assert out[0][0] == out[1][0]
+    assert np.array_equal(out[0][1], out[1][1])
+    u = 2.0 ** -24
+    assert np.all(np.abs(out[0][2].astype(np.float64) - out[1][2]) <= 16 * u * lr + u * np.abs(out[1][2]))
+    assert rel(out[0][1], omlp.gradients(params, widths, X, Y, mb.bf16)) < 2e-3
+    Yh = omlp.forward(params, widths, X, mb.bf16)[-1]
+    loss = np.mean(np.sum((Yh - Y) ** 2, axis=1) / np.sum(Y.astype(np.float64) ** 2, axis=1))
+    assert abs(out[0][0] - loss) < 2e-3 * loss
+
+
 def test_first_adam_step_follows_its_definition():
     import torch
     from paper_2209_14889_amd import mlp
