@@ -104,7 +104,10 @@ typedef struct {
     int32_t timing;             /* 1: time every field-kernel launch with HIP events */
     int32_t seg_rows;           /* rows per fused work item; 0 = tuned default */
     int32_t fused_threads;      /* fused work-group size: 64, 128 or 256 (strip of 56, 120 or 248
-                                   columns); 0 = chosen from the lattice width */
+                                   columns, or a tile of as many sites); 0 = chosen from the lattice
+                                   width.  Items of 4 to 8 rows (16 with 256 threads) of a launch with few of
+                                   them are tiles, whose rows are computed at once; other items march
+                                   down their rows.  Both give the same bits */
     int32_t autotune;           /* 1: time candidate (work-group size, rows per item, grid) shapes on
                                    the live state in lb_create and keep the fastest; 0: cost model */
     int32_t grid;               /* fused work-groups launched: 0 = one per work item; > 0 = a

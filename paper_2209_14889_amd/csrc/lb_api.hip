@@ -188,12 +188,14 @@ struct Plan {
     std::vector<BodyPlan> bodies;
     std::vector<double> clamps;
     std::vector<size_t> oTab;
-    size_t oSims, oBodies, oItems, oIbBlk, oSiteBlk, oT, oStatus, oPartial, oOut, oOutAll, oStage;
+    size_t oSims, oBodies, oItems, oTiles, oIbBlk, oSiteBlk, oT, oStatus, oPartial, oOut, oOutAll, oStage;
     std::vector<WorkItem> items;
     std::vector<int2> ib_blk;
     std::vector<SiteBlock> site_blk;
     int T = 256;
     int max_partial = 1;
+    size_t max_tiles = 0;
+    size_t least = 0;   // arena bytes without the table of tiles: short items then march like long ones
     size_t bytes = 0;
 };
 
@@ -335,6 +337,18 @@ int pick_threads(const lb_sim_params *sims, int n_sims, const Opt &o) {
     return mx <= 120 ? 128 : 256;
 }
 
+// Items of kTileMinRows .. tile_rows(T) rows are tiles (k_tile): the columns of a lattice are cut evenly
+// into as few of at most tile_width(T, rows) as it takes.
+constexpr int kTileMinRows = 4;
+constexpr size_t kMaxTiles = 8192;   // more never pay (tiles_pay)
+int tiles_across(int nx, int T, int rows) { return (nx + tile_width(T, rows) - 1) / tile_width(T, rows); }
+
+size_t count_tiles(const std::vector<SimPlan> &sims, int T, int rows) {
+    size_t n = 0;
+    for (const SimPlan &sp : sims) n += (size_t)tiles_across(sp.nx, T, rows) * (size_t)((sp.ny + rows - 1) / rows);
+    return n;
+}
+
 Plan make_plan(const lb_sim_params *sims, int n_sims, const Opt &o) {
     Plan pl;
     Arena a;
@@ -413,6 +427,11 @@ Plan make_plan(const lb_sim_params *sims, int n_sims, const Opt &o) {
     pl.oOut = a.take(sizeof(double) * 16);
     pl.oOutAll = a.take(sizeof(double) * kBodyOut * std::max(1, total_bodies));
     pl.oStage = a.take(10 * maxN * 4);
+    pl.least = a.off + 256;
+    for (int T : {64, 128, 256})
+        for (int rows = kTileMinRows; rows <= tile_rows(T); ++rows)
+            pl.max_tiles = std::max(pl.max_tiles, std::min(count_tiles(pl.sims, T, rows), kMaxTiles));
+    pl.oTiles = a.take(sizeof(WorkItem) * pl.max_tiles);
     pl.bytes = a.off + 256;
     return pl;
 }
@@ -455,6 +474,30 @@ std::vector<WorkItem> build_items(const std::vector<SimPlan> &sims, int T, int s
     return items;
 }
 
+// Whether items of `rows` rows go as tiles.  A tile is a short chain (6.5-9 us for any lattice whose
+// tiles are all resident at once, where marching items take 17-23), but computes more halo: from about
+// seven tiles a compute unit on, items marching down their rows win (FP32, no bodies, tiles against the
+// best marching shape: 512^2, 4 tiles a unit, 14.1 against 21 us; 640^2, 6.3 a unit, 21.0 against
+// 21.4; 32 lattices of 128^2, 8 a unit, 22.5 against 21.1; 768^2, 9 a unit, 26.1 against 25.8; 900^2,
+// 12.8 a unit, 34.4 against 30.3).
+bool tiles_pay(const std::vector<SimPlan> &sims, int T, int rows, int cus) {
+    return rows >= kTileMinRows && rows <= tile_rows(T) && count_tiles(sims, T, rows) <= 7 * (size_t)cus;
+}
+
+std::vector<WorkItem> build_tiles(const std::vector<SimPlan> &sims, int T, int rows) {
+    std::vector<WorkItem> items;
+    for (size_t s = 0; s < sims.size(); ++s) {
+        const int nx = sims[s].nx, ny = sims[s].ny, na = tiles_across(nx, T, rows), nd = (ny + rows - 1) / rows;
+        for (int g = 0; g < nd; ++g)
+            for (int k = 0; k < na; ++k) {
+                const int x0 = (int)((long)k * nx / na), x1 = (int)((long)(k + 1) * nx / na);
+                const int y0 = (int)((long)g * ny / nd), y1 = (int)((long)(g + 1) * ny / nd);
+                items.push_back(WorkItem{(int)s, x0, y0, x1 - x0, y1 - y0, 0, 0, 0});
+            }
+    }
+    return items;
+}
+
 // cost model of one fused launch: work items run in rounds of `slots` resident work-groups and
 // an item of seg rows takes seg + 8 row iterations (the pipeline fill)
 int model_seg(const std::vector<SimPlan> &sims, int T, int slots) {
@@ -489,6 +532,8 @@ struct lb_handle {
     SimDev *d_sims = nullptr;
     BodyDev *d_bodies = nullptr;
     WorkItem *d_items = nullptr;
+    WorkItem *d_tiles = nullptr;   // nullptr: the arena has no room for them
+    bool tiles = false;            // the items are tiles
     int2 *d_ib = nullptr;
     SiteBlock *d_site = nullptr;
     int *d_t = nullptr;
@@ -587,6 +632,16 @@ int drain_timing(lb_handle *h) {
     return LB_OK;
 }
 
+// the field pass of one step on the current items (fused kernels)
+hipError_t launch_field(lb_handle *h) {
+    const bool fp16 = h->opt.precision == 1;
+    if (h->tiles)
+        return launch_tile(h->fused_T, fp16, h->any_walls, h->any_pol, h->stream, h->d_sims, h->d_bodies, h->d_tiles, h->n_items,
+                           h->cur, h->d_t);
+    return launch_fused(h->fused_T, fp16, h->any_walls, h->any_pol, h->fused_grid, h->stream, h->d_sims, h->d_bodies, h->d_items,
+                        h->n_items, h->cur, h->d_t, h->cus);
+}
+
 // launch one step's kernels (field pass + node update); parity flips
 int launch_step(lb_handle *h, bool timed) {
     const bool fp16 = h->opt.precision == 1;
@@ -598,8 +653,7 @@ int launch_step(lb_handle *h, bool timed) {
         HIPCHK(hipEventRecord(a, h->stream));
     }
     if (h->opt.kernel == 0) {
-        HIPCHK(launch_fused(h->fused_T, fp16, h->any_walls, h->any_pol, h->fused_grid, h->stream, h->d_sims, h->d_bodies, h->d_items,
-                            h->n_items, h->cur, h->d_t, h->cus));
+        HIPCHK(launch_field(h));
     } else {
         HIPCHK(launch_multipass(fp16, (int)h->plan.site_blk.size(), h->stream, h->d_sims, h->d_bodies, h->d_site,
                                 h->cur, h->d_t));
@@ -747,7 +801,17 @@ int place_body_items(lb_handle *h, std::vector<WorkItem> &items) {
 // grid: 0 = one work-group per item; > 0 = persistent grid of that many work-groups (a multiple
 // of 8, so each XCD keeps a contiguous run of items) looping over the item table
 int upload_items(lb_handle *h, int T, int seg, int grid = 0) {
-    std::vector<WorkItem> items = build_items(h->plan.sims, T, seg);
+    h->tiles = grid <= 0 && h->d_tiles && tiles_pay(h->plan.sims, T, seg, h->cus);
+    if (h->tiles && count_tiles(h->plan.sims, T, seg) > h->plan.max_tiles) h->tiles = false;
+    std::vector<WorkItem> items = h->tiles ? build_tiles(h->plan.sims, T, seg) : build_items(h->plan.sims, T, seg);
+    if (h->tiles) {
+        HIPCHK(hipMemcpyAsync(h->d_tiles, items.data(), sizeof(WorkItem) * items.size(), hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipStreamSynchronize(h->stream));
+        h->fused_T = T;
+        h->fused_seg = seg;
+        h->n_items = h->fused_grid = (int)items.size();
+        return LB_OK;
+    }
     if (items.size() > h->plan.items.size()) return fail(LB_EINVAL, "internal: work-item table overflow");
     if (grid <= 0 || grid >= (int)items.size()) {
         const int rc = place_body_items(h, items);
@@ -846,8 +910,23 @@ int choose_fused_config(lb_handle *h) {
         for (const auto &sp : h->plan.sims) mx = std::max(mx, sp.nx);
         return mx <= 64 ? 64 : mx <= 128 ? 128 : 256;
     };
+    // A lattice small enough to be tiles: 4-row tiles of that width's work-group while they give a SIMD at
+    // most two waves (more and shorter chains: 64^2 6.4 us with 128 lanes and 4 rows, 7.5 with 8), else
+    // 256 lanes and 8 rows, which compute less halo.
+    auto model_tiles = [&](int &T, int &rows) {
+        if (h->opt.seg || h->opt.grid || !h->d_tiles) return false;
+        T = model_T();
+        rows = kTileMinRows;
+        if (count_tiles(h->plan.sims, T, rows) * (size_t)(T / 64) <= 8 * (size_t)cus && tiles_pay(h->plan.sims, T, rows, h->cus))
+            return true;
+        T = h->opt.threads ? T : 256;
+        rows = 8;
+        return tiles_pay(h->plan.sims, T, rows, h->cus);
+    };
     if (!h->opt.autotune) {
-        int T = model_T();
+        int T = 0, rows = 0;
+        if (model_tiles(T, rows)) return upload_items(h, T, rows);
+        T = model_T();
         int seg = h->opt.seg ? h->opt.seg : model_seg(h->plan.sims, T, cus * fused_blocks_per_cu(T, fp16, h->any_walls, h->any_pol));
         return upload_items(h, T, seg, h->opt.grid);
     }
@@ -865,6 +944,10 @@ int choose_fused_config(lb_handle *h) {
         bool operator==(const Cand &o) const { return T == o.T && seg == o.seg && grid == o.grid; }
     };
     std::vector<Cand> cand;
+    {
+        int T = 0, rows = 0;
+        if (model_tiles(T, rows)) cand.push_back(Cand{T, rows, 0});
+    }
     for (int T : {64, 128, 256}) {
         if (h->opt.threads && T != h->opt.threads) continue;
         int slots = cus * fused_blocks_per_cu(T, fp16, h->any_walls, h->any_pol);
@@ -895,8 +978,7 @@ int choose_fused_config(lb_handle *h) {
         int rc = upload_items(h, cand.front().T, cand.front().seg, cand.front().grid);
         if (rc) return rc;
         for (int r = 0; r < 30; ++r)
-            HIPCHK(launch_fused(cand.front().T, fp16, h->any_walls, h->any_pol, h->fused_grid, h->stream, h->d_sims, h->d_bodies,
-                                h->d_items, h->n_items, h->cur, h->d_t, h->cus));
+            HIPCHK(launch_field(h));
     }
     std::vector<float> tbest(cand.size(), 1e30f);
     for (int pass = 0; pass < 2; ++pass) {
@@ -904,12 +986,10 @@ int choose_fused_config(lb_handle *h) {
             const Cand c = cand[ci];
             int rc = upload_items(h, c.T, c.seg, c.grid);
             if (rc) return rc;
-            HIPCHK(launch_fused(c.T, fp16, h->any_walls, h->any_pol, h->fused_grid, h->stream, h->d_sims, h->d_bodies, h->d_items,
-                                h->n_items, h->cur, h->d_t, h->cus));
+            HIPCHK(launch_field(h));
             HIPCHK(hipEventRecord(e0, h->stream));
             for (int r = 0; r < 8; ++r)
-                HIPCHK(launch_fused(c.T, fp16, h->any_walls, h->any_pol, h->fused_grid, h->stream, h->d_sims, h->d_bodies, h->d_items,
-                                    h->n_items, h->cur, h->d_t, h->cus));
+                HIPCHK(launch_field(h));
             HIPCHK(hipEventRecord(e1, h->stream));
             HIPCHK(hipEventSynchronize(e1));
             float ms = 0;
@@ -1020,7 +1100,7 @@ static int create_impl(const lb_sim_params *sims, int n_sims, const lb_options *
     for (int s = 0; s < n_sims; ++s) h->any_walls = h->any_walls || sims[s].walls != 0;
     h->opt = o;
     h->plan = make_plan(sims, n_sims, o);
-    if (arena_bytes < h->plan.bytes)
+    if (arena_bytes < h->plan.least)
         return fail(LB_ENOMEM, "arena too small: %zu bytes given, %zu needed", arena_bytes, h->plan.bytes);
     h->arena = static_cast<char *>(arena);
     if (stream) {
@@ -1045,6 +1125,7 @@ static int create_impl(const lb_sim_params *sims, int n_sims, const lb_options *
     h->d_sims = A.ptr<SimDev>(pl.oSims);
     h->d_bodies = A.ptr<BodyDev>(pl.oBodies);
     h->d_items = A.ptr<WorkItem>(pl.oItems);
+    if (arena_bytes >= pl.bytes) h->d_tiles = A.ptr<WorkItem>(pl.oTiles);
     h->d_ib = A.ptr<int2>(pl.oIbBlk);
     h->d_site = A.ptr<SiteBlock>(pl.oSiteBlk);
     h->d_t = A.ptr<int>(pl.oT);

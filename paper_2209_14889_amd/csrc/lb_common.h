@@ -16,6 +16,21 @@ constexpr int kStiffSeg = 64;       // stiffness-table segments over s = |P|^2 i
 constexpr int kHalo = 4;            // fused kernel: polarization halo depth (stress and h use 3)
 constexpr int kDefaultShift = 10;   // FP16 storage: offsets scaled by 2^10
 
+// Tiles (short work items, k_tile): a work-group of T threads takes at most tile_rows(T) rows, and as many
+// columns as make one site a thread, at most tile_cols(T).  tile_cap: the most sites any such tile has
+// with its halo, `halo` more in each direction.
+constexpr int tile_rows(int T) { return T == 256 ? 16 : 8; }
+constexpr int tile_cols(int T) { return T / 8; }
+constexpr int tile_width(int T, int rows) { return T / rows < tile_cols(T) ? T / rows : tile_cols(T); }
+constexpr int tile_cap(int T, int halo) {
+    int most = 0;
+    for (int l = 1; l <= tile_rows(T); ++l) {
+        const int n = (tile_width(T, l) + halo) * (l + halo);
+        most = n > most ? n : most;
+    }
+    return most;
+}
+
 // status bits raised by kernels, read by the host at synchronising calls
 constexpr int kStatusPatch = 1;     // a body outgrew its force/velocity patch
 constexpr int kStatusUnstable = 2;  // watchdog: non-finite or drifting mass

@@ -126,14 +126,25 @@ template <> struct Pop<__half> {
     static constexpr bool kScaled = true;
 };
 
+// The field kernels share this arithmetic and give the same bits at every site.  Where an expression
+// leaves the compiler a choice of what to fuse (which of two products goes into the multiply-add, or
+// whether a product's result is added rounded), the choice is written out.
+__device__ __forceinline__ float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
 // ---- BGK collision with Guo forcing (eqBGK, Sec. II B force coupling) --------------------
 // In: pre-collision offsets d[9], force F.  Out: post-collision offsets in d, and the
 // force-corrected velocity u = (sum c h + F/2)/rho, drho = rho - 1.  SCALED: d in and out are
 // the offsets times `scale`, the power of two of the FP16 storage, so the stored words are
 // converted without a multiply (every rescaling by a power of two is exact).
+// collide_terms leaves the last multiply-add to the caller, d' = keep d + r: next to the FP16 store the
+// conversion is fused with it (one rounding), which every kernel must do alike.
 template <bool SCALED>
-__device__ __forceinline__ void collide_t(float d[9], float Fx, float Fy, float omega, float guo, float scale,
-                                          float inv_scale, float &drho, float &ux, float &uy) {
+__device__ __forceinline__ void collide_terms(const float d[9], float Fx, float Fy, float omega, float guo, float scale,
+                                              float inv_scale, float r[9], float &keep, float &drho, float &ux,
+                                              float &uy) {
     const float up = d[5] + d[6], dn = d[7] + d[8];   // the diagonal pairs with c_y = +1, -1
     drho = ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + up) + dn);
     float jx = (d[1] - d[3]) + (d[5] - d[6]) + (d[8] - d[7]);
@@ -160,20 +171,29 @@ __device__ __forceinline__ void collide_t(float d[9], float Fx, float Fy, float 
     const float orho = omega * rho;
     const float a1 = 3.0f * orho, a2 = 4.5f * orho, b1 = 3.0f * guo, b2 = 9.0f * guo;
     const float C0 = omega * drho - orho * uu15 - b1 * uF;
-    const float keep = 1.0f - omega;
+    keep = 1.0f - omega;
     const float ws = SCALED ? kW[1] * scale : kW[1], wd = SCALED ? kW[5] * scale : kW[5];
-    d[0] = fmaf(keep, d[0], (SCALED ? kW[0] * scale : kW[0]) * C0);
+    r[0] = (SCALED ? kW[0] * scale : kW[0]) * C0;
     auto pair = [&](int n, int m, float t, float g, float w) {   // m: the direction opposite to n
         const float E = fmaf(t, fmaf(a2, t, b2 * g), C0);
         const float O = fmaf(a1, t, b1 * g);
-        const float wE = w * E, wO = w * O;
-        d[n] = fmaf(keep, d[n], wE + wO);
-        d[m] = fmaf(keep, d[m], wE - wO);
+        const float wE = w * E;
+        r[n] = fmaf(w, O, wE);
+        r[m] = fmaf(-w, O, wE);
     };
     pair(1, 3, ux, Fx, ws);
     pair(2, 4, uy, Fy, ws);
-    pair(5, 7, ux + uy, Fx + Fy, wd);
-    pair(6, 8, uy - ux, Fy - Fx, wd);
+    pair(5, 7, add_rounded(ux, uy), Fx + Fy, wd);
+    pair(6, 8, add_rounded(uy, -ux), Fy - Fx, wd);
+}
+
+template <bool SCALED>
+__device__ __forceinline__ void collide_t(float d[9], float Fx, float Fy, float omega, float guo, float scale,
+                                          float inv_scale, float &drho, float &ux, float &uy) {
+    float r[9], keep;
+    collide_terms<SCALED>(d, Fx, Fy, omega, guo, scale, inv_scale, r, keep, drho, ux, uy);
+#pragma unroll
+    for (int n = 0; n < 9; ++n) d[n] = fmaf(keep, d[n], r[n]);
 }
 
 __device__ __forceinline__ void collide(float d[9], float Fx, float Fy, float omega, float guo,
@@ -233,7 +253,7 @@ __device__ __forceinline__ void stiff_apply(const SimDev &S, const Stiff &k, flo
     float C23 = k.w - k.r;
     o0 = C11 * a + C12 * b + C13 * c;
     o1 = C12 * a + C22 * b + C23 * c;
-    o2 = 0.5f * (C13 * a + C23 * b) + C33 * c;
+    o2 = fmaf(C33, c, 0.5f * (C13 * a + C23 * b));
 }
 
 // velocity gradient pieces at a site from central differences of HALF the velocity (h = v / 2 at

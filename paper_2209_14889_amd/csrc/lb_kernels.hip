@@ -5,6 +5,7 @@
 //   k_ib_nodes, k_ib_spread   the same in two launches (nodes once per body, then the tiles)
 //   k_fused       one pass per step over every lattice site: forces, BGK + Guo collide with pull
 //                 streaming, velocity gradient, stiffness, Heun stress and polarization
+//   k_tile        the same pass on tiles whose rows are computed at once, for small lattices
 //   k_mp_*        the same step as four simple site-parallel kernels (debug / reference path)
 //   k_readout     observables at the current time
 //   k_sums / k_sums_final, k_body_force   FP64 reductions
@@ -925,6 +926,328 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
 }
 
 // ------------------------------------------------------------------------------------------------
+// the same step on short items: a tile of sites, all its rows at once
+// ------------------------------------------------------------------------------------------------
+
+// k_fused marches down an item's rows, so an item of l rows takes l + 8 row iterations one after the
+// other, each a wave's chain of several hundred dependent instructions: what bounds a lattice too
+// small to give every wave slot a long item.  Here a work-group takes a tile of w x l sites and every
+// stage over the whole tile at once, with its halo: P on (w + 8) x (l + 8) sites, the Ericksen stress on
+// (w + 6) x (l + 6), the collision on (w + 4) x (l + 4), the predictor on (w + 2) x (l + 2), the
+// corrector on w x l, with one barrier between stages.  It computes more halo sites per lattice site
+// (16 x 16: 1.9, 1.6, 1.3 times the sites in the first three stages) in a chain about a tenth as
+// long.  The arithmetic of a site is k_fused's, so the results are the same bits.
+// Field pass, FP32, marching -> tiles: 64^2 18.8 -> 6.4 us, 250^2 closed box 21.9 -> 8.8, 512^2 22.9 ->
+// 14.1, of which about 1.6 are the launch itself and 2 the loads; at 4 tiles a unit a tile costs a unit
+// 2.2 us, two thirds of it VALU issue and the rest LDS.
+template <int T, typename HT, bool WALLS, bool POL>
+__global__ __launch_bounds__(T, T == 64 ? 2 : 4) void k_tile(const SimDev *__restrict__ sims, const BodyDev *__restrict__ bodies,
+                                               const WorkItem *__restrict__ items, int n_items, int cur,
+                                               int *__restrict__ d_t) {
+    typedef typename PolOf<HT>::T PT;
+    constexpr int NP = tile_cap(T, 8), NS = tile_cap(T, 6), NC = tile_cap(T, 4), ND = tile_cap(T, 2);
+    constexpr int RP = (NP + T - 1) / T, RS = (NS + T - 1) / T, RC = (NC + T - 1) / T;   // rounds of T threads
+    __shared__ PT rP[2][POL ? NP : 1];      // polarization
+    __shared__ float rS[3][NS];             // stress
+    __shared__ float rV[2][NC];             // half the velocity
+    struct Late {                           // after the collision: predicted fields, and per core site
+        PT qp[2][POL ? ND : 1];             // the velocity gradient and stiffness the corrector reuses
+        float qs[3][ND];
+        float g[8][T];
+    };
+    struct Early {
+        float e[4][POL ? NS : 1];           // before it: the Ericksen stress
+    };
+    __shared__ union {
+        Late late;
+        Early early;
+    } U;
+    __shared__ float4 sTab[2 * kStiffSeg];
+    __shared__ ItemBody sIB[kItemBodies];
+    __shared__ int sNB;
+    const int tid = threadIdx.x;
+    const int nxt = cur ^ 1;
+    if (blockIdx.x == 0 && tid == 0) d_t[0] = d_t[0] + 1;   // the body update after this step uses t+1
+    const WorkItem wi = items[xcd_remap(blockIdx.x, n_items)];
+    const SimDev &S = sims[wi.sim];
+    const int nx = S.nx, ny = S.ny, w = wi.w, l = wi.l;
+    const unsigned N = (unsigned)nx * (unsigned)ny;
+    const int WP = w + 8, WS = w + 6, WC = w + 4, WD = w + 2;
+    const bool walls = WALLS && S.walls != 0, box = WALLS && S.walls == 2;
+    const float is = S.inv_scale, sc = S.scale;
+    const unsigned HB = (unsigned)sizeof(HT);
+    const __amdgpu_buffer_rsrc_t rHi = state_rsrc(S.h[cur]), rHo = state_rsrc(S.h[nxt]), rSi = state_rsrc(S.sig[cur]),
+                                 rSo = state_rsrc(S.sig[nxt]), rPi = state_rsrc(S.P[cur]), rPo = state_rsrc(S.P[nxt]);
+
+    // site i of a region of width W that begins d sites before the tile: its coordinates in the region
+    // (i / W as i * ceil(2^16 / W) >> 16, exact for i < 2^11 and W <= 64) and its wrapped lattice site
+    // (the region reaches at most 4 sites beyond a lattice of at least 8)
+    struct Site {
+        int X, Y, x, y;
+    };
+    auto site = [&](int i, int W, int d) {
+        Site q;
+        q.Y = (int)(((unsigned)i * ((65536u + (unsigned)W - 1u) / (unsigned)W)) >> 16);
+        q.X = i - q.Y * W;
+        q.x = wrap_near(wi.x0 - d + q.X, nx);
+        q.y = wrap_near(wi.y0 - d + q.Y, ny);
+        return q;
+    };
+
+    // loads of the tile and its halo, all issued before the first is used
+    PT lp[RP][2];
+    float ls[RS][3];
+    typename Pop<HT>::Raw lh[RC][9];
+    const int nP = WP * (l + 8), nS = WS * (l + 6), nC = WC * (l + 4), nD = WD * (l + 2), nE = w * l;
+    if (POL)
+#pragma unroll
+        for (int k = 0; k < RP; ++k) {
+            if (k * T >= nP) break;
+            const Site q = site(min(tid + k * T, nP - 1), WP, 4);
+            const unsigned o = ((unsigned)q.y * (unsigned)nx + (unsigned)q.x) * (unsigned)sizeof(PT);
+            buf_ld(rPi, o, 0u, lp[k][0]);
+            buf_ld(rPi, o, N * (unsigned)sizeof(PT), lp[k][1]);
+        }
+#pragma unroll
+    for (int k = 0; k < RS; ++k) {
+        if (k * T >= nS) break;
+        const Site q = site(min(tid + k * T, nS - 1), WS, 3);
+        const unsigned o = ((unsigned)q.y * (unsigned)nx + (unsigned)q.x) * 4u;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) ls[k][c] = buf_ldf(rSi, o, (unsigned)c * N * 4u);
+    }
+#pragma unroll
+    for (int k = 0; k < RC; ++k) {
+        if (k * T >= nC) break;
+        // the populations pulled into a collision site: h_n(x, y) = h*_n(x - c_n, y - c_n)
+        const Site q = site(min(tid + k * T, nC - 1), WC, 2);
+        const unsigned xm = (unsigned)wrap_near(q.x - 1, nx), xp = (unsigned)wrap_near(q.x + 1, nx), x = (unsigned)q.x;
+        const unsigned yc = (unsigned)q.y * (unsigned)nx, ym = (unsigned)wrap_near(q.y - 1, ny) * (unsigned)nx,
+                       yp = (unsigned)wrap_near(q.y + 1, ny) * (unsigned)nx;
+        const unsigned NH = N * HB;
+        if (!WALLS) {
+            lh[k][0] = Pop<HT>::ld_buf(rHi, (yc + x) * HB, 0u);
+            lh[k][1] = Pop<HT>::ld_buf(rHi, (yc + xm) * HB, NH);
+            lh[k][2] = Pop<HT>::ld_buf(rHi, (ym + x) * HB, 2u * NH);
+            lh[k][3] = Pop<HT>::ld_buf(rHi, (yc + xp) * HB, 3u * NH);
+            lh[k][4] = Pop<HT>::ld_buf(rHi, (yp + x) * HB, 4u * NH);
+            lh[k][5] = Pop<HT>::ld_buf(rHi, (ym + xm) * HB, 5u * NH);
+            lh[k][6] = Pop<HT>::ld_buf(rHi, (ym + xp) * HB, 6u * NH);
+            lh[k][7] = Pop<HT>::ld_buf(rHi, (yp + xp) * HB, 7u * NH);
+            lh[k][8] = Pop<HT>::ld_buf(rHi, (yp + xm) * HB, 8u * NH);
+        } else {
+            // halfway bounce-back: what would come from beyond a wall is the opposite direction's
+            // post-collision value at the same site
+            const bool blo = walls && q.y == 0, bhi = walls && q.y == ny - 1;
+            const bool xw = box && q.x == 0, xe = box && q.x == nx - 1;
+            const unsigned own = yc + x;
+            auto ld = [&](bool wall, int opp, int n, unsigned from) {
+                return Pop<HT>::ld_buf(rHi, ((wall ? (unsigned)opp : (unsigned)n) * N + (wall ? own : from)) * HB, 0u);
+            };
+            lh[k][0] = Pop<HT>::ld_buf(rHi, own * HB, 0u);
+            lh[k][1] = ld(xw, 3, 1, yc + xm);
+            lh[k][2] = ld(blo, 4, 2, ym + x);
+            lh[k][3] = ld(xe, 1, 3, yc + xp);
+            lh[k][4] = ld(bhi, 2, 4, yp + x);
+            lh[k][5] = ld(blo || xw, 7, 5, ym + xm);
+            lh[k][6] = ld(blo || xe, 8, 6, ym + xp);
+            lh[k][7] = ld(bhi || xe, 5, 7, yp + xp);
+            lh[k][8] = ld(bhi || xw, 6, 8, yp + xm);
+        }
+    }
+    // per-item constants: the stiffness cubics, and the bodies whose patches reach the rows and columns
+    // of the collision region (wave 0 holds every body: at most kMaxBodies = 64 per simulation)
+    for (int q = tid; q < 2 * kStiffSeg; q += T) sTab[q] = reinterpret_cast<const float4 *>(S.tab)[q];
+    if (tid < 64) {
+        bool hit = false;
+        ItemBody ib{0, 0, 0, 0, nullptr, nullptr};
+        if (tid < S.nb) {
+            const BodyDev &B = bodies[S.b0 + tid];
+            ib.ox = gptr(B.origin)[4 * cur + 2];
+            ib.oy = gptr(B.origin)[4 * cur + 3];
+            ib.ps = B.ps;
+            ib.fib = B.fib;
+            ib.vib = B.vib;
+            hit = ring_overlap(ib.ox, ib.ps, wrap_near(wi.x0 - 2, nx), w + 4, nx) &&
+                  ring_overlap(ib.oy, ib.ps, wrap_near(wi.y0 - 2, ny), l + 4, ny);
+        }
+        const unsigned long long m = __ballot(hit);
+        const int cnt = __popcll(m);
+        if (hit) {
+            const int k = __popcll(m & ((1ull << tid) - 1ull));
+            if (k < kItemBodies) sIB[k] = ib;
+        }
+        if (tid == 0) sNB = cnt <= kItemBodies ? cnt : -1;
+    }
+    if (POL)
+#pragma unroll
+        for (int k = 0; k < RP; ++k)
+            if (tid + k * T < nP) {
+                rP[0][tid + k * T] = lp[k][0];
+                rP[1][tid + k * T] = lp[k][1];
+            }
+#pragma unroll
+    for (int k = 0; k < RS; ++k)
+        if (tid + k * T < nS)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) rS[c][tid + k * T] = ls[k][c];
+    __syncthreads();
+    const int nib = sNB;
+
+    // ---- Ericksen stress
+    if (POL) {
+#pragma unroll 1
+        for (int i = tid; i < nS; i += T) {
+            const Site q = site(i, WS, 3);
+            const int c = (q.Y + 1) * WP + q.X + 1;
+            const int e = box && q.x == nx - 1 ? c : c + 1, ww = box && q.x == 0 ? c : c - 1;
+            const int n = walls && q.y == ny - 1 ? c : c + WP, s = walls && q.y == 0 ? c : c - WP;
+            PT Pc[2] = {rP[0][c], rP[1][c]}, Pe[2] = {rP[0][e], rP[1][e]}, Pw[2] = {rP[0][ww], rP[1][ww]};
+            PT Pn[2] = {rP[0][n], rP[1][n]}, Ps[2] = {rP[0][s], rP[1][s]};
+            float E[4];
+            ericksen(S, Pc, Pe, Pw, Pn, Ps, E);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) U.early.e[k][i] = E[k];
+        }
+        __syncthreads();
+    }
+
+    // ---- force, moments, collision
+#pragma unroll 1
+    for (int k = 0; k < RC; ++k) {
+        const int i = tid + k * T;
+        float d[9];
+#pragma unroll
+        for (int r = 0; r < RC; ++r)
+            if (k == r)
+#pragma unroll
+                for (int q = 0; q < 9; ++q) d[q] = Pop<HT>::cvt_stored(lh[r][q]);
+        if (i >= nC) continue;
+        const Site q = site(i, WC, 2);
+        const int c = (q.Y + 1) * WS + q.X + 1;
+        const int e = box && q.x == nx - 1 ? c : c + 1, ww = box && q.x == 0 ? c : c - 1;
+        const int n = walls && q.y == ny - 1 ? c : c + WS, s = walls && q.y == 0 ? c : c - WS;
+        // twice the divergence of the stresses (central differences), halved once
+        float fx = (rS[0][e] - rS[0][ww]) + (rS[2][n] - rS[2][s]);
+        float fy = (rS[2][e] - rS[2][ww]) + (rS[1][n] - rS[1][s]);
+        if (POL && S.ericksen) {
+            fx += (U.early.e[0][e] - U.early.e[0][ww]) + (U.early.e[1][n] - U.early.e[1][s]);
+            fy += (U.early.e[2][e] - U.early.e[2][ww]) + (U.early.e[3][n] - U.early.e[3][s]);
+        }
+        float Fx = fmaf(0.5f, fx, S.gx), Fy = fmaf(0.5f, fy, S.gy);
+        if (nib > 0)
+            ib_force_list(sIB, nib, nx, ny, q.x, q.y, Fx, Fy);
+        else if (nib < 0)
+            ib_force(S, bodies, cur, q.x, q.y, Fx, Fy);
+        float r[9], keep, drho, ux, uy;
+        collide_terms<Pop<HT>::kScaled>(d, Fx, Fy, S.omega, S.guo, sc, is, r, keep, drho, ux, uy);
+        rV[0][i] = 0.5f * ux;   // the gradient and advection stages take v / 2
+        rV[1][i] = 0.5f * uy;
+        if (q.X >= 2 && q.X < w + 2 && q.Y >= 2 && q.Y < l + 2) {
+            const unsigned o = ((unsigned)q.y * (unsigned)nx + (unsigned)q.x) * HB, NH = N * HB;
+#pragma unroll
+            for (int m = 0; m < 9; ++m) Pop<HT>::st_buf(rHo, o, (unsigned)m * NH, fmaf(keep, d[m], r[m]));
+            if (nib > 0)
+                ib_store_v_list(sIB, nib, nx, ny, q.x, q.y, ux, uy);
+            else if (nib < 0)
+                ib_store_v(S, bodies, cur, q.x, q.y, ux, uy);
+        }
+    }
+    __syncthreads();
+
+    // ---- predictor
+#pragma unroll 1
+    for (int i = tid; i < nD; i += T) {
+        const Site q = site(i, WD, 1);
+        const bool xe = box && q.x == nx - 1, xw = box && q.x == 0;
+        const bool yhi = walls && q.y == ny - 1, ylo = walls && q.y == 0;
+        const int v = (q.Y + 1) * WC + q.X + 1, ve = xe ? v : v + 1, vw = xw ? v : v - 1, vn = yhi ? v : v + WC,
+                  vs = ylo ? v : v - WC;
+        const float hx = rV[0][v], hy = rV[1][v];
+        // walls: no-slip (negated) ghosts for v, mirror ghosts for sigma and P
+        const float sxe = xe ? -1.0f : 1.0f, sxw = xw ? -1.0f : 1.0f, syn = yhi ? -1.0f : 1.0f, sys = ylo ? -1.0f : 1.0f;
+        const Grad g = grad_v(sxe * rV[0][ve], sxw * rV[0][vw], syn * rV[0][vn], sys * rV[0][vs],
+                              sxe * rV[1][ve], sxw * rV[1][vw], syn * rV[1][vn], sys * rV[1][vs]);
+        const int p = (q.Y + 3) * WP + q.X + 3;
+        PT Pc[2] = {POL ? rP[0][p] : (PT)0, POL ? rP[1][p] : (PT)0};
+        const Stiff k = POL ? stiffness(S, sTab, (float)((PT)S.pref[0] + Pc[0]), (float)((PT)S.pref[1] + Pc[1]))
+                            : Stiff{0.f, 0.f, 0.f, 0.f};
+        const int c = (q.Y + 2) * WS + q.X + 2;
+        const int e = xe ? c : c + 1, ww = xw ? c : c - 1, n = yhi ? c : c + WS, s = ylo ? c : c - WS;
+        float X[3], Xe[3], Xw[3], Xn[3], Xs[3], Rs[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            X[m] = rS[m][c];
+            Xe[m] = rS[m][e];
+            Xw[m] = rS[m][ww];
+            Xn[m] = rS[m][n];
+            Xs[m] = rS[m][s];
+        }
+        rhs_sigma(S, k, g, hx, hy, X, Xe, Xw, Xn, Xs, Rs);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) U.late.qs[m][i] = X[m] + Rs[m];
+        if (POL) {
+            const int pe = xe ? p : p + 1, pw = xw ? p : p - 1, pn = yhi ? p : p + WP, ps = ylo ? p : p - WP;
+            PT Pe[2] = {rP[0][pe], rP[1][pe]}, Pw[2] = {rP[0][pw], rP[1][pw]};
+            PT Pn[2] = {rP[0][pn], rP[1][pn]}, Ps[2] = {rP[0][ps], rP[1][ps]};
+            PT Rp[2];
+            rhs_P(S, g, hx, hy, Pc, Pe, Pw, Pn, Ps, Rp);
+            U.late.qp[0][i] = Pc[0] + Rp[0];
+            U.late.qp[1][i] = Pc[1] + Rp[1];
+        }
+        if (q.X >= 1 && q.X <= w && q.Y >= 1 && q.Y <= l) {   // the corrector's frozen inputs
+            const int j = (q.Y - 1) * w + q.X - 1;
+            const float f[8] = {g.psi0, g.psi1, g.psi2, g.om, k.p, k.q, k.r, k.w};
+#pragma unroll
+            for (int m = 0; m < (POL ? 8 : 4); ++m) U.late.g[m][j] = f[m];
+        }
+    }
+    __syncthreads();
+
+    // ---- corrector (at most one site a thread)
+    if (tid < nE) {
+        const Site q = site(tid, w, 0);
+        const bool xe = box && q.x == nx - 1, xw = box && q.x == 0;
+        const bool yhi = walls && q.y == ny - 1, ylo = walls && q.y == 0;
+        const int v = (q.Y + 2) * WC + q.X + 2, c = (q.Y + 3) * WS + q.X + 3, p = (q.Y + 4) * WP + q.X + 4;
+        const float hx = rV[0][v], hy = rV[1][v];
+        const Grad g{U.late.g[0][tid], U.late.g[1][tid], U.late.g[2][tid], U.late.g[3][tid]};
+        const Stiff k = POL ? Stiff{U.late.g[4][tid], U.late.g[5][tid], U.late.g[6][tid], U.late.g[7][tid]}
+                            : Stiff{0.f, 0.f, 0.f, 0.f};
+        const int j = (q.Y + 1) * WD + q.X + 1;
+        const int je = xe ? j : j + 1, jw = xw ? j : j - 1, jn = yhi ? j : j + WD, js = ylo ? j : j - WD;
+        float X[3], Xe[3], Xw[3], Xn[3], Xs[3], Rs[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            X[m] = U.late.qs[m][j];
+            Xe[m] = U.late.qs[m][je];
+            Xw[m] = U.late.qs[m][jw];
+            Xn[m] = U.late.qs[m][jn];
+            Xs[m] = U.late.qs[m][js];
+        }
+        rhs_sigma(S, k, g, hx, hy, X, Xe, Xw, Xn, Xs, Rs);
+        const unsigned at = (unsigned)q.y * (unsigned)nx + (unsigned)q.x;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) buf_stf(rSo, at * 4u, (unsigned)m * N * 4u, 0.5f * ((rS[m][c] + X[m]) + Rs[m]));
+        if (POL) {   // without P both P buffers stay zero
+            PT Y[2], Ye[2], Yw[2], Yn[2], Ys[2], Rp[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                Y[m] = U.late.qp[m][j];
+                Ye[m] = U.late.qp[m][je];
+                Yw[m] = U.late.qp[m][jw];
+                Yn[m] = U.late.qp[m][jn];
+                Ys[m] = U.late.qp[m][js];
+            }
+            rhs_P(S, g, hx, hy, Y, Ye, Yw, Yn, Ys, Rp);
+            const unsigned SP = (unsigned)sizeof(PT);
+            buf_st(rPo, at * SP, 0u, (PT)0.5 * ((rP[0][p] + Y[0]) + Rp[0]));
+            buf_st(rPo, at * SP, N * SP, (PT)0.5 * ((rP[1][p] + Y[1]) + Rp[1]));
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // multi-pass reference step: one thread per site, intermediate fields in scratch planes
 // ------------------------------------------------------------------------------------------------
 
@@ -1395,6 +1718,27 @@ static FusedFn fused_fn(int T, bool fp16, bool walls, bool pol) {
     if (T == 128) return fp16 ? fused_fn_t<128, __half>(walls, pol) : fused_fn_t<128, float>(walls, pol);
     if (T == 256) return fp16 ? fused_fn_t<256, __half>(walls, pol) : fused_fn_t<256, float>(walls, pol);
     return nullptr;
+}
+
+typedef void (*TileFn)(const SimDev *, const BodyDev *, const WorkItem *, int, int, int *);
+template <int T, typename HT>
+static TileFn tile_fn_t(bool walls, bool pol) {
+    if (walls) return pol ? k_tile<T, HT, true, true> : k_tile<T, HT, true, false>;
+    return pol ? k_tile<T, HT, false, true> : k_tile<T, HT, false, false>;
+}
+static TileFn tile_fn(int T, bool fp16, bool walls, bool pol) {
+    if (T == 64) return fp16 ? tile_fn_t<64, __half>(walls, pol) : tile_fn_t<64, float>(walls, pol);
+    if (T == 128) return fp16 ? tile_fn_t<128, __half>(walls, pol) : tile_fn_t<128, float>(walls, pol);
+    if (T == 256) return fp16 ? tile_fn_t<256, __half>(walls, pol) : tile_fn_t<256, float>(walls, pol);
+    return nullptr;
+}
+
+hipError_t launch_tile(int T, bool fp16, bool walls, bool pol, hipStream_t st, const SimDev *sims, const BodyDev *bodies,
+                       const WorkItem *items, int n_items, int cur, int *d_t) {
+    TileFn f = tile_fn(T, fp16, walls, pol);
+    if (!f) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(f, dim3(n_items), dim3(T), 0, st, sims, bodies, items, n_items, cur, d_t);
+    return hipGetLastError();
 }
 
 hipError_t launch_fused(int T, bool fp16, bool walls, bool pol, int grid, hipStream_t st, const SimDev *sims,

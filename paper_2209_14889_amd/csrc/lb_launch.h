@@ -16,6 +16,9 @@ hipError_t launch_ib(bool advance, int nbodies, int ntiles, hipStream_t st, cons
 // cus: the device's compute units (work-groups of the first round are dealt to them in turn)
 hipError_t launch_fused(int T, bool fp16, bool walls, bool pol, int grid, hipStream_t st, const SimDev *sims,
                         const BodyDev *bodies, const WorkItem *items, int n_items, int cur, int *d_t, int cus);
+// the same step with short items as tiles, one work-group per item (T: 64, 128 or 256)
+hipError_t launch_tile(int T, bool fp16, bool walls, bool pol, hipStream_t st, const SimDev *sims, const BodyDev *bodies,
+                       const WorkItem *items, int n_items, int cur, int *d_t);
 // resident fused work-groups per compute unit for work-group size T
 int fused_blocks_per_cu(int T, bool fp16, bool walls, bool pol);
 hipError_t launch_multipass(bool fp16, int nblocks, hipStream_t st, const SimDev *sims, const BodyDev *bodies,

@@ -1,0 +1,71 @@
+"""Short work items as tiles (all rows of a tile at once) against items that march down their rows: the
+same arithmetic at every site, so the same bits."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2209_14889_amd import lb
+from paper_2209_14889_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+FE = dict(alpha=-1.8e-3, beta=2e-3, kappa=2e-6)
+
+
+def run(spec, opt, steps=9):
+    g = lb.Sim([spec], opt)
+    g.step(steps)
+    out = g.fields(), g.nodes(), g.launch_shape()
+    g.close()
+    return out
+
+
+def same(a, b, what):
+    for k in lb.FIELDS:
+        assert np.array_equal(a[0][k], b[0][k]), (what, k)
+    for x, y in zip(a[1], b[1]):
+        assert np.array_equal(x, y), (what, "nodes")
+
+
+# lattices at and beside whole numbers of tiles, narrower than a tile with its halo, and ragged; 39 rows of
+# any work-group size are more than a tile takes, so they march
+@pytest.mark.parametrize("nx,ny", [(32, 32), (33, 31), (8, 9), (130, 47)])
+@pytest.mark.parametrize("walls,precision,polar", [(0, 0, 1), (0, 1, 1), (1, 0, 0), (2, 1, 1), (2, 0, 1)])
+def test_tiles_agree_with_marching_items_bitwise(nx, ny, walls, precision, polar):
+    bodies = 1 if min(nx, ny) > 30 else 0
+    w = wl.small_case(81, nx, ny, n_bodies=bodies, radius=4.5, pull=2e-4, walls=walls, gx=1e-6, **(FE if walls else {}))
+    s = w.sims[0]
+    if not polar:
+        s.P0 = np.zeros_like(s.P0)
+    ref = run(s, lb.make_options(precision=precision, fused_threads=64, seg_rows=39))
+    for T, rows in ((64, 4), (64, 7), (64, 8), (128, 5), (128, 8), (256, 4), (256, 9), (256, 16)):
+        print(f"case tiles {nx}x{ny} walls {walls} precision {precision} threads {T} rows {rows}", flush=True)
+        same(run(s, lb.make_options(precision=precision, fused_threads=T, seg_rows=rows)), ref, (T, rows))
+    same(run(s, lb.make_options(precision=precision)), ref, "default")
+
+
+def test_arena_without_room_for_tiles():
+    """An arena of the size that the marching items alone need is accepted, and gives the same bits."""
+    s = wl.small_case(82, 96, 80, n_bodies=1, radius=6.0).sims[0]
+    opt = lb.make_options()
+    g = lb.Sim([s], opt)
+    a = g.launch_shape()
+    g.step(20)
+    f = g.fields()
+    lb.check(lb.lib().lb_destroy(g.h))
+    m = lb._Marshal([s])
+    table = 32 * max(-(-96 // (T // max(8, r))) * -(-80 // r) for T in (64, 128, 256)
+                     for r in range(4, (16 if T == 256 else 8) + 1))
+    h = ctypes.c_void_p()
+    lb.check(lb.lib().lb_create(m.params, 1, ctypes.byref(opt), ctypes.c_void_p(g.arena.data_ptr()),
+                                ctypes.c_size_t(g.arena.numel() - table), ctypes.c_void_p(g.stream.cuda_stream),
+                                ctypes.byref(h)))
+    g.h = h
+    b = g.launch_shape()
+    assert a["seg_rows"] == 4 and a["n_items"] != b["n_items"]
+    g.step(20)
+    f2 = g.fields()
+    for k in lb.FIELDS:
+        assert np.array_equal(f[k], f2[k]), k
+    g.close()
