@@ -194,6 +194,7 @@ struct Plan {
     std::vector<SiteBlock> site_blk;
     int T = 256;
     int max_partial = 1;
+    int nmax = 0;       // nodes of the largest body
     size_t max_tiles = 0;
     size_t least = 0;   // arena bytes without the table of tiles: short items then march like long ones
     size_t bytes = 0;
@@ -394,6 +395,7 @@ Plan make_plan(const lb_sim_params *sims, int n_sims, const Opt &o) {
             BodyPlan bp;
             bp.sim = s;
             bp.n = d.n_nodes;
+            pl.nmax = std::max(pl.nmax, bp.n);
             bp.ps = std::min(2 * (int)std::ceil(body_extent(d)) + 24, std::min(p.nx, p.ny));
             bp.nside = (bp.ps + kPatchTile - 1) / kPatchTile;
             bp.oR0 = a.take(16 * (size_t)bp.n);
@@ -670,8 +672,8 @@ int launch_step(lb_handle *h, bool timed) {
             if (!c || !d) return fail(LB_EDEVICE, "hipEventCreate failed");
             HIPCHK(hipEventRecord(c, h->stream));
         }
-        HIPCHK(launch_ib(true, (int)h->plan.bodies.size(), (int)h->plan.ib_blk.size(), h->stream, h->d_sims,
-                         h->d_bodies, h->d_ib, h->cur, h->d_t, h->d_status));
+        HIPCHK(launch_ib(true, (int)h->plan.bodies.size(), (int)h->plan.ib_blk.size(), h->plan.nmax, h->stream,
+                         h->d_sims, h->d_bodies, h->d_ib, h->cur, h->d_t, h->d_status));
         if (timed) {
             HIPCHK(hipEventRecord(d, h->stream));
             h->pending_ib.emplace_back(c, d);
@@ -912,10 +914,14 @@ int choose_fused_config(lb_handle *h) {
     };
     // A lattice small enough to be tiles: 4-row tiles of that width's work-group while they give a SIMD at
     // most two waves (more and shorter chains: 64^2 6.4 us with 128 lanes and 4 rows, 7.5 with 8), else
-    // 256 lanes and 8 rows, which compute less halo.
+    // 256 lanes and 8 rows, which compute less halo.  Beyond 2048 sites at least 128 lanes (64^2 takes 8.2
+    // us with 64, whose one wave does everything; below, narrow lattices keep the documented width).
     auto model_tiles = [&](int &T, int &rows) {
         if (h->opt.seg || h->opt.grid || !h->d_tiles) return false;
+        size_t sites = 0;
+        for (const auto &sp : h->plan.sims) sites += sp.N;
         T = model_T();
+        if (!h->opt.threads && sites > 2048) T = std::max(T, 128);
         rows = kTileMinRows;
         if (count_tiles(h->plan.sims, T, rows) * (size_t)(T / 64) <= 8 * (size_t)cus && tiles_pay(h->plan.sims, T, rows, h->cus))
             return true;
@@ -1333,7 +1339,7 @@ static int create_impl(const lb_sim_params *sims, int n_sims, const lb_options *
 
     // initial body forces spread onto their patches
     if (!pl.ib_blk.empty())
-        HIPCHK(launch_ib(false, (int)pl.bodies.size(), (int)pl.ib_blk.size(), h->stream, h->d_sims, h->d_bodies,
+        HIPCHK(launch_ib(false, (int)pl.bodies.size(), (int)pl.ib_blk.size(), pl.nmax, h->stream, h->d_sims, h->d_bodies,
                          h->d_ib, 0, h->d_t, h->d_status));
     // reference mass for the watchdog
     for (int s = 0; s < n_sims; ++s) {

@@ -48,71 +48,82 @@ __device__ __forceinline__ void phi4(double R, int &i0, float w[4]) {
     w[3] = 0.25f * (1.0f - cs);
 }
 
-__device__ __forceinline__ double pull_factor(const BodyDev &B, double t) {
-    if (B.width <= 0.0) return 1.0;
-    return 1.0 / (1.0 + exp(-(t - B.t_on) / B.width)) - 1.0 / (1.0 + exp(-(t - B.t_off) / B.width));
+// The schedule at time t, by the lanes of one wave: pull = S((t - t_on)/w) - S((t - t_off)/w) with S the
+// logistic function (1 for a constant pull); the trap's stiffness k = trap_k [S(u1) - S(u2)] and travelled
+// share rho = w / T [sp(u1) - sp(u2)], sp(x) = ln(1 + e^x) (App. A, eqUtrap; App. C).  Lanes 0, 1 take
+// the pull's S, 2, 3 the trap's S and 4, 5 its sp, each one exponential.
+struct Schedule {
+    double pull, k, rho;
+};
+__device__ __forceinline__ Schedule schedule(const BodyDev &B, double t) {
+    Schedule q{1.0, 0.0, 0.0};
+    if (B.width <= 0.0 && B.trap_k == 0.0) return q;
+    const int lane = threadIdx.x & 63;
+    const bool pull = lane < 2, on = (lane & 1) == 0, soft = lane >= 4;
+    const double x = pull ? (t - (on ? B.t_on : B.t_off)) / B.width : (t - (on ? B.trap_t1 : B.trap_t2)) / B.trap_w;
+    const bool up = soft && !(x > 30.0);
+    const double e = exp(up ? x : -x);
+    double r;
+    if (soft)
+        r = x > 30.0 ? x + log1p(e) : log1p(e);
+    else
+        r = 1.0 / (1.0 + e);
+    const double d = r - __shfl_xor(r, 1);   // even lanes: on minus off
+    const double T = B.trap_t2 - B.trap_t1;
+    if (B.width > 0.0) q.pull = __shfl(d, 0);
+    if (B.trap_k != 0.0) {
+        q.k = B.trap_k * __shfl(d, 2);
+        q.rho = T > 0.0 ? (B.trap_w / T) * __shfl(d, 4) : 0.0;
+    }
+    return q;
 }
 
-// v at point R from a body's velocity patch V (side ps, origin ox, oy; the x plane, then the y
-// plane); flags reads outside the patch
-__device__ __forceinline__ void interp_patch(const float *V, int ps, int ox, int oy, double Rx, double Ry,
-                                             double &vx, double &vy, bool &bad) {
-    int ix, iy;
-    float wx[4], wy[4];
-    phi4(Rx, ix, wx);
-    phi4(Ry, iy, wy);
-    const size_t pp = (size_t)ps * ps;
-    vx = 0.0;
-    vy = 0.0;
-    const int px0 = ix - ox, py0 = iy - oy;
-    if (px0 < 0 || py0 < 0 || px0 + 3 >= ps || py0 + 3 >= ps) {
-        bad = true;
-        return;
-    }
-    for (int j = 0; j < 4; ++j) {
-        double ax = 0.0, ay = 0.0;
-        const size_t q = (size_t)(py0 + j) * ps + px0;
-        for (int i = 0; i < 4; ++i) {
-            ax += (double)wx[i] * (double)V[q + i];
-            ay += (double)wx[i] * (double)V[pp + q + i];
+// four consecutive floats at any 4-byte boundary (one 16-byte load)
+typedef float Row4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// Heun step of one node by a pair of lanes, lane c taking the component c (0: x, 1: y) of the node
+// position r: r + (v(R) + v(R + v(R))) / 2 with v interpolated from the body's velocity patch V (side
+// ps, origin o[2]; the x plane, then the y plane).  Each lane forms the kernel weights of its own
+// coordinate, takes the other's from its partner and sums its own plane's 4 x 4 values.  The second
+// position is a small fraction of a site away, so its footprint is nearly always the first one's and
+// reuses the values loaded for it.  bad: a footprint outside the patch.
+__device__ __forceinline__ double heun_component(const float *V, int ps, int ox, int oy, int c, double r, bool &bad) {
+    const float *plane = V + (size_t)c * ps * ps;
+    Row4 row[4];
+    int at = -1;   // where row[] was loaded from
+    double v[2] = {0.0, 0.0};
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+        int i0;
+        float w[4], u[4];
+        phi4(r + v[0], i0, w);
+        const int j0 = __shfl_xor(i0, 1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = __shfl_xor(w[k], 1);
+        const int px0 = (c ? j0 : i0) - ox, py0 = (c ? i0 : j0) - oy;
+        const bool out = px0 < 0 || py0 < 0 || px0 + 3 >= ps || py0 + 3 >= ps;
+        bad = bad || out;
+        double s = 0.0;
+        if (!out) {
+            const int q = py0 * ps + px0;
+            if (q != at)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) row[j] = *(const LBK_GLOBAL Row4 *)gptr(plane + q + j * ps);
+            at = q;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                double a = 0.0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a += (double)(c ? u[i] : w[i]) * (double)row[j][i];
+                s += (double)(c ? w[j] : u[j]) * a;
+            }
         }
-        vx += (double)wy[j] * ax;
-        vy += (double)wy[j] * ay;
+        v[1] = v[0] + s;
+        if (pass == 0) v[0] = s;
     }
+    return r + 0.5 * v[1];
 }
 
-// Heun step of one node through the velocity patch V: R + (v(R) + v(R + v(R))) / 2
-__device__ __forceinline__ void heun_node(const float *V, int ps, int ox, int oy, double2 &R, bool &bad) {
-    double v1x, v1y, v2x, v2y;
-    interp_patch(V, ps, ox, oy, R.x, R.y, v1x, v1y, bad);
-    interp_patch(V, ps, ox, oy, R.x + v1x, R.y + v1y, v2x, v2y, bad);
-    R.x += 0.5 * (v1x + v2x);
-    R.y += 0.5 * (v1y + v2y);
-}
-
-// derivative of cos(gamma_j) with respect to e1 = R_{j-1} - R_j (d1) and e2 = R_{j+1} - R_j (d2)
-__device__ __forceinline__ void angle_grads(const double2 *R, int n, int j, double2 &d1, double2 &d2) {
-    int jm = j == 0 ? n - 1 : j - 1, jp = j == n - 1 ? 0 : j + 1;
-    double e1x = R[jm].x - R[j].x, e1y = R[jm].y - R[j].y;
-    double e2x = R[jp].x - R[j].x, e2y = R[jp].y - R[j].y;
-    double n1 = sqrt(e1x * e1x + e1y * e1y), n2 = sqrt(e2x * e2x + e2y * e2y);
-    double in12 = 1.0 / (n1 * n2);
-    double cg = (e1x * e2x + e1y * e2y) * in12;
-    d1.x = e2x * in12 - cg * e1x / (n1 * n1);
-    d1.y = e2y * in12 - cg * e1y / (n1 * n1);
-    d2.x = e1x * in12 - cg * e2x / (n2 * n2);
-    d2.y = e1y * in12 - cg * e2y / (n2 * n2);
-}
-
-// spring force k (l - l_eq) d/l on node i from the spring to node j (d = R_j - R_i)
-__device__ __forceinline__ double2 spring_pull(const double2 *R, int i, int j, double k, double leq) {
-    double dx = R[j].x - R[i].x, dy = R[j].y - R[i].y;
-    double l = sqrt(dx * dx + dy * dy);
-    double c = k * (l - leq) / l;
-    return make_double2(c * dx, c * dy);
-}
-
-// -dU/dR_a for U = sum springs + sum bending (eqConst), plus the pull share
 __device__ __forceinline__ double wave_min(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
     return v;
@@ -126,194 +137,273 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// centre of mass of the n nodes in LDS, the same in every block: per-thread sums in node order,
-// wave sums, then the four waves in a fixed order (256-thread blocks)
+// centre of mass of the n nodes in LDS, the same in every block: the first 256 threads' sums in node
+// order, wave sums, then the four waves in a fixed order
 __device__ __forceinline__ double2 block_com(const double2 *sR, int n, double (*sC)[2]) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    double cx = 0.0, cy = 0.0;
-    for (int a = tid; a < n; a += 256) {
-        cx += sR[a].x;
-        cy += sR[a].y;
-    }
-    cx = wave_sum(cx);
-    cy = wave_sum(cy);
-    if (lane == 0) {
-        sC[wv][0] = cx;
-        sC[wv][1] = cy;
+    if (tid < 256) {
+        double cx = 0.0, cy = 0.0;
+        for (int a = tid; a < n; a += 256) {
+            cx += sR[a].x;
+            cy += sR[a].y;
+        }
+        cx = wave_sum(cx);
+        cy = wave_sum(cy);
+        if (lane == 0) {
+            sC[wv][0] = cx;
+            sC[wv][1] = cy;
+        }
     }
     __syncthreads();
     return make_double2(((sC[0][0] + sC[1][0]) + (sC[2][0] + sC[3][0])) / n,
                         ((sC[0][1] + sC[1][1]) + (sC[2][1] + sC[3][1])) / n);
 }
 
-// each node's share k(t) (R_ext(t) - R_com) / n of the harmonic trap (App. A, eqUtrap): stiffness
-// switched by logistics, trap moved by their integral (a smoothed constant-speed ramp)
-__device__ __forceinline__ double2 trap_share(const BodyDev &B, double t, double2 com) {
-    if (B.trap_k == 0.0) return make_double2(0.0, 0.0);
-    const double w = B.trap_w, T = B.trap_t2 - B.trap_t1;
-    const double u1 = (t - B.trap_t1) / w, u2 = (t - B.trap_t2) / w;
-    const double k = B.trap_k * (1.0 / (1.0 + exp(-u1)) - 1.0 / (1.0 + exp(-u2)));
-    auto sp = [](double x) { return x > 30.0 ? x + log1p(exp(-x)) : log1p(exp(x)); };
-    const double rho = T > 0.0 ? (w / T) * (sp(u1) - sp(u2)) : 0.0;
-    return make_double2(k * (B.trap_x0 + B.trap_dx * rho - com.x) / B.n, k * (B.trap_y0 + B.trap_dy * rho - com.y) / B.n);
-}
+// ---- the body update, shared by the one-launch and the two-launch form (the same bits) ----
+// A body's block has kIbThreads threads.  What bounds it is its chain: the descriptor, the nodes, the
+// velocities, then some hundred FP64 instructions one after the other in every wave.  So each quantity
+// is computed once (a spring and an angle belong to one node and reach its neighbours through LDS), the
+// second velocity interpolation reuses the first one's values, pairs of lanes share a node's
+// interpolation and a site's gather, the extent is reduced in whole sites, and the drive's schedule is
+// one wave's work beside the others' nodes.  One launch, before -> after (the same bits): 64^2, 40
+// nodes 9.3 -> 7.4 us; 2048^2, 8 bodies of 75-150 nodes 10.1 -> 8.3; the 250^2 box with its trap 11.8 ->
+// 9.1; 32 pulled bodies 12.4 -> 9.5.
+constexpr int kIbThreads = 512;
 
-__device__ __forceinline__ double2 node_force(const BodyDev &B, const double2 *R, int a, double pf, double2 trap) {
-    const int n = B.n;
-    int am = a == 0 ? n - 1 : a - 1, ap = a == n - 1 ? 0 : a + 1;
-    double2 s1 = spring_pull(R, a, ap, B.k, B.leq);
-    double2 s0 = spring_pull(R, a, am, B.k, B.leq);
-    double2 d1a, d2a, d1m, d2m, d1p, d2p;
-    angle_grads(R, n, a, d1a, d2a);
-    angle_grads(R, n, am, d1m, d2m);
-    angle_grads(R, n, ap, d1p, d2p);
-    double fx = s1.x + s0.x + B.eps * ((d1a.x + d2a.x) - d2m.x - d1p.x) + pf * B.fx / n + trap.x;
-    double fy = s1.y + s0.y + B.eps * ((d1a.y + d2a.y) - d2m.y - d1p.y) + pf * B.fy / n + trap.y;
-    return make_double2(fx, fy);
-}
+// LDS of the nodes, sized by the launch for its largest body: position, then spring to the next
+// node, d1 and d2
+struct BodyNodes {
+    double2 *R, *spring, *d1, *d2;
+    __device__ BodyNodes(double2 *p, int n) : R(p), spring(p + n), d1(p + 2 * n), d2(p + 3 * n) {}
+};
+struct BodyScratch {
+    Schedule at;   // the schedule at *d_t
+    int ext[kIbThreads / 64][4];
+    double com[4][2];
+};
 
-
-// Two-launch body update for many bodies (each node advanced once): k_ib_nodes, then k_ib_spread.
-// One block per body.  ADVANCE: move the nodes from R(t) to R(t+1) by Heun with the velocity patch
-// written during step t (App. A: overdamped, no slip); otherwise take R[cur] as it is.  Then the
-// node forces at the new positions with the pull at time *d_t, the new patch origin, and each
-// node's footprint weights for the spreading kernel.
+// Phase 1: the nodes in LDS (ADVANCE: moved from R(t) to R(t+1) by Heun with the velocity patch written
+// during step t, App. A: overdamped, no slip; otherwise R[cur] as it is), their extent in whole sites
+// and, for a trapped body, their centre of mass; then every node's spring and the derivatives of the
+// cosine of its angle with respect to e1 = R_{a-1} - R_a (d1) and e2 = R_{a+1} - R_a (d2).
+// Returns the patch origin: 3 sites of margin below the lowest node cover the kernel support (2) plus one
+// site of node motion; the same margin above is checked against the patch side.
+// The last wave, which has nodes of its own only in a large body, also evaluates the schedule.
 template <bool ADVANCE>
-__global__ __launch_bounds__(256) void k_ib_nodes(const SimDev *__restrict__ sims, BodyDev *__restrict__ bodies,
-                                                  int cur, const int *__restrict__ d_t, int *__restrict__ d_status) {
-    __shared__ double2 sR[kMaxNodes];
-    __shared__ double sRed[4][4];
-    __shared__ double sC[4][2];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const BodyDev &B = bodies[blockIdx.x];
-    const SimDev &S = sims[B.sim];
-    const int n = B.n;
-    const int dst = ADVANCE ? (cur ^ 1) : cur;
-    bool bad = false;
-    bool wall = false;   // a node's kernel footprint reaches a wall
-
-    const double2 *Rc = reinterpret_cast<const double2 *>(B.R[cur]);
+__device__ __forceinline__ int2 body_phase1(const BodyDev &B, int cur, const int *d_t, BodyNodes N, BodyScratch &sc,
+                                            double2 &com, bool &bad) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, c = tid & 1, n = B.n;
+    const double *Rc = B.R[cur];
     int ox = 0, oy = 0;
     if (ADVANCE) {
-        ox = B.origin[4 * cur];
-        oy = B.origin[4 * cur + 1];
+        ox = gptr(B.origin)[4 * cur];
+        oy = gptr(B.origin)[4 * cur + 1];
     }
-    for (int a = tid; a < n; a += 256) {
-        double2 R = Rc[a];
-        if (ADVANCE) heun_node(B.vib, B.ps, ox, oy, R, bad);
-        sR[a] = R;
+    if (__builtin_amdgcn_readfirstlane(wv) == kIbThreads / 64 - 1) {
+        const Schedule q = schedule(B, (double)d_t[0]);
+        if (lane == 0) sc.at = q;
+    }
+    int lo = 0x7fffffff, hi = -0x7fffffff;
+#pragma unroll 1
+    for (int a = tid >> 1; a < n; a += kIbThreads / 2) {
+        double r = gptr(Rc)[2 * a + c];
+        if (ADVANCE) r = heun_component(B.vib, B.ps, ox, oy, c, r, bad);
+        reinterpret_cast<double *>(N.R)[2 * a + c] = r;
+        const int f = (int)floor(r);
+        lo = min(lo, f);
+        hi = max(hi, f);
+    }
+#pragma unroll
+    for (int o = 2; o < 64; o <<= 1) {
+        lo = min(lo, __shfl_xor(lo, o));
+        hi = max(hi, __shfl_xor(hi, o));
+    }
+    if (lane < 2) {
+        sc.ext[wv][c] = lo;
+        sc.ext[wv][2 + c] = hi;
     }
     __syncthreads();
+    int mn[2] = {0x7fffffff, 0x7fffffff}, mx[2] = {-0x7fffffff, -0x7fffffff};
+#pragma unroll
+    for (int w = 0; w < kIbThreads / 64; ++w)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            mn[k] = min(mn[k], sc.ext[w][k]);
+            mx[k] = max(mx[k], sc.ext[w][2 + k]);
+        }
+    const int nox = mn[0] - 3, noy = mn[1] - 3;
+    if (mx[0] + 3 - nox >= B.ps || mx[1] + 3 - noy >= B.ps) bad = true;
+    if (B.trap_k != 0.0) com = block_com(N.R, n, sc.com);
+#pragma unroll 1
+    for (int a = tid; a < n; a += kIbThreads) {
+        const int am = a == 0 ? n - 1 : a - 1, ap = a == n - 1 ? 0 : a + 1;
+        const double2 R = N.R[a], Rm = N.R[am], Rp = N.R[ap];
+        const double e1x = Rm.x - R.x, e1y = Rm.y - R.y, e2x = Rp.x - R.x, e2y = Rp.y - R.y;
+        const double n1 = sqrt(e1x * e1x + e1y * e1y), n2 = sqrt(e2x * e2x + e2y * e2y);
+        // spring force k (l - l_eq) d/l on node a from the spring to the next node
+        const double cs = B.k * (n2 - B.leq) / n2;
+        N.spring[a] = make_double2(cs * e2x, cs * e2y);
+        const double in12 = 1.0 / (n1 * n2);
+        const double cg = (e1x * e2x + e1y * e2y) * in12;
+        N.d1[a] = make_double2(e2x * in12 - cg * e1x / (n1 * n1), e2y * in12 - cg * e1y / (n1 * n1));
+        N.d2[a] = make_double2(e1x * in12 - cg * e2x / (n2 * n2), e1y * in12 - cg * e2y / (n2 * n2));
+    }
+    __syncthreads();
+    return make_int2(nox, noy);
+}
 
-    const double pf = pull_factor(B, (double)d_t[0]);
-    const double2 trap = trap_share(B, (double)d_t[0], block_com(sR, n, sC));
-    double2 *Fn = reinterpret_cast<double2 *>(B.fnode);
-    double2 *Rd = reinterpret_cast<double2 *>(B.R[dst]);
-    double mnx = 1e300, mny = 1e300, mxx = -1e300, mxy = -1e300;
-    for (int a = tid; a < n; a += 256) {
-        const double2 R = sR[a];
-        Fn[a] = node_force(B, sR, a, pf, trap);
-        if (ADVANCE) Rd[a] = R;
+// -dU/dR_a for U = sum springs + sum bending (eqConst), plus the node's share of the pull and the trap
+__device__ __forceinline__ double2 node_force(const BodyDev &B, const BodyNodes &N, int a, double2 share) {
+    const int n = B.n, am = a == 0 ? n - 1 : a - 1, ap = a == n - 1 ? 0 : a + 1;
+    const double2 s1 = N.spring[a], s0 = N.spring[am], d1 = N.d1[a], d2 = N.d2[a], d2m = N.d2[am], d1p = N.d1[ap];
+    return make_double2(s1.x - s0.x + B.eps * ((d1.x + d2.x) - d2m.x - d1p.x) + share.x,
+                        s1.y - s0.y + B.eps * ((d1.y + d2.y) - d2m.y - d1p.y) + share.y);
+}
+
+// each node's share of the pull and of the trap, k(t) (R_ext(t) - R_com) / n
+__device__ __forceinline__ double2 node_share(const BodyDev &B, const Schedule &q, double2 com) {
+    double2 s = make_double2(q.pull * B.fx / B.n, q.pull * B.fy / B.n);
+    if (B.trap_k != 0.0) {
+        s.x += q.k * (B.trap_x0 + B.trap_dx * q.rho - com.x) / B.n;
+        s.y += q.k * (B.trap_y0 + B.trap_dy * q.rho - com.y) / B.n;
+    }
+    return s;
+}
+
+// a node's kernel footprint [ix, ix + 4) x [iy, iy + 4) (with one site of margin for the predicted
+// position) reaches a wall
+__device__ __forceinline__ bool at_wall(const SimDev &S, int ix, int iy) {
+    return (S.walls && (iy < 1 || iy + 4 >= S.ny)) || (S.walls == 2 && (ix < 1 || ix + 4 >= S.nx));
+}
+
+// Two-launch body update for many bodies (each node advanced once): k_ib_nodes, then k_ib_spread.
+// One block per body: phase 1, then the node forces at the new positions with the pull at time *d_t, the
+// new patch origin, and each node's footprint weights for the spreading kernel.
+template <bool ADVANCE>
+__global__ __launch_bounds__(kIbThreads) void k_ib_nodes(const SimDev *__restrict__ sims, BodyDev *__restrict__ bodies,
+                                                         int nmax, int cur, const int *__restrict__ d_t,
+                                                         int *__restrict__ d_status) {
+    extern __shared__ __align__(16) double2 sNodes[];   // 4 nmax
+    __shared__ BodyScratch sc;
+    const int tid = threadIdx.x;
+    const BodyDev &B = bodies[blockIdx.x];
+    const SimDev &S = sims[B.sim];
+    const BodyNodes N(sNodes, nmax);
+    const int n = B.n, dst = ADVANCE ? (cur ^ 1) : cur;
+    bool bad = false, wall = false;
+    double2 com = make_double2(0.0, 0.0);
+    const int2 o = body_phase1<ADVANCE>(B, cur, d_t, N, sc, com, bad);
+    const double2 share = node_share(B, sc.at, com);
+#pragma unroll 1
+    for (int a = tid; a < n; a += kIbThreads) {
+        const double2 R = N.R[a];
+        reinterpret_cast<double2 *>(B.fnode)[a] = node_force(B, N, a, share);
+        if (ADVANCE) reinterpret_cast<double2 *>(B.R[dst])[a] = R;
         int ix, iy;
         float wx[4], wy[4];
         phi4(R.x, ix, wx);
         phi4(R.y, iy, wy);
-        if ((S.walls && (iy < 1 || iy + 4 >= S.ny)) || (S.walls == 2 && (ix < 1 || ix + 4 >= S.nx)))
-            wall = true;   // one site of margin for the predicted position
+        wall = wall || at_wall(S, ix, iy);
         B.nix[2 * a] = ix;
         B.nix[2 * a + 1] = iy;
         float4 *w = reinterpret_cast<float4 *>(B.nw) + 2 * a;
         w[0] = make_float4(wx[0], wx[1], wx[2], wx[3]);
         w[1] = make_float4(wy[0], wy[1], wy[2], wy[3]);
-        mnx = fmin(mnx, R.x);
-        mny = fmin(mny, R.y);
-        mxx = fmax(mxx, R.x);
-        mxy = fmax(mxy, R.y);
     }
-    mnx = wave_min(mnx);
-    mny = wave_min(mny);
-    mxx = wave_max(mxx);
-    mxy = wave_max(mxy);
-    if (lane == 0) {
-        sRed[wv][0] = mnx;
-        sRed[wv][1] = mny;
-        sRed[wv][2] = mxx;
-        sRed[wv][3] = mxy;
-    }
-    __syncthreads();
     if (tid == 0) {
-        mnx = fmin(fmin(sRed[0][0], sRed[1][0]), fmin(sRed[2][0], sRed[3][0]));
-        mny = fmin(fmin(sRed[0][1], sRed[1][1]), fmin(sRed[2][1], sRed[3][1]));
-        mxx = fmax(fmax(sRed[0][2], sRed[1][2]), fmax(sRed[2][2], sRed[3][2]));
-        mxy = fmax(fmax(sRed[0][3], sRed[1][3]), fmax(sRed[2][3], sRed[3][3]));
-        // patch: 3 sites of margin below the lowest node cover the kernel support (2) plus one
-        // site of node motion; the same margin above is checked against the patch side
-        const int nox = (int)floor(mnx) - 3, noy = (int)floor(mny) - 3;
-        if ((int)floor(mxx) + 3 - nox >= B.ps || (int)floor(mxy) + 3 - noy >= B.ps) bad = true;
-        B.origin[4 * dst] = nox;
-        B.origin[4 * dst + 1] = noy;
-        B.origin[4 * dst + 2] = wrapi(nox, S.nx);
-        B.origin[4 * dst + 3] = wrapi(noy, S.ny);
+        B.origin[4 * dst] = o.x;
+        B.origin[4 * dst + 1] = o.y;
+        B.origin[4 * dst + 2] = wrapi(o.x, S.nx);
+        B.origin[4 * dst + 3] = wrapi(o.y, S.ny);
     }
     if (bad) atomicOr(d_status, kStatusPatch);
     if (wall) atomicOr(d_status, kStatusWall);
 }
 
-// f_IB at tile site (lx, ly) = sum over the listed nodes, in list (node) order, of
-// f_a phi(x) phi(y), from each node's 4x4 footprint origin o (tile coordinates) and its
-// separable weights.  The LDS reads of four nodes are issued before any of them is used, so
-// each group of four costs one LDS round trip instead of two per node.
-__device__ __forceinline__ void gather_one(int lx, int ly, int2 o, float4 wxv, float4 wyv, double2 f, double &fx,
-                                           double &fy) {
-    const int i = lx - o.x, jj = ly - o.y;
-    if ((unsigned)i < 4u && (unsigned)jj < 4u) {
-        const float wxs = i == 0 ? wxv.x : i == 1 ? wxv.y : i == 2 ? wxv.z : wxv.w;
-        const float wys = jj == 0 ? wyv.x : jj == 1 ? wyv.y : jj == 2 ? wyv.z : wyv.w;
-        const double w = (double)wxs * (double)wys;
-        fx += f.x * w;
-        fy += f.y * w;
-    }
-}
-__device__ __forceinline__ void gather_site(const int2 *sI, const float4 (*sW)[2], const double2 *sF, int cnt, int lx,
-                                            int ly, double &fx, double &fy) {
-    int q = 0;
-    for (; q + 4 <= cnt; q += 4) {
+// The nodes whose footprint reaches a tile, in node order: footprint origin (tile coordinates),
+// separable weights, force.
+struct TileNodes {
+    int2 o[kMaxCand];
+    float4 w[kMaxCand][2];
+    double2 f[kMaxCand];
+    int cnt[kIbThreads / 64];
+};
+
+// f_IB at tile site (lx, ly): the listed nodes' f_a phi(x) phi(y), the entries first, first + step, ...
+// in order.  The LDS reads of four entries are issued before any of them is used, so each group
+// costs one LDS round trip.
+__device__ __forceinline__ double2 gather(const TileNodes &L, int cnt, int lx, int ly, int first, int step) {
+    double2 s = make_double2(0.0, 0.0);
+#pragma unroll 1
+    for (int q = first; q < cnt; q += 4 * step) {
         int2 o[4];
         float4 wx[4], wy[4];
         double2 f[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            o[u] = sI[q + u];
-            wx[u] = sW[q + u][0];
-            wy[u] = sW[q + u][1];
-            f[u] = sF[q + u];
+            const int e = min(q + step * u, kMaxCand - 1);
+            o[u] = L.o[e];
+            wx[u] = L.w[e][0];
+            wy[u] = L.w[e][1];
+            f[u] = L.f[e];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) gather_one(lx, ly, o[u], wx[u], wy[u], f[u], fx, fy);
+        for (int u = 0; u < 4; ++u) {
+            const int i = lx - o[u].x, j = ly - o[u].y;
+            if (q + step * u < cnt && (unsigned)i < 4u && (unsigned)j < 4u) {
+                const float wxs = i == 0 ? wx[u].x : i == 1 ? wx[u].y : i == 2 ? wx[u].z : wx[u].w;
+                const float wys = j == 0 ? wy[u].x : j == 1 ? wy[u].y : j == 2 ? wy[u].z : wy[u].w;
+                const double w = (double)wxs * (double)wys;
+                s.x += f[u].x * w;
+                s.y += f[u].y * w;
+            }
+        }
     }
-    for (; q < cnt; ++q) gather_one(lx, ly, sI[q], sW[q][0], sW[q][1], sF[q], fx, fy);
+    return s;
+}
+
+// the listed nodes' forces on the 16 x 16 sites of tile (tx, ty) of a body's patch, by 256 threads, or
+// 512 with a pair of lanes per site (lane h then stores component h).  The even and the odd entries are
+// summed apart and then added, so both give the same bits.
+template <int THREADS>
+__device__ __forceinline__ void spread_tile(const BodyDev &B, const TileNodes &L, int cnt, int tx, int ty) {
+    constexpr bool pair = THREADS == 2 * kPatchTile * kPatchTile;
+    const int s = pair ? threadIdx.x >> 1 : threadIdx.x, h = pair ? threadIdx.x & 1 : 0;
+    const int lx = s % kPatchTile, ly = s / kPatchTile, px = tx * kPatchTile + lx, py = ty * kPatchTile + ly;
+    double2 a = gather(L, cnt, lx, ly, h, 2), b;
+    if (pair)
+        b = make_double2(__shfl_xor(a.x, 1), __shfl_xor(a.y, 1));
+    else
+        b = gather(L, cnt, lx, ly, 1, 2);
+    a.x += b.x;
+    a.y += b.y;
+    if (px < B.ps && py < B.ps) {
+        const unsigned i = (unsigned)(py * B.ps + px), plane = (unsigned)(B.ps * B.ps);
+        if (pair) {
+            B.fib[h * plane + i] = (float)(h ? a.y : a.x);
+        } else {
+            B.fib[i] = (float)a.x;
+            B.fib[plane + i] = (float)a.y;
+        }
+    }
 }
 
 // One block per (body, 16x16 tile of its patch): f_IB(r) = sum_a f_a phi phi (App. A) as a gather
-// over the nodes whose 4x4 footprint reaches the tile, summed in node order (deterministic).
-__global__ __launch_bounds__(256) void k_ib_spread(const BodyDev *__restrict__ bodies, const int2 *__restrict__ blk,
-                                                   int dst, int *__restrict__ d_status) {
-    __shared__ int sA[kMaxCand];
-    __shared__ int2 sI[kMaxCand];
-    __shared__ float4 sW[kMaxCand][2];
-    __shared__ double2 sF[kMaxCand];
-    __shared__ int sCnt[4];
-    __shared__ int sTot;
+// over the nodes whose 4x4 footprint reaches the tile (deterministic).
+constexpr int kSpreadThreads = 256;
+__global__ __launch_bounds__(kSpreadThreads) void k_ib_spread(const BodyDev *__restrict__ bodies, const int2 *__restrict__ blk,
+                                                          int dst, int *__restrict__ d_status) {
+    __shared__ TileNodes L;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int2 bt = blk[blockIdx.x];
     const BodyDev &B = bodies[bt.x];
     const int n = B.n;
     const int tx = bt.y % B.nside, ty = bt.y / B.nside;
     const int X0 = B.origin[4 * dst] + tx * kPatchTile, Y0 = B.origin[4 * dst + 1] + ty * kPatchTile;
-    if (tid == 0) sTot = 0;
-    __syncthreads();
     bool bad = false;
-    for (int base = 0; base < n; base += 256) {
+    int tot = 0;
+#pragma unroll 1
+    for (int base = 0; base < n; base += kSpreadThreads) {
         const int a = base + tid;
         bool flag = false;
         int ix = 0, iy = 0;
@@ -323,186 +413,107 @@ __global__ __launch_bounds__(256) void k_ib_spread(const BodyDev *__restrict__ b
             flag = ix > X0 - 4 && ix < X0 + kPatchTile && iy > Y0 - 4 && iy < Y0 + kPatchTile;
         }
         const unsigned long long m = __ballot(flag);
-        const int pre = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) sCnt[wv] = __popcll(m);
+        if (lane == 0) L.cnt[wv] = __popcll(m);
         __syncthreads();
-        int off = sTot;
-        for (int w = 0; w < wv; ++w) off += sCnt[w];
+        int q = tot + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int w = 0; w < kSpreadThreads / 64; ++w) {
+            if (w < wv) q += L.cnt[w];
+            tot += L.cnt[w];
+        }
         if (flag) {
-            const int q = off + pre;
             if (q < kMaxCand) {
-                sA[q] = a;
-                sI[q] = make_int2(ix - X0, iy - Y0);
                 const float4 *w = reinterpret_cast<const float4 *>(B.nw) + 2 * a;
-                sW[q][0] = w[0];
-                sW[q][1] = w[1];
-                sF[q] = reinterpret_cast<const double2 *>(B.fnode)[a];
+                L.o[q] = make_int2(ix - X0, iy - Y0);
+                L.w[q][0] = w[0];
+                L.w[q][1] = w[1];
+                L.f[q] = reinterpret_cast<const double2 *>(B.fnode)[a];
             } else {
                 bad = true;
             }
         }
         __syncthreads();
-        if (tid == 0) sTot += sCnt[0] + sCnt[1] + sCnt[2] + sCnt[3];
-        __syncthreads();
     }
-    const int cnt = min(sTot, kMaxCand);
-    const int lx = tid % kPatchTile, ly = tid / kPatchTile;
-    const int px = tx * kPatchTile + lx, py = ty * kPatchTile + ly;
-    if (px < B.ps && py < B.ps) {
-        double fx = 0.0, fy = 0.0;
-        gather_site(sI, sW, sF, cnt, lx, ly, fx, fy);
-        const unsigned i = (unsigned)(py * B.ps + px);
-        B.fib[i] = (float)fx;
-        B.fib[(unsigned)(B.ps * B.ps) + i] = (float)fy;
-    }
+    spread_tile<kSpreadThreads>(B, L, min(tot, kMaxCand), tx, ty);
     if (bad) atomicOr(d_status, kStatusPatch);
 }
 
-// Body update and force spreading in one launch, one 256-thread block per (body, 16x16 tile of
-// its patch).  Every block of a body repeats the node update (a few hundred nodes):
-//  ADVANCE: move the nodes from R(t) to R(t+1) by Heun with the velocity patch written during
-//  step t (App. A: overdamped, no slip); otherwise take R[cur] as it is;
-//  the patch origin for the new positions (3 sites of margin around the nodes), found in the same
-//  pass as the centre of mass;
-//  every node's force at the new positions with the pull at time *d_t (once, each by the thread
-//  that lists the node), and of those the nodes whose 4x4 footprint reaches the tile gathered onto
-//  the tile's sites in node order (deterministic): f_IB(r) = sum_a f_a phi phi (App. A).
-// Tile 0 of each body publishes the new positions, all node forces and the origin; the other
-// blocks only read the current-parity buffers, so blocks never wait on each other.
+// Body update and force spreading in one launch, one block per (body, 16x16 tile of its patch).  Every
+// block of a body repeats phase 1 (a few hundred nodes) and evaluates every node's force with the pull at
+// time *d_t; of those, the nodes whose 4x4 footprint reaches the tile are listed in node order and
+// gathered onto the tile's sites: f_IB(r) = sum_a f_a phi phi (App. A).
+// Tile 0 of each body publishes the new positions, all node forces and the origin; the other blocks
+// only read the current-parity buffers, so blocks never wait on each other.
 template <bool ADVANCE>
-__global__ __launch_bounds__(256) void k_ib_step(const SimDev *__restrict__ sims, BodyDev *__restrict__ bodies,
-                                                 const int2 *__restrict__ blk, int cur, const int *__restrict__ d_t,
-                                                 int *__restrict__ d_status) {
-    __shared__ double2 sR[kMaxNodes];
-    __shared__ double sRed[4][4];
-    __shared__ int2 sI[kMaxCand];
-    __shared__ float4 sW[kMaxCand][2];
-    __shared__ double2 sF[kMaxCand];
-    __shared__ double2 sFall[kMaxNodes];   // every node's force (each thread's own nodes)
-    __shared__ int sCnt[4];
-    __shared__ double sC[4][2];
+__global__ __launch_bounds__(kIbThreads) void k_ib_step(const SimDev *__restrict__ sims, BodyDev *__restrict__ bodies,
+                                                        const int2 *__restrict__ blk, int nmax, int cur,
+                                                        const int *__restrict__ d_t, int *__restrict__ d_status) {
+    extern __shared__ __align__(16) double2 sNodes[];   // 4 nmax
+    __shared__ BodyScratch sc;
+    __shared__ TileNodes L;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int2 bt = blk[blockIdx.x];
-    BodyDev &B = bodies[bt.x];
+    const BodyDev &B = bodies[bt.x];
     const SimDev &S = sims[B.sim];
-    const int n = B.n;
-    const int dst = ADVANCE ? (cur ^ 1) : cur;
+    const BodyNodes N(sNodes, nmax);
+    const int n = B.n, dst = ADVANCE ? (cur ^ 1) : cur;
     const bool lead = bt.y == 0;
     bool bad = false;        // node outside its patch (every block finds the same; tile 0 reports)
     bool overflow = false;   // more footprints reach this tile than it can list
     bool wall = false;       // a node's kernel footprint reaches a wall
-
-    const double2 *Rc = reinterpret_cast<const double2 *>(B.R[cur]);
-    int ox = 0, oy = 0;
-    if (ADVANCE) {
-        ox = B.origin[4 * cur];
-        oy = B.origin[4 * cur + 1];
-    }
-    // one pass for the extent and the centre of mass (the sums in block_com's order)
-    double mnx = 1e300, mny = 1e300, mxx = -1e300, mxy = -1e300, cx = 0.0, cy = 0.0;
-    for (int a = tid; a < n; a += 256) {
-        double2 R = Rc[a];
-        if (ADVANCE) heun_node(B.vib, B.ps, ox, oy, R, bad);
-        sR[a] = R;
-        mnx = fmin(mnx, R.x);
-        mny = fmin(mny, R.y);
-        mxx = fmax(mxx, R.x);
-        mxy = fmax(mxy, R.y);
-        cx += R.x;
-        cy += R.y;
-    }
-    mnx = wave_min(mnx);
-    mny = wave_min(mny);
-    mxx = wave_max(mxx);
-    mxy = wave_max(mxy);
-    cx = wave_sum(cx);
-    cy = wave_sum(cy);
-    if (lane == 0) {
-        sRed[wv][0] = mnx;
-        sRed[wv][1] = mny;
-        sRed[wv][2] = mxx;
-        sRed[wv][3] = mxy;
-        sC[wv][0] = cx;
-        sC[wv][1] = cy;
-    }
-    __syncthreads();
-    const double2 com = make_double2(((sC[0][0] + sC[1][0]) + (sC[2][0] + sC[3][0])) / n,
-                                     ((sC[0][1] + sC[1][1]) + (sC[2][1] + sC[3][1])) / n);
-    mnx = fmin(fmin(sRed[0][0], sRed[1][0]), fmin(sRed[2][0], sRed[3][0]));
-    mny = fmin(fmin(sRed[0][1], sRed[1][1]), fmin(sRed[2][1], sRed[3][1]));
-    mxx = fmax(fmax(sRed[0][2], sRed[1][2]), fmax(sRed[2][2], sRed[3][2]));
-    mxy = fmax(fmax(sRed[0][3], sRed[1][3]), fmax(sRed[2][3], sRed[3][3]));
-    // patch: 3 sites of margin below the lowest node cover the kernel support (2) plus one site of
-    // node motion; the same margin above is checked against the patch side
-    const int nox = (int)floor(mnx) - 3, noy = (int)floor(mny) - 3;
-    if ((int)floor(mxx) + 3 - nox >= B.ps || (int)floor(mxy) + 3 - noy >= B.ps) bad = true;
-
-    const double pf = pull_factor(B, (double)d_t[0]);
-    const double2 trap = trap_share(B, (double)d_t[0], com);
-    // every node's force once, by the thread that lists the node below (so no barrier)
-    for (int a = tid; a < n; a += 256) sFall[a] = node_force(B, sR, a, pf, trap);
-    if (lead) {
-        double2 *Fn = reinterpret_cast<double2 *>(B.fnode);
-        double2 *Rd = reinterpret_cast<double2 *>(B.R[dst]);
-        for (int a = tid; a < n; a += 256) {
-            Fn[a] = sFall[a];
-            if (ADVANCE) Rd[a] = sR[a];
-        }
-        if (tid == 0) {
-            B.origin[4 * dst] = nox;
-            B.origin[4 * dst + 1] = noy;
-            B.origin[4 * dst + 2] = wrapi(nox, S.nx);
-            B.origin[4 * dst + 3] = wrapi(noy, S.ny);
-        }
-    }
-
-    // nodes whose footprint reaches this tile, compacted in node order
+    double2 com = make_double2(0.0, 0.0);
+    const int2 o = body_phase1<ADVANCE>(B, cur, d_t, N, sc, com, bad);
+    const double2 share = node_share(B, sc.at, com);
     const int tx = bt.y % B.nside, ty = bt.y / B.nside;
-    const int X0 = nox + tx * kPatchTile, Y0 = noy + ty * kPatchTile;
+    const int X0 = o.x + tx * kPatchTile, Y0 = o.y + ty * kPatchTile;
     int tot = 0;
-    for (int base = 0; base < n; base += 256) {
+#pragma unroll 1
+    for (int base = 0; base < n; base += kIbThreads) {
         const int a = base + tid;
         bool flag = false;
         int ix = 0, iy = 0;
         float wx[4], wy[4];
+        double2 f = make_double2(0.0, 0.0);
         if (a < n) {
-            const double2 R = sR[a];
+            const double2 R = N.R[a];
+            f = node_force(B, N, a, share);
             phi4(R.x, ix, wx);
             phi4(R.y, iy, wy);
-            if ((S.walls && (iy < 1 || iy + 4 >= S.ny)) || (S.walls == 2 && (ix < 1 || ix + 4 >= S.nx)))
-            wall = true;   // one site of margin for the predicted position
+            wall = wall || at_wall(S, ix, iy);
             flag = ix > X0 - 4 && ix < X0 + kPatchTile && iy > Y0 - 4 && iy < Y0 + kPatchTile;
+            if (lead) {
+                reinterpret_cast<double2 *>(B.fnode)[a] = f;
+                if (ADVANCE) reinterpret_cast<double2 *>(B.R[dst])[a] = R;
+            }
         }
         const unsigned long long m = __ballot(flag);
-        const int pre = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) sCnt[wv] = __popcll(m);
+        if (lane == 0) L.cnt[wv] = __popcll(m);
         __syncthreads();
-        int off = tot;
-        for (int w = 0; w < wv; ++w) off += sCnt[w];
+        int q = tot + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int w = 0; w < kIbThreads / 64; ++w) {
+            if (w < wv) q += L.cnt[w];
+            tot += L.cnt[w];
+        }
         if (flag) {
-            const int q = off + pre;
             if (q < kMaxCand) {
-                sI[q] = make_int2(ix - X0, iy - Y0);
-                sW[q][0] = make_float4(wx[0], wx[1], wx[2], wx[3]);
-                sW[q][1] = make_float4(wy[0], wy[1], wy[2], wy[3]);
-                sF[q] = sFall[a];
+                L.o[q] = make_int2(ix - X0, iy - Y0);
+                L.w[q][0] = make_float4(wx[0], wx[1], wx[2], wx[3]);
+                L.w[q][1] = make_float4(wy[0], wy[1], wy[2], wy[3]);
+                L.f[q] = f;
             } else {
                 overflow = true;
             }
         }
-        tot += sCnt[0] + sCnt[1] + sCnt[2] + sCnt[3];
         __syncthreads();
     }
-    const int cnt = min(tot, kMaxCand);
-    const int lx = tid % kPatchTile, ly = tid / kPatchTile;
-    const int px = tx * kPatchTile + lx, py = ty * kPatchTile + ly;
-    if (px < B.ps && py < B.ps) {
-        double fx = 0.0, fy = 0.0;
-        gather_site(sI, sW, sF, cnt, lx, ly, fx, fy);
-        const unsigned i = (unsigned)(py * B.ps + px);
-        B.fib[i] = (float)fx;
-        B.fib[(unsigned)(B.ps * B.ps) + i] = (float)fy;
+    if (lead && tid == 0) {
+        B.origin[4 * dst] = o.x;
+        B.origin[4 * dst + 1] = o.y;
+        B.origin[4 * dst + 2] = wrapi(o.x, S.nx);
+        B.origin[4 * dst + 3] = wrapi(o.y, S.ny);
     }
+    spread_tile<kIbThreads>(B, L, min(tot, kMaxCand), tx, ty);
     if ((bad && lead) || overflow) atomicOr(d_status, kStatusPatch);
     if (wall && lead) atomicOr(d_status, kStatusWall);
 }
@@ -1687,21 +1698,22 @@ __global__ __launch_bounds__(256) void k_stream_copy(const uint4 *__restrict__ s
 // launch wrappers (host)
 // ------------------------------------------------------------------------------------------------
 
-hipError_t launch_ib(bool advance, int nbodies, int ntiles, hipStream_t st, const SimDev *sims, BodyDev *bodies,
+hipError_t launch_ib(bool advance, int nbodies, int ntiles, int nmax, hipStream_t st, const SimDev *sims, BodyDev *bodies,
                      const int2 *blk, int cur, const int *d_t, int *d_status) {
+    const size_t lds = 4 * (size_t)nmax * sizeof(double2);
     if (nbodies <= 0) return hipSuccess;
     if (ntiles <= kIbOneLaunchTiles) {
         // few tiles: one launch, each block repeats its body's node update
         if (advance)
-            k_ib_step<true><<<ntiles, 256, 0, st>>>(sims, bodies, blk, cur, d_t, d_status);
+            k_ib_step<true><<<ntiles, kIbThreads, lds, st>>>(sims, bodies, blk, nmax, cur, d_t, d_status);
         else
-            k_ib_step<false><<<ntiles, 256, 0, st>>>(sims, bodies, blk, cur, d_t, d_status);
+            k_ib_step<false><<<ntiles, kIbThreads, lds, st>>>(sims, bodies, blk, nmax, cur, d_t, d_status);
     } else {
         if (advance)
-            k_ib_nodes<true><<<nbodies, 256, 0, st>>>(sims, bodies, cur, d_t, d_status);
+            k_ib_nodes<true><<<nbodies, kIbThreads, lds, st>>>(sims, bodies, nmax, cur, d_t, d_status);
         else
-            k_ib_nodes<false><<<nbodies, 256, 0, st>>>(sims, bodies, cur, d_t, d_status);
-        k_ib_spread<<<ntiles, 256, 0, st>>>(bodies, blk, advance ? (cur ^ 1) : cur, d_status);
+            k_ib_nodes<false><<<nbodies, kIbThreads, lds, st>>>(sims, bodies, nmax, cur, d_t, d_status);
+        k_ib_spread<<<ntiles, kSpreadThreads, 0, st>>>(bodies, blk, advance ? (cur ^ 1) : cur, d_status);
     }
     return hipGetLastError();
 }

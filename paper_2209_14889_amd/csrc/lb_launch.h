@@ -9,7 +9,8 @@ namespace lbk {
 // message returned by lb_last_error() on this thread
 void set_last_error(const char *msg);
 
-hipError_t launch_ib(bool advance, int nbodies, int ntiles, hipStream_t st, const SimDev *sims, BodyDev *bodies,
+// nmax: nodes of the largest body
+hipError_t launch_ib(bool advance, int nbodies, int ntiles, int nmax, hipStream_t st, const SimDev *sims, BodyDev *bodies,
                      const int2 *blk, int cur, const int *d_t, int *d_status);
 // walls: the variant with wall handling (needed when any simulation of the launch has walls);
 // pol: the variant with the polarization field (needed unless P is zero in every simulation);

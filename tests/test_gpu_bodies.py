@@ -112,3 +112,46 @@ def test_body_with_the_most_nodes():
     g = lb.Sim(w, lb.make_options())
     check(g, oracle_sim(w.sims[0]), 200)
     g.close()
+
+
+@pytest.mark.parametrize("n,drive", [(40, "constant"), (257, "pull"), (600, "trap and pull")])
+def test_node_steps_of_fast_bodies_and_schedules(n, drive):
+    """Every node step of a body carried by a flow of a tenth of a site per step, so that the second
+    velocity interpolation of the Heun step often starts in another site than the first; fewer nodes
+    than a block has lane pairs, one more than that, and more than it has threads; constant, pulled and
+    trapped, at times around the schedules' switches.
+
+    Each step is checked against the oracle's interpolation of the GPU's own velocity field: the FP32
+    kernel weights (16 products of two cosines of FP32 arguments, each within 4e-7) bound a node's
+    error by 2 * 16 * 4e-7 of the largest velocity.  The total node
+    force is the drive's (the internal forces cancel): FP64, within 1e-14."""
+    import oracle
+    w = wl.small_case(91, 72, 64, n_bodies=1, radius=9.0, pull=2e-4)
+    s = w.sims[0]
+    say(f"case fast body 72x64 seed=91 {n} nodes, {drive}, 50 steps")
+    sched = dict(t_on=10.0, t_off=40.0, width=4.0) if "pull" in drive else {}
+    b = wl.make_body(36.2, 31.7, 9.0, n, (2e-4, -1e-4), k_spring=0.01, **sched)
+    if "trap" in drive:
+        b.trap = dict(k=2e-3, x0=36.2, y0=31.7, dx=4.0, dy=1.0, t1=8.0, t2=48.0, w=3.0)
+    s.bodies = [b]
+    one = np.ones((64, 72))
+    s.h0 = oracle.equilibrium(one, 0.12 * one, -0.07 * one)
+    r = oracle_sim(s)
+    g = lb.Sim(w, lb.make_options(kernel=0))
+    crossed, worst = 0, 0.0
+    for t in range(50):
+        f, R = g.fields(names=["vx", "vy"]), g.nodes()[0]
+        vmax = max(float(np.max(np.abs(f[k]))) for k in f)
+        body = r.bodies[0]
+        body.R = R.copy()
+        total = g.body_force(0, 0)["node_force"]
+        assert np.max(np.abs(total - body.forces(t).sum(axis=0))) <= 1e-14, t
+        v1 = r.interp(R, f["vx"], f["vy"])
+        crossed += int(np.any(np.floor(R + v1) != np.floor(R), axis=1).sum())
+        step = R + 0.5 * (v1 + r.interp(R + v1, f["vx"], f["vy"]))
+        g.step(1)
+        worst = max(worst, float(np.max(np.abs(g.nodes()[0] - step))) / (2 * 16 * 4e-7 * vmax))
+    say(f"  worst node step error / bound {worst:.2e}, {crossed} second interpolations in another site")
+    assert crossed > 20
+    assert worst <= 1.0
+    g.close()
