@@ -419,6 +419,30 @@ struct ItemBody {
     float *vib;
 };
 
+// The only body of a work item (most items that touch one touch just one), its constants in scalar
+// registers.  A site outside the patch takes kOutside as its byte offset: buffer loads return zero there
+// and stores are dropped.
+constexpr unsigned kOutside = 0xfffffff0u;
+struct OneBody {
+    int ox, oy, ps;
+    __amdgpu_buffer_rsrc_t fib, vib;
+};
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T> __device__ __forceinline__ T *uniform(T *p) {
+    const uintptr_t q = (uintptr_t)p;
+    return (T *)((uintptr_t)(unsigned)uniform((int)(unsigned)q) | ((uintptr_t)(unsigned)uniform((int)(unsigned)(q >> 32)) << 32));
+}
+__device__ __forceinline__ OneBody one_body(const ItemBody &B) {
+    OneBody b;
+    b.ox = uniform(B.ox);
+    b.oy = uniform(B.oy);
+    b.ps = uniform(B.ps);
+    const int bytes = 8 * b.ps * b.ps;
+    b.fib = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(uniform(B.fib)), (short)0, bytes, 0x00020000);
+    b.vib = __builtin_amdgcn_make_buffer_rsrc(uniform(B.vib), (short)0, bytes, 0x00020000);
+    return b;
+}
+
 // do the periodic intervals [a, a + la) and [b, b + lb) on a ring of n sites intersect?
 // (0 <= a, b < n)
 __device__ __forceinline__ bool ring_overlap(int a, int la, int b, int lb, int n) {

@@ -640,6 +640,7 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
             PT P0, P1;                     // P(f+1)
             float S0, S1, S2;              // sigma(f)
             typename Pop<HT>::Raw H[9];    // populations pulled into row f-1
+            float F0, F1;                  // the only body's spread force at row f-1 (kOneBody)
         };
         // Values of this column handed from one iteration to the next: stage D's centre row
         // (the corrector's frozen inputs and the next predictor's south neighbours) and stage E's
@@ -652,6 +653,7 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
             float q0, q1, q2;
             PT qp0, qp1;
         };
+        constexpr bool kOneBody = !std::is_same<HT, __half>::value && !WALLS;
         Pre preA, preB;
         Carry carA, carB;
         // Row iterations 0 and 1 would only commit P rows f0 and f0+1 (their stress rows f0-1 and
@@ -678,12 +680,25 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
             preA.S1 = buf_ldf(rSi, b4, N4 + rS0);
             preA.S2 = buf_ldf(rSi, b4, 2u * N4 + rS0);
         }
+        if (kOneBody) preA.F0 = preA.F1 = preB.F0 = preB.F1 = 0.f;
         // Ericksen xy, yy of this column at rows f-1, f-2, f-3
         float exy1 = 0.f, eyy1 = 0.f, exy2 = 0.f, eyy2 = 0.f, exy3 = 0.f, eyy3 = 0.f;
 
         __syncthreads();
         const int nib = sNB;
         const int niter = wi.l + 8;
+        // An item with one body keeps its constants in registers (the column's offset in the patch is the
+        // same for every row, the row's is scalar) and loads the spread force a row ahead.  The FP16 form
+        // takes the list: at four waves a SIMD it would spill; so does the one with walls, which the extra
+        // registers slow down (1400 x 1001 channel 46.1 -> 47.8 us).
+        const bool one = kOneBody && nib == 1;
+        OneBody ob{0, 0, 0, rSi, rSi};
+        unsigned bcol = kOutside;
+        if (one) {
+            ob = one_body(sIB[0]);
+            const int px = wrap_near((int)x - ob.ox, (int)nx);
+            bcol = (unsigned)px < (unsigned)ob.ps ? 4u * (unsigned)px : kOutside;
+        }
 
         // one row iteration j; pin/cin were filled by iteration j-1, pout/cout are for j+1
         auto iterate = [&](const int j, const Pre &pin, Pre &pout, const Carry &cin, Carry &cout) {
@@ -723,6 +738,14 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
                 pout.S0 = buf_ldf(rSi, b4, rS1);
                 pout.S1 = buf_ldf(rSi, b4, N4 + rS1);
                 pout.S2 = buf_ldf(rSi, b4, 2u * N4 + rS1);
+                if (one) {
+                    const int py = wrap_near((int)rm1 - ob.oy, (int)ny);
+                    pout.F0 = pout.F1 = 0.f;
+                    if ((unsigned)py < (unsigned)ob.ps) {
+                        pout.F0 = buf_ldf(ob.fib, bcol, (unsigned)(4 * py * ob.ps));
+                        pout.F1 = buf_ldf(ob.fib, bcol, (unsigned)(4 * (py + ob.ps) * ob.ps));
+                    }
+                }
                 if (!WALLS && j + 1 >= 4) {
                     // periodic: plane and row in the scalar offset, the column in the lane offset
                     const unsigned NH = N * HB, yc = rm1 * nx * HB, ym = rm2 * nx * HB, yp = r0 * nx * HB;
@@ -787,7 +810,10 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
                     fy += (rE[o0][1][te] - rE[o0][1][tw]) + (eyn - eys);
                 }
                 float Fx = fmaf(0.5f, fx, S.gx), Fy = fmaf(0.5f, fy, S.gy);
-                if (nib > 0)
+                if (one) {
+                    Fx += pin.F0;
+                    Fy += pin.F1;
+                } else if (nib > 0)
                     ib_force_list(sIB, nib, (int)nx, (int)ny, (int)x, (int)rm2, Fx, Fy);
                 else if (nib < 0)
                     ib_force(S, bodies, cur, (int)x, (int)rm2, Fx, Fy);
@@ -800,7 +826,13 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
                     const unsigned o = rm2 * nx * HB, NH = N * HB;
 #pragma unroll
                     for (int q = 0; q < 9; ++q) Pop<HT>::st_buf(rHo, bh, (unsigned)q * NH + o, d[q]);
-                    if (nib > 0)
+                    if (one) {
+                        const int py = wrap_near((int)rm2 - ob.oy, (int)ny);
+                        if ((unsigned)py < (unsigned)ob.ps) {
+                            buf_stf(ob.vib, bcol, (unsigned)(4 * py * ob.ps), ux);
+                            buf_stf(ob.vib, bcol, (unsigned)(4 * (py + ob.ps) * ob.ps), uy);
+                        }
+                    } else if (nib > 0)
                         ib_store_v_list(sIB, nib, (int)nx, (int)ny, (int)x, (int)rm2, ux, uy);
                     else if (nib < 0)
                         ib_store_v(S, bodies, cur, (int)x, (int)rm2, ux, uy);
@@ -1104,6 +1136,22 @@ __global__ __launch_bounds__(T, T == 64 ? 2 : 4) void k_tile(const SimDev *__res
             for (int c = 0; c < 3; ++c) rS[c][tid + k * T] = ls[k][c];
     __syncthreads();
     const int nib = sNB;
+    // the spread force of the tile's only body, in flight during the next stage
+    OneBody ob{0, 0, 0, rSi, rSi};
+    unsigned bat[RC];
+    float lf[RC][2];
+    if (nib == 1) {
+        ob = one_body(sIB[0]);
+#pragma unroll
+        for (int k = 0; k < RC; ++k) {
+            const Site q = site(min(tid + k * T, nC - 1), WC, 2);
+            const int px = wrap_near(q.x - ob.ox, nx), py = wrap_near(q.y - ob.oy, ny);
+            bat[k] = (unsigned)px < (unsigned)ob.ps && (unsigned)py < (unsigned)ob.ps ? 4u * (unsigned)(py * ob.ps + px)
+                                                                                    : kOutside;
+            lf[k][0] = buf_ldf(ob.fib, bat[k], 0u);
+            lf[k][1] = buf_ldf(ob.fib, bat[k], (unsigned)(4 * ob.ps * ob.ps));
+        }
+    }
 
     // ---- Ericksen stress
     if (POL) {
@@ -1127,12 +1175,19 @@ __global__ __launch_bounds__(T, T == 64 ? 2 : 4) void k_tile(const SimDev *__res
 #pragma unroll 1
     for (int k = 0; k < RC; ++k) {
         const int i = tid + k * T;
-        float d[9];
+        float d[9], bx = 0.f, by = 0.f;
+        unsigned bo = kOutside;
 #pragma unroll
         for (int r = 0; r < RC; ++r)
-            if (k == r)
+            if (k == r) {
 #pragma unroll
                 for (int q = 0; q < 9; ++q) d[q] = Pop<HT>::cvt_stored(lh[r][q]);
+                if (nib == 1) {
+                    bx = lf[r][0];
+                    by = lf[r][1];
+                    bo = bat[r];
+                }
+            }
         if (i >= nC) continue;
         const Site q = site(i, WC, 2);
         const int c = (q.Y + 1) * WS + q.X + 1;
@@ -1146,7 +1201,10 @@ __global__ __launch_bounds__(T, T == 64 ? 2 : 4) void k_tile(const SimDev *__res
             fy += (U.early.e[2][e] - U.early.e[2][ww]) + (U.early.e[3][n] - U.early.e[3][s]);
         }
         float Fx = fmaf(0.5f, fx, S.gx), Fy = fmaf(0.5f, fy, S.gy);
-        if (nib > 0)
+        if (nib == 1) {
+            Fx += bx;
+            Fy += by;
+        } else if (nib > 1)
             ib_force_list(sIB, nib, nx, ny, q.x, q.y, Fx, Fy);
         else if (nib < 0)
             ib_force(S, bodies, cur, q.x, q.y, Fx, Fy);
@@ -1158,7 +1216,10 @@ __global__ __launch_bounds__(T, T == 64 ? 2 : 4) void k_tile(const SimDev *__res
             const unsigned o = ((unsigned)q.y * (unsigned)nx + (unsigned)q.x) * HB, NH = N * HB;
 #pragma unroll
             for (int m = 0; m < 9; ++m) Pop<HT>::st_buf(rHo, o, (unsigned)m * NH, fmaf(keep, d[m], r[m]));
-            if (nib > 0)
+            if (nib == 1) {
+                buf_stf(ob.vib, bo, 0u, ux);
+                buf_stf(ob.vib, bo, (unsigned)(4 * ob.ps * ob.ps), uy);
+            } else if (nib > 1)
                 ib_store_v_list(sIB, nib, nx, ny, q.x, q.y, ux, uy);
             else if (nib < 0)
                 ib_store_v(S, bodies, cur, q.x, q.y, ux, uy);
