@@ -161,6 +161,10 @@ int lb_step(lb_handle *h, int32_t n_steps);
  * n_out is the capacity of host_out in doubles (LB_ERANGE if too small).  Synchronous. */
 int lb_read_fields(lb_handle *h, int32_t sim, uint32_t field_mask, double *host_out, size_t n_out);
 
+/* lb_read_fields with a buffer of its own, ny*nx doubles, for each selected plane (in bit order;
+ * LB_F_NODES is not a plane). */
+int lb_read_planes(lb_handle *h, int32_t sim, uint32_t field_mask, double *const *host_planes);
+
 /* Body observables at the current time, FP64 (synchronous):
  * out[0..1] restoring force: sum of div sigma^p over the lattice sites inside the node polygon;
  * out[2..3] the current external force (pull plus trap); out[4..5] centre of mass of the nodes;

@@ -1512,34 +1512,43 @@ __global__ __launch_bounds__(256) void k_mp_corr(const SimDev *__restrict__ sims
 // observables and reductions
 // ------------------------------------------------------------------------------------------------
 
-// planes of `out` (floats): drho, vx, vy, sxx, syy, sxy, Px, Py, fpx, fpy at the current time
+// the planes of `mask` (bits 0 .. 9: drho, vx, vy, sxx, syy, sxy, Px, Py, fpx, fpy) at the current time,
+// packed in bit order into `out` (floats).  Only what the mask needs is read: the forces for v and f^p,
+// the populations for rho and v.  Bound by memory, and small beside the copy to the host that follows.
 template <typename HT>
 __global__ __launch_bounds__(256) void k_readout(const SimDev *__restrict__ sims, const BodyDev *__restrict__ bodies,
-                                                 const SiteBlock *__restrict__ blk, int cur, float *__restrict__ out) {
+                                                 const SiteBlock *__restrict__ blk, int cur, unsigned mask,
+                                                 float *__restrict__ out) {
     int sim, x, y;
     if (!site_of(blk, sims, sim, x, y)) return;
     const SimDev &S = sims[sim];
     const size_t N = (size_t)S.nx * S.ny;
     Nb q = nbrs(x, y, S.nx, S.ny, S.walls);
-    float Fx, Fy, fpx, fpy;
-    site_force(S, bodies, cur, x, y, q, Fx, Fy, fpx, fpy);
-    float d[9];
-    pull_pops<HT>(S, reinterpret_cast<const HT *>(S.h[cur]), x, y, d);
-    float drho, ux, uy;
-    collide(d, Fx, Fy, S.omega, S.guo, drho, ux, uy);
+    float *o = out + q.c;
+    auto put = [&](int bit, float v) {
+        if (!((mask >> bit) & 1u)) return;
+        *o = v;
+        o += N;
+    };
+    float Fx = 0.f, Fy = 0.f, fpx = 0.f, fpy = 0.f, drho = 0.f, ux = 0.f, uy = 0.f;
+    if (mask & kReadForce) site_force(S, bodies, cur, x, y, q, Fx, Fy, fpx, fpy);
+    if (mask & kReadPops) {
+        float d[9];
+        pull_pops<HT>(S, reinterpret_cast<const HT *>(S.h[cur]), x, y, d);
+        collide(d, Fx, Fy, S.omega, S.guo, drho, ux, uy);
+    }
     typedef typename PolOf<HT>::T PT;
     const float *sg = S.sig[cur];
     const PT *P = static_cast<const PT *>(S.P[cur]);
-    out[0 * N + q.c] = drho;
-    out[1 * N + q.c] = ux;
-    out[2 * N + q.c] = uy;
-    out[3 * N + q.c] = sg[q.c];
-    out[4 * N + q.c] = sg[N + q.c];
-    out[5 * N + q.c] = sg[2 * N + q.c];
-    out[6 * N + q.c] = (float)((PT)S.pref[0] + P[q.c]);
-    out[7 * N + q.c] = (float)((PT)S.pref[1] + P[N + q.c]);
-    out[8 * N + q.c] = fpx;
-    out[9 * N + q.c] = fpy;
+    put(0, drho);
+    put(1, ux);
+    put(2, uy);
+    for (int k = 0; k < 3; ++k)
+        if ((mask >> (3 + k)) & 1u) put(3 + k, sg[k * N + q.c]);
+    for (int k = 0; k < 2; ++k)
+        if ((mask >> (6 + k)) & 1u) put(6 + k, (float)((PT)S.pref[k] + P[k * N + q.c]));
+    put(8, fpx);
+    put(9, fpy);
 }
 
 // block partial sums (FP64) of drho and sum_n c_n d_n over the stored populations of one sim;
@@ -1846,15 +1855,17 @@ hipError_t launch_multipass(bool fp16, int nblocks, hipStream_t st, const SimDev
 }
 
 hipError_t launch_readout(bool fp16, int nblocks, int block0, hipStream_t st, const SimDev *sims, const BodyDev *bodies,
-                          const SiteBlock *blk, int cur, float *out) {
+                          const SiteBlock *blk, int cur, unsigned mask, float *out) {
+    if (mask & kReadForce) {
+        if (fp16)
+            k_mp_sigE<float><<<nblocks, 256, 0, st>>>(sims, blk + block0, cur, nullptr);
+        else
+            k_mp_sigE<double><<<nblocks, 256, 0, st>>>(sims, blk + block0, cur, nullptr);
+    }
     if (fp16)
-        k_mp_sigE<float><<<nblocks, 256, 0, st>>>(sims, blk + block0, cur, nullptr);
+        k_readout<__half><<<nblocks, 256, 0, st>>>(sims, bodies, blk + block0, cur, mask, out);
     else
-        k_mp_sigE<double><<<nblocks, 256, 0, st>>>(sims, blk + block0, cur, nullptr);
-    if (fp16)
-        k_readout<__half><<<nblocks, 256, 0, st>>>(sims, bodies, blk + block0, cur, out);
-    else
-        k_readout<float><<<nblocks, 256, 0, st>>>(sims, bodies, blk + block0, cur, out);
+        k_readout<float><<<nblocks, 256, 0, st>>>(sims, bodies, blk + block0, cur, mask, out);
     return hipGetLastError();
 }
 

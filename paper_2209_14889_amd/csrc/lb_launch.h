@@ -24,8 +24,11 @@ hipError_t launch_tile(int T, bool fp16, bool walls, bool pol, hipStream_t st, c
 int fused_blocks_per_cu(int T, bool fp16, bool walls, bool pol);
 hipError_t launch_multipass(bool fp16, int nblocks, hipStream_t st, const SimDev *sims, const BodyDev *bodies,
                             const SiteBlock *blk, int cur, int *d_t);
+// the planes of `mask` (bits 0 .. 9 in the order of lb_read_fields), packed into out
+constexpr unsigned kReadForce = 0x306u;   // those that need the force density: vx, vy, fpx, fpy
+constexpr unsigned kReadPops = 0x007u;    // those that need the populations: rho, vx, vy
 hipError_t launch_readout(bool fp16, int nblocks, int block0, hipStream_t st, const SimDev *sims,
-                          const BodyDev *bodies, const SiteBlock *blk, int cur, float *out);
+                          const BodyDev *bodies, const SiteBlock *blk, int cur, unsigned mask, float *out);
 hipError_t launch_sums(bool fp16, int sim, int nblocks, hipStream_t st, const SimDev *sims, int cur, double *partial,
                        double *out, double check_mass, int *d_status);
 // body observables of bodies body0 .. body0+nbodies-1, 6 doubles each into out

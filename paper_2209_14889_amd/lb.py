@@ -83,6 +83,7 @@ def lib():
                                 ctypes.c_size_t, vp, ctypes.POINTER(vp)]
         L.lb_step.argtypes = [vp, ctypes.c_int32]
         L.lb_read_fields.argtypes = [vp, ctypes.c_int32, ctypes.c_uint32, _dp, ctypes.c_size_t]
+        L.lb_read_planes.argtypes = [vp, ctypes.c_int32, ctypes.c_uint32, ctypes.POINTER(_dp)]
         L.lb_body_force.argtypes = [vp, ctypes.c_int32, ctypes.c_int32, _dp]
         L.lb_conservation.argtypes = [vp, ctypes.c_int32, _dp]
         L.lb_body_forces.argtypes = [vp, _dp, ctypes.c_size_t]
@@ -97,8 +98,8 @@ def lib():
         L.lb_state_bytes.argtypes = [vp, _dp]
         L.lb_stream_copy.argtypes = [vp, vp, ctypes.c_size_t, vp]
         L.lb_last_error.restype = ctypes.c_char_p
-        for name in ("lb_query_arena_bytes", "lb_create", "lb_step", "lb_read_fields", "lb_body_force",
-                     "lb_conservation", "lb_sync", "lb_time", "lb_timing", "lb_destroy", "lb_launch_shape",
+        for name in ("lb_query_arena_bytes", "lb_create", "lb_step", "lb_read_fields", "lb_read_planes",
+                     "lb_body_force", "lb_conservation", "lb_sync", "lb_time", "lb_timing", "lb_destroy", "lb_launch_shape",
                      "lb_body_forces", "lb_body_forces_device", "lb_state_bytes", "lb_stream_copy"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
@@ -241,11 +242,10 @@ class Sim:
         for nm in names:
             mask |= 1 << FIELDS.index(nm)
         s = self.specs[sim]
-        N = s.nx * s.ny
-        out = np.empty(len(names) * N)
-        check(lib().lb_read_fields(self.h, sim, mask, out.ctypes.data_as(_dp), out.size))
-        order = [f for f in FIELDS if f in names]
-        return {nm: out[i * N:(i + 1) * N].reshape(s.ny, s.nx).copy() for i, nm in enumerate(order)}
+        out = {f: np.empty((s.ny, s.nx)) for f in FIELDS if f in names}
+        planes = (_dp * max(1, len(out)))(*(a.ctypes.data_as(_dp) for a in out.values()))
+        check(lib().lb_read_planes(self.h, sim, mask, planes))
+        return out
 
     def nodes(self, sim: int = 0) -> list:
         s = self.specs[sim]
