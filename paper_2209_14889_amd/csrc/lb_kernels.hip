@@ -1611,49 +1611,70 @@ __global__ __launch_bounds__(64) void k_sums_final(const SimDev *__restrict__ si
     }
 }
 
-// Integral along the directed edge (xa, ya) -> (xb, yb), restricted to y0 <= y <= y1, of
-// g(x) dy with g(x) = clamp(x, x0, x1) - x0.  Summed over a closed polygon this is, by Green's
-// theorem, the signed area of the polygon inside the box [x0, x1] x [y0, y1].  g is piecewise
-// linear along the edge, so the midpoint rule on the pieces between its kinks is exact.
-__device__ __forceinline__ double edge_box(double xa, double ya, double xb, double yb, double x0, double x1,
-                                           double y0, double y1) {
-    const double lo = fmax(fmin(ya, yb), y0), hi = fmin(fmax(ya, yb), y1);
-    if (!(hi > lo)) return 0.0;   // outside the band, or a horizontal edge
-    const double s = (xb - xa) / (yb - ya);
-    const double xl = xa + s * (lo - ya), xh = xa + s * (hi - ya);
-    double ta = 0.0, tb = 0.0;
-    if (xh != xl) {
-        const double inv = 1.0 / (xh - xl);
-        ta = fmin(fmax((x0 - xl) * inv, 0.0), 1.0);
-        tb = fmin(fmax((x1 - xl) * inv, 0.0), 1.0);
-        if (ta > tb) {
-            const double u = ta;
-            ta = tb;
-            tb = u;
-        }
+// What one directed edge (xa, ya) -> (xb, yb) of a polygon adds to the site X and the unit cell around it,
+// in the row Y: where it crosses the row (NaN if it does not), and the integral along its part within
+// [Y - 1/2, Y + 1/2] of g(x) dy with g(x) = clamp(x, x0, x1) - x0.  Summed over a closed polygon the latter
+// is, by Green's theorem, the signed area of the polygon inside the cell [x0, x1] x [Y - 1/2, Y + 1/2].  g is
+// piecewise linear along the edge, so the midpoint rule on the pieces between its kinks is exact.
+struct RowEdge {
+    double cross;        // the row is crossed here: sites to the left of it are inside or outside by it
+    double xl, dx, inv;  // x at the lower end of the part in the band, its extent, 1 / extent (0 if none)
+    double c;            // signed height of the part
+};
+__device__ __forceinline__ bool touches_row(double ya, double yb, double Y) {
+    return fmin(fmax(ya, yb), Y + 0.5) > fmax(fmin(ya, yb), Y - 0.5);   // horizontal edges do not
+}
+__device__ __forceinline__ RowEdge row_edge(double2 a, double2 b, double Y) {
+    const double lo = fmax(fmin(a.y, b.y), Y - 0.5), hi = fmin(fmax(a.y, b.y), Y + 0.5);
+    const double s = (b.x - a.x) / (b.y - a.y);
+    RowEdge e;
+    e.cross = (b.y > Y) != (a.y > Y) ? (a.x - b.x) * (Y - b.y) / (a.y - b.y) + b.x : __builtin_nan("");
+    e.xl = a.x + s * (lo - a.y);
+    e.dx = (a.x + s * (hi - a.y)) - e.xl;
+    e.inv = e.dx != 0.0 ? 1.0 / e.dx : 0.0;
+    e.c = (b.y > a.y ? 1.0 : -1.0) * (hi - lo);
+    return e;
+}
+__device__ __forceinline__ double cell_share(const RowEdge &e, double x0, double x1) {
+    double ta = fmin(fmax((x0 - e.xl) * e.inv, 0.0), 1.0), tb = fmin(fmax((x1 - e.xl) * e.inv, 0.0), 1.0);
+    if (ta > tb) {
+        const double u = ta;
+        ta = tb;
+        tb = u;
     }
-    auto g = [&](double t) { return fmin(fmax(xl + t * (xh - xl), x0), x1) - x0; };
-    const double integral = ta * g(0.5 * ta) + (tb - ta) * g(0.5 * (ta + tb)) + (1.0 - tb) * g(0.5 * (tb + 1.0));
-    return (yb > ya ? 1.0 : -1.0) * (hi - lo) * integral;
+    auto g = [&](double t) { return fmin(fmax(e.xl + t * e.dx, x0), x1) - x0; };
+    return e.c * (ta * g(0.5 * ta) + (tb - ta) * g(0.5 * (ta + tb)) + (1.0 - tb) * g(0.5 * (tb + 1.0)));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {   // the same lane for the whole wave
+    const long long q = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)q, lane), hi = __builtin_amdgcn_readlane((unsigned)(q >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// body observables, one 256-thread block per body: restoring force as the sum of div sigma over
+// body observables, one 1024-thread block per body: restoring force as the sum of div sigma over
 // the sites inside the node polygon (even-odd rule), centre of mass, total node force, and the
 // area-weighted restoring force: the sum over sites of (area of the site's unit cell inside the
-// polygon) * div sigma, which varies continuously with the node positions
-__global__ __launch_bounds__(256) void k_body_force(const SimDev *__restrict__ sims, const BodyDev *__restrict__ bodies,
-                                                    int body0, int cur, double *__restrict__ out_all) {
+// polygon) * div sigma, which varies continuously with the node positions.
+// Bound by the chain of one wave's FP64 instructions.  A wave takes 64 sites of a row at a time; its lanes
+// first look at 64 edges at once and work out those few that touch the row, which then go round the wave
+// one by one.  (Every site against every edge, with its divisions, in one wave a SIMD: 64 bodies of radius
+// 4 to 32 took 542 us, now 33; 32 of radius 4 to 16 took 91, now 21.)
+constexpr int kForceThreads = 1024;
+__global__ __launch_bounds__(kForceThreads) void k_body_force(const SimDev *__restrict__ sims,
+                                                              const BodyDev *__restrict__ bodies, int body0, int cur,
+                                                              double *__restrict__ out_all) {
+    constexpr int kWaves = kForceThreads / 64;
     __shared__ double2 sR[kMaxNodes];
-    __shared__ double sh[9][4];
+    __shared__ double sh[9][kWaves];
     const BodyDev &B = bodies[body0 + blockIdx.x];
     double *out = out_all + kBodyOut * blockIdx.x;
     const SimDev &S = sims[B.sim];
-    const int n = B.n, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n = B.n, tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
     const double2 *R = reinterpret_cast<const double2 *>(B.R[cur]);
     const double2 *Fn = reinterpret_cast<const double2 *>(B.fnode);
     double mnx = 1e300, mny = 1e300, mxx = -1e300, mxy = -1e300, cx = 0, cy = 0, fx = 0, fy = 0, ar = 0;
-    for (int a = tid; a < n; a += 256) {
-        double2 r = R[a], q = R[a == 0 ? n - 1 : a - 1];
+    for (int a = tid; a < n; a += kForceThreads) {
+        double2 r = R[a], q = R[a == 0 ? n - 1 : a - 1], f = Fn[a];
         sR[a] = r;
         mnx = fmin(mnx, r.x);
         mny = fmin(mny, r.y);
@@ -1661,8 +1682,8 @@ __global__ __launch_bounds__(256) void k_body_force(const SimDev *__restrict__ s
         mxy = fmax(mxy, r.y);
         cx += r.x;
         cy += r.y;
-        fx += Fn[a].x;
-        fy += Fn[a].y;
+        fx += f.x;
+        fy += f.y;
         ar += q.x * r.y - r.x * q.y;
     }
     double v9[9] = {wave_min(mnx), wave_min(mny), wave_max(mxx), wave_max(mxy),
@@ -1670,73 +1691,77 @@ __global__ __launch_bounds__(256) void k_body_force(const SimDev *__restrict__ s
     if (lane == 0)
         for (int k = 0; k < 9; ++k) sh[k][wv] = v9[k];
     __syncthreads();
-    mnx = fmin(fmin(sh[0][0], sh[0][1]), fmin(sh[0][2], sh[0][3]));
-    mny = fmin(fmin(sh[1][0], sh[1][1]), fmin(sh[1][2], sh[1][3]));
-    mxx = fmax(fmax(sh[2][0], sh[2][1]), fmax(sh[2][2], sh[2][3]));
-    mxy = fmax(fmax(sh[3][0], sh[3][1]), fmax(sh[3][2], sh[3][3]));
-    double scx = (sh[4][0] + sh[4][1]) + (sh[4][2] + sh[4][3]);
-    double scy = (sh[5][0] + sh[5][1]) + (sh[5][2] + sh[5][3]);
-    double sfx = (sh[6][0] + sh[6][1]) + (sh[6][2] + sh[6][3]);
-    double sfy = (sh[7][0] + sh[7][1]) + (sh[7][2] + sh[7][3]);
-    const double orient = (sh[8][0] + sh[8][1]) + (sh[8][2] + sh[8][3]) < 0.0 ? -1.0 : 1.0;
+    double all[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) all[k] = sh[k][0];
+#pragma unroll 1
+    for (int w = 1; w < kWaves; ++w)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) all[k] = k < 2 ? fmin(all[k], sh[k][w]) : k < 4 ? fmax(all[k], sh[k][w]) : all[k] + sh[k][w];
+    mnx = all[0];
+    mny = all[1];
+    mxx = all[2];
+    mxy = all[3];
+    const double orient = all[8] < 0.0 ? -1.0 : 1.0;
     __syncthreads();
     const size_t N = (size_t)S.nx * S.ny;
     const float *sg = S.sig[cur];
-    auto divx = [&](const Nb &q) {
-        return 0.5 * ((double)sg[q.e] - (double)sg[q.w]) + 0.5 * ((double)sg[2 * N + q.n] - (double)sg[2 * N + q.s]);
-    };
-    auto divy = [&](const Nb &q) {
-        return 0.5 * ((double)sg[2 * N + q.e] - (double)sg[2 * N + q.w]) + 0.5 * ((double)sg[N + q.n] - (double)sg[N + q.s]);
-    };
-    // sites strictly inside (even-odd)
-    double ax = 0.0, ay = 0.0;
-    {
-        const int x0 = (int)ceil(mnx), x1 = (int)floor(mxx), y0 = (int)ceil(mny), y1 = (int)floor(mxy);
-        const int wdt = x1 - x0 + 1, hgt = y1 - y0 + 1;
-        for (int i = tid; i < wdt * hgt; i += 256) {
-            const int X = x0 + i % wdt, Y = y0 + i / wdt;
-            bool in = false;
-            for (int a = 0, b = n - 1; a < n; b = a++) {
-                double xa = sR[a].x, ya = sR[a].y, xb = sR[b].x, yb = sR[b].y;
-                if ((ya > Y) != (yb > Y) && X < (xb - xa) * (Y - ya) / (yb - ya) + xa) in = !in;
+    // every cell that the bounding box touches; the sites strictly inside it are among them
+    const int x0 = (int)floor(mnx + 0.5), x1 = (int)ceil(mxx - 0.5), y0 = (int)floor(mny + 0.5), y1 = (int)ceil(mxy - 0.5);
+    const int ix0 = (int)ceil(mnx), ix1 = (int)floor(mxx), iy0 = (int)ceil(mny), iy1 = (int)floor(mxy);
+    double ax = 0.0, ay = 0.0, bx = 0.0, by = 0.0;
+    // a body that has outgrown its patch (a status of its own reports it) has no sums
+    const bool whole = x1 >= x0 && y1 >= y0 && mxx - mnx < (double)B.ps && mxy - mny < (double)B.ps;
+    const int across = whole ? (x1 - x0) / 64 + 1 : 0, units = whole ? across * (y1 - y0 + 1) : 0;
+    if (!whole) ax = ay = bx = by = __builtin_nan("");
+    for (int u = wv; u < units; u += kWaves) {
+        const int Y = y0 + u / across, X = x0 + (u % across) * 64 + lane;
+        const Nb q = nbrs(wrapi(min(X, x1), S.nx), wrapi(Y, S.ny), S.nx, S.ny, S.walls);
+        const double e0 = sg[q.e], w0 = sg[q.w], n1 = sg[N + q.n], s1 = sg[N + q.s];
+        const double e2 = sg[2 * N + q.e], w2 = sg[2 * N + q.w], n2 = sg[2 * N + q.n], s2 = sg[2 * N + q.s];
+        bool in = false;
+        double w = 0.0;
+        for (int a0 = 0; a0 < n; a0 += 64) {
+            const int a = a0 + lane;
+            const double2 to = sR[min(a, n - 1)], from = sR[a == 0 ? n - 1 : min(a, n) - 1];
+            const bool mine = a < n && touches_row(from.y, to.y, Y);
+            unsigned long long hit = __ballot(mine);
+            if (!hit) continue;
+            RowEdge own{};
+            if (mine) own = row_edge(from, to, Y);
+            for (; hit; hit &= hit - 1) {
+                const int k = __builtin_ctzll(hit);
+                const RowEdge e{lane_value(own.cross, k), lane_value(own.xl, k), lane_value(own.dx, k),
+                                lane_value(own.inv, k), lane_value(own.c, k)};
+                in = in != ((double)X < e.cross);
+                w += cell_share(e, X - 0.5, X + 0.5);
             }
-            if (!in) continue;
-            Nb q = nbrs(wrapi(X, S.nx), wrapi(Y, S.ny), S.nx, S.ny, S.walls);
-            ax += divx(q);
-            ay += divy(q);
         }
-    }
-    // every cell [X - 1/2, X + 1/2] x [Y - 1/2, Y + 1/2] the bounding box touches, weighted by area
-    double bx = 0.0, by = 0.0;
-    {
-        const int x0 = (int)floor(mnx + 0.5), x1 = (int)ceil(mxx - 0.5), y0 = (int)floor(mny + 0.5),
-                  y1 = (int)ceil(mxy - 0.5);
-        const int wdt = x1 - x0 + 1, hgt = y1 - y0 + 1;
-        for (int i = tid; i < wdt * hgt; i += 256) {
-            const int X = x0 + i % wdt, Y = y0 + i / wdt;
-            double w = 0.0;
-            for (int a = 0, b = n - 1; a < n; b = a++)
-                w += edge_box(sR[b].x, sR[b].y, sR[a].x, sR[a].y, X - 0.5, X + 0.5, Y - 0.5, Y + 0.5);
-            w *= orient;
-            if (w == 0.0) continue;
-            Nb q = nbrs(wrapi(X, S.nx), wrapi(Y, S.ny), S.nx, S.ny, S.walls);
-            bx += w * divx(q);
-            by += w * divy(q);
+        if (X > x1) continue;
+        const double dx = 0.5 * (e0 - w0) + 0.5 * (n2 - s2), dy = 0.5 * (e2 - w2) + 0.5 * (n1 - s1);
+        if (in && X >= ix0 && X <= ix1 && Y >= iy0 && Y <= iy1) {
+            ax += dx;
+            ay += dy;
+        }
+        w *= orient;
+        if (w != 0.0) {
+            bx += w * dx;
+            by += w * dy;
         }
     }
     double red[4] = {wave_sum(ax), wave_sum(ay), wave_sum(bx), wave_sum(by)};
     if (lane == 0)
         for (int k = 0; k < 4; ++k) sh[k][wv] = red[k];
     __syncthreads();
-    if (tid == 0) {
-        out[0] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
-        out[1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
-        out[2] = scx / n;
-        out[3] = scy / n;
-        out[4] = sfx;
-        out[5] = sfy;
-        out[6] = (sh[2][0] + sh[2][1]) + (sh[2][2] + sh[2][3]);
-        out[7] = (sh[3][0] + sh[3][1]) + (sh[3][2] + sh[3][3]);
+    if (tid < 4) {
+        double v = 0.0;
+        for (int w = 0; w < kWaves; ++w) v += sh[tid][w];
+        out[tid < 2 ? tid : tid + 4] = v;
+    } else if (tid == 4) {
+        out[2] = all[4] / n;
+        out[3] = all[5] / n;
+        out[4] = all[6];
+        out[5] = all[7];
     }
 }
 
@@ -1882,7 +1907,7 @@ hipError_t launch_sums(bool fp16, int sim, int nblocks, hipStream_t st, const Si
 hipError_t launch_body_force(hipStream_t st, const SimDev *sims, const BodyDev *bodies, int body0, int nbodies, int cur,
                              double *out) {
     if (nbodies <= 0) return hipSuccess;
-    k_body_force<<<nbodies, 256, 0, st>>>(sims, bodies, body0, cur, out);
+    k_body_force<<<nbodies, kForceThreads, 0, st>>>(sims, bodies, body0, cur, out);
     return hipGetLastError();
 }
 
