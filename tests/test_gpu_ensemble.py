@@ -196,3 +196,23 @@ def test_scalar_variant_matches_oracle():
         say(f"  {k} {e:.2e}")
         assert e <= 1e-4, k
     assert np.max(np.abs(g.nodes()[0] - r.bodies[0].R)) <= 1e-5
+
+
+@pytest.mark.parametrize("threads,seg", [(256, 17), (128, 24), (64, 40)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_unlike_members_dealt_by_work(threads, seg, precision):
+    """One round of items of unlike work (more than one per compute unit, fewer than are resident): every
+    member is the same lattice as on its own, to the bit."""
+    specs = wl.c4(18).sims
+    ens = lb.Sim(specs, lb.make_options(precision=precision, fused_threads=threads, seg_rows=seg))
+    assert ens.launch_shape()["n_items"] > 256
+    ens.step(7)
+    for i, s in enumerate(specs):
+        one = lb.Sim(s, lb.make_options(precision=precision))
+        one.step(7)
+        a, b = ens.fields(i), one.fields(0)
+        for k in lb.FIELDS:
+            np.testing.assert_array_equal(a[k], b[k], err_msg=f"{i} {k}")
+        np.testing.assert_array_equal(ens.nodes(i)[0], one.nodes(0)[0])
+        one.close()
+    ens.close()
