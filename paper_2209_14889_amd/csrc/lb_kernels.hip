@@ -329,52 +329,71 @@ struct TileNodes {
     int cnt[kIbThreads / 64];
 };
 
-// f_IB at tile site (lx, ly): the listed nodes' f_a phi(x) phi(y), the entries first, first + step, ...
-// in order.  The LDS reads of four entries are issued before any of them is used, so each group
-// costs one LDS round trip.
-__device__ __forceinline__ double2 gather(const TileNodes &L, int cnt, int lx, int ly, int first, int step) {
-    double2 s = make_double2(0.0, 0.0);
+// f_IB at tile site (lx, ly): the listed nodes' f_a phi(x) phi(y), of the entries with an even number (h 0),
+// an odd one (h 1) or of both apart (s[0], s[1]), each in order.  The wave's sites are [x0, x1] x [y0, y1]: its
+// lanes first look at 64 entries at once, and only those that reach them are read and weighed, the LDS
+// reads of four entries before any of them is used.  An entry costs some forty instructions of the chain, and
+// of the nodes of an arc across the tile about half reach a wave's 8 x 4 sites (whole rows of the tile, 16 x 2,
+// gain nothing from an arc along them: 512^2 22.2 us a step, with 8 x 4 21.6, every entry 21.7; 64^2 14.1, 14.1
+// and 14.6; 32 pulled bodies 32.3, 32.2 and 32.8).
+template <bool BOTH>
+__device__ __forceinline__ void gather(const TileNodes &L, int cnt, int lx, int ly, int x0, int y0, int x1, int y1, int h, double2 s[2]) {
+    constexpr unsigned long long kEven = 0x5555555555555555ull;
+    const int lane = threadIdx.x & 63;
 #pragma unroll 1
-    for (int q = first; q < cnt; q += 4 * step) {
-        int2 o[4];
-        float4 wx[4], wy[4];
-        double2 f[4];
+    for (int base = 0; base < cnt; base += 64) {
+        const int2 at = L.o[min(base + lane, kMaxCand - 1)];
+        const unsigned long long near =
+            __ballot(base + lane < cnt && at.y <= y1 && at.y + 4 > y0 && at.x <= x1 && at.x + 4 > x0);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = min(q + step * u, kMaxCand - 1);
-            o[u] = L.o[e];
-            wx[u] = L.w[e][0];
-            wy[u] = L.w[e][1];
-            f[u] = L.f[e];
-        }
+        for (int p = 0; p < (BOTH ? 2 : 1); ++p) {
+            unsigned long long m = near & ((BOTH ? p : h) ? kEven << 1 : kEven);
+#pragma unroll 1
+            for (int left = max(__popcll(near & kEven), __popcll(near & (kEven << 1))); left > 0; left -= 4) {
+                int2 o[4];
+                float4 wx[4], wy[4];
+                double2 f[4];
+                bool have[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = lx - o[u].x, j = ly - o[u].y;
-            if (q + step * u < cnt && (unsigned)i < 4u && (unsigned)j < 4u) {
-                const float wxs = i == 0 ? wx[u].x : i == 1 ? wx[u].y : i == 2 ? wx[u].z : wx[u].w;
-                const float wys = j == 0 ? wy[u].x : j == 1 ? wy[u].y : j == 2 ? wy[u].z : wy[u].w;
-                const double w = (double)wxs * (double)wys;
-                s.x += f[u].x * w;
-                s.y += f[u].y * w;
+                for (int u = 0; u < 4; ++u) {
+                    have[u] = m != 0;
+                    const int e = base + (have[u] ? __builtin_ctzll(m) : 0);
+                    m &= m - 1;
+                    o[u] = L.o[e];
+                    wx[u] = L.w[e][0];
+                    wy[u] = L.w[e][1];
+                    f[u] = L.f[e];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = lx - o[u].x, j = ly - o[u].y;
+                    if (have[u] && (unsigned)i < 4u && (unsigned)j < 4u) {
+                        const float wxs = i == 0 ? wx[u].x : i == 1 ? wx[u].y : i == 2 ? wx[u].z : wx[u].w;
+                        const float wys = j == 0 ? wy[u].x : j == 1 ? wy[u].y : j == 2 ? wy[u].z : wy[u].w;
+                        const double w = (double)wxs * (double)wys;
+                        s[p].x += f[u].x * w;
+                        s[p].y += f[u].y * w;
+                    }
+                }
             }
         }
     }
-    return s;
 }
 
-// the listed nodes' forces on the 16 x 16 sites of tile (tx, ty) of a body's patch, by 256 threads, or
-// 512 with a pair of lanes per site (lane h then stores component h).  The even and the odd entries are
+// the listed nodes' forces on the 16 x 16 sites of tile (tx, ty) of a body's patch, by 256 threads (8 x 8 sites
+// to a wave), or 512 (8 x 4) with a pair of lanes per site (lane h then stores component h).  The even and the odd entries are
 // summed apart and then added, so both give the same bits.
 template <int THREADS>
 __device__ __forceinline__ void spread_tile(const BodyDev &B, const TileNodes &L, int cnt, int tx, int ty) {
     constexpr bool pair = THREADS == 2 * kPatchTile * kPatchTile;
     const int s = pair ? threadIdx.x >> 1 : threadIdx.x, h = pair ? threadIdx.x & 1 : 0;
-    const int lx = s % kPatchTile, ly = s / kPatchTile, px = tx * kPatchTile + lx, py = ty * kPatchTile + ly;
-    double2 a = gather(L, cnt, lx, ly, h, 2), b;
-    if (pair)
-        b = make_double2(__shfl_xor(a.x, 1), __shfl_xor(a.y, 1));
-    else
-        b = gather(L, cnt, lx, ly, 1, 2);
+    constexpr int kRows = pair ? 4 : 8;   // of a wave's sites
+    const int wv = uniform((int)(threadIdx.x >> 6)), x0 = (wv & 1) * 8, y0 = (wv >> 1) * kRows;
+    const int lx = x0 + s % 8, ly = y0 + s / 8 % kRows, px = tx * kPatchTile + lx, py = ty * kPatchTile + ly;
+    double2 part[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+    gather<!pair>(L, cnt, lx, ly, x0, y0, x0 + 7, y0 + kRows - 1, h, part);
+    double2 a = part[0], b = part[1];
+    if (pair) b = make_double2(__shfl_xor(a.x, 1), __shfl_xor(a.y, 1));
     a.x += b.x;
     a.y += b.y;
     if (px < B.ps && py < B.ps) {
