@@ -343,9 +343,9 @@ __global__ __launch_bounds__(256) void k_weights(Grads gr, int batch, float *__r
 // the first layer to the last.
 constexpr int kNarrow = 512;
 
-// LDS row stride in BF16 values for rows of n: 8 words more than a multiple of 64, so that the 16 rows
-// of an operand read spread over all banks
-constexpr __host__ __device__ int row_stride(int n) { return ((n + 127) & ~127) + 16; }
+// LDS row stride in BF16 values for rows of n: 4 words more than a multiple of 64, so that the 16 rows
+// of an operand read spread over all banks (a training step of 256 rows 43.0 us; with 2 words 43.3, 8 words 44.4)
+constexpr __host__ __device__ int row_stride(int n) { return ((n + 127) & ~127) + 8; }
 
 constexpr int kWaves = 16;      // waves of a narrow-network block
 constexpr int kPanel = 128;     // k of the weights that a wave stages at a time
@@ -366,11 +366,11 @@ struct Net {
 // are handed on through two LDS buffers.  The first layer, whose few inputs need no 16-byte rows, takes
 // single loads.  The products, their order and the epilogues are those of k_gemm, so the results are
 // the same bits.
-// What bounds it: at a few hundred rows a chain of dependent steps (one round of loads per panel, and
-// the fetch of the code itself, which every launch starts cold: the same kernel unrolled to 8.4 KB of
-// code took 16-27 us for 512 rows, this form of 4.2 KB 13), at tens of thousands the tanh (about 40
-// instructions a value).
-// 512 rows of 5-256-256-256-64: 31 -> 13 us against a launch per layer; 65 536 rows 210 -> 90 us.
+// What bounds it: at a few hundred rows a chain of dependent steps (one round of loads per panel, some
+// eight cycles for each instruction of a wave; deeper unrolled forms were slower, 16-27 us for 512 rows
+// against 13), at tens of thousands the vector instructions, most of them the tanh (about 30 a value: 50
+// of the 97 us for 65 536 rows, the products 16).
+// 512 rows of 5-256-256-256-64: 31 -> 12.5 us against a launch per layer; 65 536 rows 210 -> 97 us.
 // KEEP: every hidden layer's activations are also stored, in FP32, for the backward pass.
 struct Kept {
     float *act[8];
