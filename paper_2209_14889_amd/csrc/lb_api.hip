@@ -479,13 +479,19 @@ std::vector<WorkItem> build_items(const std::vector<SimPlan> &sims, int T, int s
 }
 
 // Whether items of `rows` rows go as tiles.  A tile is a short chain (6.5-9 us for any lattice whose
-// tiles are all resident at once, where marching items take 17-23), but computes more halo: from about
-// seven tiles a compute unit on, items marching down their rows win (FP32, no bodies, tiles against the
-// best marching shape: 512^2, 4 tiles a unit, 14.1 against 21 us; 640^2, 6.3 a unit, 21.0 against
-// 21.4; 32 lattices of 128^2, 8 a unit, 22.5 against 21.1; 768^2, 9 a unit, 26.1 against 25.8; 900^2,
-// 12.8 a unit, 34.4 against 30.3).
-bool tiles_pay(const std::vector<SimPlan> &sims, int T, int rows, int cus) {
-    return rows >= kTileMinRows && rows <= tile_rows(T) && count_tiles(sims, T, rows) <= 7 * (size_t)cus;
+// tiles are all resident at once, where marching items take 17-23), but computes more halo: with more tiles
+// a compute unit, items marching down their rows win.  The line, steps with one body a lattice, tiles
+// against the best marching shape: FP32, 640^2, 6.25 tiles a unit, 29.7 against 30.0 us; 680^2, 7.3, 31.8 against
+// 30.4.  Lattices of up to 128 columns march without halo columns, so earlier: 20 of 128^2, 5 a unit, 28.0
+// against 28.1; 24 of them, 6 a unit, 30.1 against 28.8; 96 of 64^2, 6 a unit, 37.3 against 36.6.  FP16 tiles
+// are resident eight to a unit: 28 of 128^2, 7 a unit, 30.5 against 32.1; 700^2, 7.6, 28.8 against 28.9; 720^2,
+// 8.1, 32.8 against 28.8.
+bool tiles_pay(const std::vector<SimPlan> &sims, int T, int rows, int cus, bool fp16) {
+    if (rows < kTileMinRows || rows > tile_rows(T)) return false;
+    int widest = 0;
+    for (const SimPlan &sp : sims) widest = std::max(widest, sp.nx);
+    const size_t halves = fp16 ? 16 : widest <= 128 ? 11 : 13;   // of a tile a unit
+    return 2 * count_tiles(sims, T, rows) <= halves * (size_t)cus;
 }
 
 std::vector<WorkItem> build_tiles(const std::vector<SimPlan> &sims, int T, int rows) {
@@ -503,12 +509,15 @@ std::vector<WorkItem> build_tiles(const std::vector<SimPlan> &sims, int T, int r
 }
 
 // cost model of one fused launch: work items run in rounds of `slots` resident work-groups and
-// an item of seg rows takes seg + 8 row iterations (the pipeline fill)
-int model_seg(const std::vector<SimPlan> &sims, int T, int slots) {
+// an item of seg rows takes seg + 8 row iterations (the pipeline fill).  From three rows on: where they
+// still fit in one round they beat four (700^2 33.1 -> 30.8 us a step); two rows gain nothing more.  The item
+// table (`room`) is sized for four: narrow strips of three rows may not fit.
+int model_seg(const std::vector<SimPlan> &sims, int T, int slots, size_t room) {
     int best = 8;
     double best_cost = 1e300;
-    for (int seg = 4; seg <= 128; ++seg) {
+    for (int seg = 3; seg <= 128; ++seg) {
         size_t items = build_items(sims, T, seg).size();
+        if (items > room) continue;
         double rounds = std::ceil((double)items / slots);
         double cost = rounds * (seg + 8) + 1e-3 * seg;   // ties: shorter segments
         if (cost < best_cost) {
@@ -836,7 +845,7 @@ int place_body_items(lb_handle *h, std::vector<WorkItem> &items) {
 // grid: 0 = one work-group per item; > 0 = persistent grid of that many work-groups (a multiple
 // of 8, so each XCD keeps a contiguous run of items) looping over the item table
 int upload_items(lb_handle *h, int T, int seg, int grid = 0) {
-    h->tiles = grid <= 0 && h->d_tiles && tiles_pay(h->plan.sims, T, seg, h->cus);
+    h->tiles = grid <= 0 && h->d_tiles && tiles_pay(h->plan.sims, T, seg, h->cus, h->opt.precision == 1);
     if (h->tiles && count_tiles(h->plan.sims, T, seg) > h->plan.max_tiles) h->tiles = false;
     std::vector<WorkItem> items = h->tiles ? build_tiles(h->plan.sims, T, seg) : build_items(h->plan.sims, T, seg);
     if (h->tiles) {
@@ -957,17 +966,18 @@ int choose_fused_config(lb_handle *h) {
         T = model_T();
         if (!h->opt.threads && sites > 2048) T = std::max(T, 128);
         rows = kTileMinRows;
-        if (count_tiles(h->plan.sims, T, rows) * (size_t)(T / 64) <= 8 * (size_t)cus && tiles_pay(h->plan.sims, T, rows, h->cus))
+        if (count_tiles(h->plan.sims, T, rows) * (size_t)(T / 64) <= 8 * (size_t)cus && tiles_pay(h->plan.sims, T, rows, h->cus, fp16))
             return true;
         T = h->opt.threads ? T : 256;
         rows = 8;
-        return tiles_pay(h->plan.sims, T, rows, h->cus);
+        return tiles_pay(h->plan.sims, T, rows, h->cus, fp16);
     };
     if (!h->opt.autotune) {
         int T = 0, rows = 0;
         if (model_tiles(T, rows)) return upload_items(h, T, rows);
         T = model_T();
-        int seg = h->opt.seg ? h->opt.seg : model_seg(h->plan.sims, T, cus * fused_blocks_per_cu(T, fp16, h->any_walls, h->any_pol));
+        int seg = h->opt.seg ? h->opt.seg : model_seg(h->plan.sims, T, cus * fused_blocks_per_cu(T, fp16, h->any_walls, h->any_pol),
+                                                     h->plan.items.size());
         return upload_items(h, T, seg, h->opt.grid);
     }
     const uint64_t key = tune_key(h, h->params, dev);
@@ -991,7 +1001,7 @@ int choose_fused_config(lb_handle *h) {
     for (int T : {64, 128, 256}) {
         if (h->opt.threads && T != h->opt.threads) continue;
         int slots = cus * fused_blocks_per_cu(T, fp16, h->any_walls, h->any_pol);
-        int m = model_seg(h->plan.sims, T, slots);
+        int m = model_seg(h->plan.sims, T, slots, h->plan.items.size());
         for (int seg : {m, std::max(4, m / 2), m * 2, m + 4, std::max(4, m - 4), 64}) {
             for (int grid : {0, (slots / 8) * 8}) {
                 Cand c{T, seg, grid};

@@ -69,3 +69,35 @@ def test_arena_without_room_for_tiles():
     for k in lb.FIELDS:
         assert np.array_equal(f[k], f2[k]), k
     g.close()
+
+
+@pytest.mark.parametrize("walls", [0, 1, 2])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_marching_items_of_three_rows(walls, precision):
+    """The shortest marching items that the launch model takes (the last ones of two and three rows of 91)
+    against long ones; a grid of one work-group per item keeps both from being tiles."""
+    w = wl.small_case(21, 150, 91, n_bodies=1, radius=8.0, walls=walls)
+    want = None
+    for threads, seg in ((256, 91), (256, 3), (128, 3)):
+        g = lb.Sim(w, lb.make_options(precision=precision, fused_threads=threads, seg_rows=seg, grid=1 << 20))
+        g.step(9)
+        f = g.fields()
+        want = f if want is None else want
+        for k in lb.FIELDS:
+            np.testing.assert_array_equal(f[k], want[k], err_msg=f"{threads} {seg} {k}")
+        g.close()
+
+
+@pytest.mark.parametrize("nx,threads", [(24, 0), (56, 0), (57, 64), (112, 64), (113, 128), (240, 256)])
+def test_the_model_fits_the_item_table(nx, threads):
+    """Widths whose strips fill the item table at four rows an item: the chosen shape must fit and step."""
+    w = wl.small_case(21, nx, 90, n_bodies=0)
+    one = lb.Sim(w)
+    g = lb.Sim(w, lb.make_options(fused_threads=threads, grid=1 << 20))
+    one.step(5)
+    g.step(5)
+    a, b = one.fields(), g.fields()
+    for k in lb.FIELDS:
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+    one.close()
+    g.close()
