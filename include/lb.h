@@ -121,7 +121,8 @@ typedef struct {
 } lb_options;
 
 /* Bytes of device memory lb_create needs for these simulations (arena for all state, tables,
- * patches and scratch).  sims: n_sims parameter sets; opt may be NULL (defaults). */
+ * patches and scratch).  sims: n_sims parameter sets; opt may be NULL (defaults).  The figure includes
+ * the table of the tile items (at most 256 KiB, the last part of the arena). */
 int lb_query_arena_bytes(const lb_sim_params *sims, int32_t n_sims, const lb_options *opt,
                          size_t *bytes);
 
@@ -132,7 +133,8 @@ int lb_query_arena_bytes(const lb_sim_params *sims, int32_t n_sims, const lb_opt
  * 0 < P_clamp < 1, eta_p > 0, sizes, node counts, that every body's force patch fits the
  * lattice and that no two bodies' bounding circles (centre of the nodes, farthest node)
  * intersect, across periodic directions too (LB_EINVAL otherwise, also for an arena not 256-byte aligned; LB_ENOMEM if arena_bytes
- * is smaller than lb_query_arena_bytes).  Uploads the initial state and spreads the initial body
+ * is smaller than lb_query_arena_bytes by more than the tile table: without room for that table
+ * the items march).  Uploads the initial state and spreads the initial body
  * forces; synchronous. */
 int lb_create(const lb_sim_params *sims, int32_t n_sims, const lb_options *opt,
               void *device_arena, size_t arena_bytes, void *hip_stream, lb_handle **out);

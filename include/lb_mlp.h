@@ -31,7 +31,9 @@ typedef struct {
     float beta1, beta2, eps;/* Adam coefficients (0 selects 0.9, 0.999, 1e-8) */
 } lb_mlp_config;
 
-/* Device bytes for the parameters, gradients, Adam moments and activations of max_batch rows. */
+/* Device bytes for the parameters, gradients, Adam moments, activations of max_batch rows and the hidden
+ * layers' errors.  (lb_mlp_create also takes an arena with room for two layers' errors only; gradients and
+ * training steps then run layer by layer.) */
 int lb_mlp_query_bytes(const lb_mlp_config *cfg, size_t *bytes);
 
 /* Number of FP32 parameters. */
@@ -69,7 +71,8 @@ int lb_mlp_destroy(lb_mlp *m);
  * (batch x w[L]): device FP32, row major.  The hidden activations live in a fixed scratch array of
  * the library in each GPU's memory (2^20 floats, 4 MiB, held until the process ends; its address
  * is looked up on the first call on a device): batch x (widest hidden layer) must not exceed
- * 2^19 (LB_ERANGE otherwise).  Every call on one GPU uses that GPU's array, so calls that may
+ * 2^19 (LB_ERANGE otherwise).  Networks of widths up to 512 hold them in the compute units instead, with
+ * the same limit.  Every other call on one GPU uses that GPU's array, so calls that may
  * overlap on one GPU (different streams, threads) race; calls in order on one stream are safe.
  * Same products and results as lb_mlp_forward.  Asynchronous on hip_stream. */
 int lb_mlp_forward_noalloc(const lb_mlp_config *cfg, const float *params, const float *X, int32_t batch,
