@@ -184,7 +184,7 @@ struct LayerGrad {
 };
 struct Grads {
     LayerGrad l[8];
-    int n, blocks;         // layers; blocks of all of them (one more takes the mean loss)
+    int n, blocks, bias;   // layers; blocks of all their tiles, and of all their biases (64 columns each)
 };
 struct Adam {
     float *p, *m1, *m2;
@@ -192,8 +192,8 @@ struct Adam {
 };
 
 __device__ __forceinline__ void adam_update(const Adam &o, float gi, float &p, float &m1, float &m2) {
-    float a = o.b1 * m1 + (1.0f - o.b1) * gi;
-    float b = o.b2 * m2 + (1.0f - o.b2) * gi * gi;
+    const float a = fmaf(1.0f - o.b1, gi, o.b1 * m1);   // written out: the same bits wherever it is inlined
+    const float b = fmaf(gi, (1.0f - o.b2) * gi, o.b2 * m2);
     m1 = a;
     m2 = b;
     p -= o.lr * (a / o.c1) / (sqrtf(b / o.c2) + o.eps);
@@ -203,9 +203,9 @@ __device__ __forceinline__ void adam_update(const Adam &o, float gi, float &p, f
 // with STEP the Adam update of the parameters on the spot (the gradients then need no memory); else
 // they go to G.  Half the threads load 4 x 4 blocks of dZ, the other half of A, 64 rows of the batch
 // a trip, transposed in registers; each of the four waves multiplies 16 x 16 in the order of the
-// rows.  The first block along K of each layer also sums its columns of dZ, each thread the values it
-// loads anyway, then the 16 threads of a column in a fixed order.  The last block takes the mean of
-// the rows' losses.
+// rows.  Further blocks take the mean of the rows' losses and the biases: 64 columns of dZ, every fourth
+// row by one wave in order, 16 loads in flight, beside the tiles (the order of k_colsum: Adam's first steps
+// turn the last bit of a sum that cancels into a step of either sign).
 // Bounded by the chain of loads over the batch and the fetch of its code: hence one small tile a wave
 // (a 64 x 64 tile's 16 values a lane cost 15 KB of unrolled update), and more blocks than units.
 // A training step of 256 rows of the 256-wide network: 134 us in 19 launches -> 39 us in three
@@ -215,9 +215,36 @@ template <bool STEP>
 __global__ __launch_bounds__(256) void k_weights(Grads gr, int batch, float *__restrict__ G, Adam adam,
                                                  const float *__restrict__ rows, float *__restrict__ loss) {
     __shared__ __align__(16) short S[2][2][WT][LDK];   // [buffer][dZ, A]
-    __shared__ float part[16 * WT];
+    __shared__ float part[256];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if ((int)blockIdx.x >= gr.blocks) {
+    if ((int)blockIdx.x > gr.blocks) {
+        int q = 0, t = (int)blockIdx.x - gr.blocks - 1;
+#pragma unroll 1
+        for (; t >= (gr.l[q].N + 63) / 64; ++q) t -= (gr.l[q].N + 63) / 64;
+        const LayerGrad &l = gr.l[q];
+        const int N = l.N, n = t * 64 + lane;
+        float s = 0.f;
+#pragma unroll 1
+        for (int k = wv; k < batch; k += 64) {
+            const __amdgpu_buffer_rsrc_t b = operand_rsrc(l.dZ + (long)k * N);
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = load1(b, n < N && k + 4 * i < batch ? 4u * (unsigned)(4 * i * N + n) : kOut);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s += v[i];
+        }
+        part[tid] = s;
+        __syncthreads();
+        if (wv != 0 || n >= N) return;
+        const float g = (part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]);
+        const long at = l.oW + (long)N * l.K + n;
+        if (STEP)
+            adam_update(adam, g, adam.p[at], adam.m1[at], adam.m2[at]);
+        else
+            G[at] = g;
+        return;
+    }
+    if ((int)blockIdx.x == gr.blocks) {
         float s = 0.f;
         for (int i = tid; i < batch; i += 256) s += rows[i];
         part[tid] = s;
@@ -241,7 +268,7 @@ __global__ __launch_bounds__(256) void k_weights(Grads gr, int batch, float *__r
     const int ld = half ? K : N, left = ld - (half ? n0 : m0) - c4;
     const float *src = (half ? l.A + n0 : l.dZ + m0);
     const int wm = (wv >> 1) * 16, wn = (wv & 1) * 16, r = lane & 15, g4 = (lane >> 4) * 4;
-    f32x4 acc{0.f, 0.f, 0.f, 0.f}, sum{0.f, 0.f, 0.f, 0.f};
+    f32x4 acc{0.f, 0.f, 0.f, 0.f};
     auto products = [&](auto vec) {
         f32x4 v[4];
         auto load = [&](int k0) {
@@ -262,7 +289,6 @@ __global__ __launch_bounds__(256) void k_weights(Grads gr, int batch, float *__r
 #pragma unroll 1
         for (int k0 = 0, s = 0; k0 < batch; k0 += TK, s ^= 1) {
             // buffer s was last read two trips ago, before the previous trip's barrier
-            sum += (v[0] + v[1]) + (v[2] + v[3]);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 *reinterpret_cast<bf16x4 *>(&S[s][half][c4 + j][k4]) = bf16_rne4(f32x4{v[0][j], v[1][j], v[2][j], v[3][j]});
@@ -281,60 +307,36 @@ __global__ __launch_bounds__(256) void k_weights(Grads gr, int batch, float *__r
         products(std::true_type{});
     else
         products(std::false_type{});
-    float *const out = STEP ? adam.p : G;
-    auto put = [&](const bool in[4], const long at[4], f32x4 g) {
-        if (!STEP) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (in[i]) out[at[i]] = g[i];
-            return;
-        }
-        float p[4], m1[4], m2[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const long o = in[i] ? at[i] : 0;
-            p[i] = adam.p[o];
-            m1[i] = adam.m1[o];
-            m2[i] = adam.m2[o];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            adam_update(adam, g[i], p[i], m1[i], m2[i]);
-            if (in[i]) {
-                adam.p[at[i]] = p[i];
-                adam.m1[at[i]] = m1[i];
-                adam.m2[at[i]] = m2[i];
-            }
-        }
-    };
     bool in[4];
     long at[4];
-    f32x4 g = acc;
-#pragma unroll 1
-    for (int pass = 0;; ++pass) {   // the tile's weights, then (first blocks only) its biases
-        if (pass == 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = m0 + wm + g4 + i, n = n0 + wn + r;
-                in[i] = m < N && n < K;
-                at[i] = l.oW + (long)m * K + n;
-            }
-        } else {
-            const int m = m0 + (tid & (WT - 1));
-            float s = 0.f;
-#pragma unroll 1
-            for (int k = 0; k < 16; ++k) s += part[k * WT + (tid & (WT - 1))];
-            g = f32x4{s, 0.f, 0.f, 0.f};
-            in[0] = tid < WT && m < N;
-            in[1] = in[2] = in[3] = false;
-            at[0] = l.oW + (long)N * K + m;
+    for (int i = 0; i < 4; ++i) {
+        const int m = m0 + wm + g4 + i, n = n0 + wn + r;
+        in[i] = m < N && n < K;
+        at[i] = l.oW + (long)m * K + n;
+    }
+    if (!STEP) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (in[i]) G[at[i]] = acc[i];
+        return;
+    }
+    float p[4], m1[4], m2[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const long o = in[i] ? at[i] : 0;
+        p[i] = adam.p[o];
+        m1[i] = adam.m1[o];
+        m2[i] = adam.m2[o];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        adam_update(adam, acc[i], p[i], m1[i], m2[i]);
+        if (in[i]) {
+            adam.p[at[i]] = p[i];
+            adam.m1[at[i]] = m1[i];
+            adam.m2[at[i]] = m2[i];
         }
-        put(in, at, g);
-        if (n0 != 0 || pass == 1) break;
-        if (half == 0)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) part[(u >> 3) * WT + c4 + j] = sum[j];
-        __syncthreads();
     }
 }
 
@@ -880,6 +882,7 @@ void add_layer(Grads &g, lb_mlp *m, int l, const float *dZ, const float *A) {
     const int tn = (K + WT - 1) / WT;
     g.l[g.n++] = LayerGrad{dZ, A, (long)m->lo.oW[l], N, K, vec(dZ, N) && vec(A, K), g.blocks, tn};
     g.blocks += tn * ((N + WT - 1) / WT);
+    g.bias += (N + 63) / 64;
 }
 
 // Forward pass, loss and gradients of the mean squared relative error: with `adam` the update of the
@@ -920,9 +923,9 @@ int gradients(lb_mlp *m, const float *X, const float *Y, int B, const Adam *adam
         }
         for (int l = 0; l < L; ++l) add_layer(g, m, l, m->dz(l), l > 0 ? m->act(l - 1) : X);
         if (adam)
-            k_weights<true><<<g.blocks + 1, 256, 0, m->stream>>>(g, B, nullptr, *adam, m->rows(), loss);
+            k_weights<true><<<g.blocks + 1 + g.bias, 256, 0, m->stream>>>(g, B, nullptr, *adam, m->rows(), loss);
         else
-            k_weights<false><<<g.blocks + 1, 256, 0, m->stream>>>(g, B, m->G(), Adam{}, m->rows(), loss);
+            k_weights<false><<<g.blocks + 1 + g.bias, 256, 0, m->stream>>>(g, B, m->G(), Adam{}, m->rows(), loss);
         HIPCHK(hipGetLastError());
         return LB_OK;
     }
@@ -936,7 +939,7 @@ int gradients(lb_mlp *m, const float *X, const float *Y, int B, const Adam *adam
         const float *Aprev = l > 0 ? m->act(l - 1) : X;
         g = Grads{};
         add_layer(g, m, l, dZ, Aprev);
-        k_weights<false><<<g.blocks + 1, 256, 0, m->stream>>>(g, B, m->G(), Adam{}, m->rows(), loss);
+        k_weights<false><<<g.blocks + 1 + g.bias, 256, 0, m->stream>>>(g, B, m->G(), Adam{}, m->rows(), loss);
         HIPCHK(hipGetLastError());
         if (l > 0) {
             HIPCHK((gemm<EPI_TANH_GRAD, true, false>(dZ, N, m->P() + lo.oW[l], K, dA, B, K, N, nullptr, Aprev, m->stream)));
