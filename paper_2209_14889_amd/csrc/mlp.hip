@@ -57,11 +57,14 @@ __device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, unsigned off) {
 // the thread takes the 4 x 4 block of rows r0 .. r0+3 and k4 .. k4+3, v[i] holding k4 + i.
 // VEC: p and ld, and with ld the extent along the contiguous direction, are multiples of four
 // floats.  Values outside R x K are zero.
-template <bool KC, bool VEC>
+// Buffer offsets are taken from the tile's corner and hold 63 rows (or k) of up to kLongRow floats: any
+// network's, whose widths are at most 4096.  LONG: rows beyond that (lb_mlp_gemm_bf16 only), 64-bit
+// addresses and a branch around what lies outside.
+constexpr long kLongRow = 1l << 23;
+static_assert(4 * (63 * kLongRow + 64) <= 0x7fffffff, "a tile's offsets stay within its buffer resource");
+template <bool KC, bool VEC, bool LONG>
 __device__ __forceinline__ void tile_load(f32x4 v[4], const float *__restrict__ p, long ld, int R, int K, int row, int k0) {
     const int t = threadIdx.x;
-    // offsets are taken from the tile's corner: at most 64 rows (or k) of ld <= 4096 floats in the
-    // network, and of ld < 2^23 in lb_mlp_gemm_bf16
     const __amdgpu_buffer_rsrc_t src = operand_rsrc(KC ? p + (long)row * ld + k0 : p + (long)k0 * ld + row);
     const unsigned l = (unsigned)ld;
 #pragma unroll
@@ -69,6 +72,18 @@ __device__ __forceinline__ void tile_load(f32x4 v[4], const float *__restrict__ 
         const int r = KC ? (t >> 4) + 16 * i : (t & 15) * 4;
         const int k = KC ? (t & 15) * 4 : (t >> 4) * 4 + i;
         const int n = KC ? (row + r < R ? K - k0 - k : 0) : (k0 + k < K ? R - row - r : 0);   // values left
+        if (LONG) {
+            const float *q = p + (KC ? (long)(row + r) * ld + k0 + k : (long)(k0 + k) * ld + row + r);
+            v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (VEC) {
+                if (n > 0) v[i] = *reinterpret_cast<const f32x4 *>(q);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (j < n) v[i][j] = q[j];
+            }
+            continue;
+        }
         const unsigned o = 4u * (KC ? (unsigned)r * l + (unsigned)k : (unsigned)k * l + (unsigned)r);
         if (VEC) {
             v[i] = load4(src, n > 0 ? o : kOut);
@@ -106,7 +121,7 @@ struct Stage {   // the two LDS buffers of both operands' tiles
 // trip of 16 of k with scalar loads and two barriers, same results bit for bit: the four products of
 // a 512-row forward pass of the 256-wide network 104 -> 31 us, one of 1000 x 1000 x 1000 78-152 -> about
 // 30 us.
-template <bool AK, bool BK, bool VEC>
+template <bool AK, bool BK, bool VEC, bool LONG>
 __device__ __forceinline__ void product_tile(Stage &S, f32x4 acc[2][2], const float *__restrict__ A, long lda,
                                              const float *__restrict__ B, long ldb, int M, int N, int K, int m0,
                                              int n0) {
@@ -115,16 +130,16 @@ __device__ __forceinline__ void product_tile(Stage &S, f32x4 acc[2][2], const fl
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 va[4], vb[4];
-    tile_load<AK, VEC>(va, A, lda, M, K, m0, 0);
-    tile_load<BK, VEC>(vb, B, ldb, N, K, n0, 0);
+    tile_load<AK, VEC, LONG>(va, A, lda, M, K, m0, 0);
+    tile_load<BK, VEC, LONG>(vb, B, ldb, N, K, n0, 0);
     for (int k0 = 0, s = 0; k0 < K; k0 += TK, s ^= 1) {
         // buffer s was last read two trips ago, before the previous trip's barrier
         tile_store<AK>(S.a[s], va);
         tile_store<BK>(S.b[s], vb);
         __syncthreads();
         if (k0 + TK < K) {
-            tile_load<AK, VEC>(va, A, lda, M, K, m0, k0 + TK);
-            tile_load<BK, VEC>(vb, B, ldb, N, K, n0, k0 + TK);
+            tile_load<AK, VEC, LONG>(va, A, lda, M, K, m0, k0 + TK);
+            tile_load<BK, VEC, LONG>(vb, B, ldb, N, K, n0, k0 + TK);
         }
         // operand layout of the 16x16x16 BF16 MFMA: lane l holds A(l%16, 4*(l/16)+0..3) and
         // B(4*(l/16)+0..3, l%16)
@@ -144,14 +159,14 @@ __device__ __forceinline__ void product_tile(Stage &S, f32x4 acc[2][2], const fl
 
 // D(m, n) = epilogue(product).  Epilogues: + bias[n]; tanh(+ bias); times (1 - aux(m, n)^2) with aux
 // row-major M x N (the tanh derivative from stored activations).
-template <int EPI, bool AK, bool BK, bool VEC>
+template <int EPI, bool AK, bool BK, bool VEC, bool LONG = false>
 __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long lda, const float *__restrict__ B, long ldb,
                                               float *__restrict__ D, int M, int N, int K,
                                               const float *__restrict__ bias, const float *__restrict__ aux) {
     __shared__ __align__(16) Stage S;
     const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
     f32x4 acc[2][2];
-    product_tile<AK, BK, VEC>(S, acc, A, lda, B, ldb, M, N, K, m0, n0);
+    product_tile<AK, BK, VEC, LONG>(S, acc, A, lda, B, ldb, M, N, K, m0, n0);
     // result layout: lane l holds D(4*(l/16)+q, l%16), q = 0..3
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int c = n0 + (wv & 1) * 32 + (lane & 15), rq = m0 + (wv >> 1) * 32 + (lane >> 4) * 4;
@@ -781,6 +796,14 @@ hipError_t gemm(const float *A, long lda, const float *B, long ldb, float *D, in
     // 16-byte loads where every row (or k) of the operand starts on 16 bytes
     auto vec = [](const float *p, long ld) { return ((uintptr_t)p & 15) == 0 && (ld & 3) == 0; };
     dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
+    if constexpr (EPI == EPI_STORE)
+        if (std::max(lda, ldb) > kLongRow) {
+            if (vec(A, lda) && vec(B, ldb))
+                k_gemm<EPI, AK, BK, true, true><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
+            else
+                k_gemm<EPI, AK, BK, false, true><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
+            return hipGetLastError();
+        }
     if (vec(A, lda) && vec(B, ldb))
         k_gemm<EPI, AK, BK, true><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
     else

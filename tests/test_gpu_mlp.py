@@ -73,6 +73,36 @@ def test_gemm_bf16_tile_edges(M, N, K, offset):
     assert np.all(np.abs(D.cpu().numpy() - bf16(A) @ bf16(B)) <= K * 2.0 ** -24 * scale + 1e-30)
 
 
+@pytest.mark.parametrize("M,N,K", [(2, 20_000_004, 65), (3, 9_000_001, 66), (66, 1, 9_000_001), (65, 2, 20_000_004)])
+def test_gemm_bf16_rows_beyond_a_tiles_buffer_range(M, N, K):
+    """Rows so long that 64 of them pass 2^31 and 2^32 bytes, of either operand, from 16-byte and scalar
+    loads.  Small whole numbers: every product and sum is exact, so the result is too."""
+    import torch
+    from paper_2209_14889_amd import mlp
+    rng = np.random.default_rng(M + N + K)
+
+    def whole(*shape):
+        return torch.from_numpy(rng.integers(-3, 4, shape).astype(np.float32)).cuda()
+
+    if N > K:
+        row = torch.arange(N, device="cuda", dtype=torch.int32) % 7 - 3
+        A, B = whole(M, K), torch.empty((K, N), dtype=torch.float32, device="cuda")
+        for k in range(K):
+            B[k] = torch.roll(row, k)
+        want = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+        for m in range(M):
+            for k in range(K):
+                want[m] += A[m, k] * B[k]
+    else:
+        at = torch.from_numpy(np.unique(np.r_[0, 1, K // 2, K - 2, K - 1, rng.integers(0, K, 50)])).cuda()
+        A, B = torch.zeros((M, K), dtype=torch.float32, device="cuda"), whole(K, N)
+        A[:, at] = whole(M, at.numel()).abs() + 1
+        want = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+        for j in at.tolist():
+            want += A[:, j:j + 1] * B[j:j + 1]
+    assert torch.equal(mlp.gemm_bf16(A, B), want)
+
+
 @pytest.mark.parametrize("widths,batch", [
     ([5, 256, 256, 256, 64], 1), ([5, 256, 256, 256, 64], 17), ([5, 256, 256, 256, 64], 4097),
     ([5, 256, 256, 256, 64], 8193 + 15), ([3, 512, 20, 512, 1], 33), ([130, 4], 5), ([7, 300, 100, 65], 70),
