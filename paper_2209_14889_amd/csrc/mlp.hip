@@ -367,6 +367,14 @@ constexpr __host__ __device__ int row_stride(int n) { return ((n + 127) & ~127) 
 constexpr int kWaves = 16;      // waves of a narrow-network block
 constexpr int kPanel = 128;     // k of the weights that a wave stages at a time
 
+// Between a wave's stores to its own panel and the reads of it by other lanes, and between those and the
+// next panel's stores.  A wave's LDS accesses are performed in the order of the code, so nothing is
+// waited for; what the fence holds is the compiler, to which the lanes are threads of their own.
+__device__ __forceinline__ void order_wave_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 struct Net {
     int L;
     int w[9];
@@ -480,6 +488,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_forward(Net net, const float *_
             bias = b.bias;
             b = issue(now);
         }
+        order_wave_lds();
         if (p.kc == 0)
 #pragma unroll
             for (int t = 0; t < RT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -492,6 +501,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_forward(Net net, const float *_
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, w, acc[t], 0, 0, 0);
             }
         }
+        order_wave_lds();
         if (p.kc + kPanel < p.K) continue;
         if (p.l + 1 == L) {
             if (n < p.N)
@@ -658,6 +668,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_backward(Net net, Chain ch, con
                 a[q] = load1(src, n < p.K && m0 + g4 + q < B ? 4u * (unsigned)((g4 + q) * p.K + n) : kOut);
         }
         b = issue(now);
+        order_wave_lds();
         if (p.kc == 0) acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 2
         for (int j = 0; j < steps; j += 16) {
@@ -665,6 +676,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_backward(Net net, Chain ch, con
             const bf16x4 d = *reinterpret_cast<const bf16x4 *>(in + r * S + j + g4);
             acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(d, w, acc, 0, 0, 0);
         }
+        order_wave_lds();
         if (p.kc + kPanel < p.N) continue;
         f32x4 v;
         float *dz = ch.dz[p.l - 1];
