@@ -873,8 +873,14 @@ int upload_items(lb_handle *h, int T, int seg, int grid = 0) {
 
 // ---- autotune cache: one line per tuned key, "lbtune1 <key> <threads> <seg_rows> <grid> <ms>" ----
 
+// What a shape (threads, rows, grid) stands for, raised with every change of the field kernels or of the
+// rules that pick one of them for a shape, so that shapes timed with other kernels are tuned again:
+// 2: short items as tiles where they pay.
+constexpr uint64_t kShapeMeaning = 2;
+
 // FNV-1a over everything the tuned shape depends on: the lattices (sizes, walls, P or not), the
-// storage precision, the field kernel, a forced work-group size, and the GPU (model, CUs)
+// storage precision, the field kernel, a forced work-group size, the GPU (model, CUs), what a shape means
+// and whether there is a table for tiles (without one the same shape marches)
 uint64_t tune_key(const lb_handle *h, const std::vector<lb_sim_params> &sims, int dev) {
     uint64_t k = 1469598103934665603ull;
     auto mix = [&](uint64_t v) {
@@ -891,6 +897,8 @@ uint64_t tune_key(const lb_handle *h, const std::vector<lb_sim_params> &sims, in
     mix((uint64_t)h->opt.precision);
     mix((uint64_t)h->opt.kernel);
     mix((uint64_t)h->opt.threads);
+    mix(kShapeMeaning);
+    mix((uint64_t)(h->d_tiles != nullptr));
     mix((uint64_t)sims.size());
     for (const auto &p : sims) {
         mix((uint64_t)p.nx);

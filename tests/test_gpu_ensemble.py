@@ -142,6 +142,40 @@ def test_autotune_cache(tmp_path):
     assert len(lines()) == 3
 
 
+def _former_tune_key(sim, precision, threads):
+    """The autotune file's key of one simulation as it was when every shape marched."""
+    import torch
+    prop = torch.cuda.get_device_properties(0)
+    k = 1469598103934665603
+    for v in [ord(c) for c in prop.gcnArchName] + [prop.multi_processor_count, precision, 0, threads, 1, sim.nx,
+                                                    sim.ny, sim.params.get("walls", 0), int(sim.P0 is not None)]:
+        for b in v.to_bytes(8, "little"):
+            k = ((k ^ b) * 1099511628211) % 2 ** 64
+    return k
+
+
+def test_autotune_cache_knows_the_kernel_of_a_shape(tmp_path):
+    """A shape that was tuned when all items marched is not taken for the tiles that it names now, nor one
+    tuned with a table for tiles by a handle whose arena has no room for them."""
+    import ctypes
+    cache = str(tmp_path / "tune.txt")
+    opt = lb.make_options(autotune=1, autotune_cache=cache)
+    s = wl.small_case(65, 96, 80, n_bodies=1).sims[0]
+    with open(cache, "w") as f:
+        f.write("lbtune1 %016x 64 4 0 123.5\n" % _former_tune_key(s, 0, 0))
+    g = lb.Sim([s], opt)
+    assert g.launch_shape()["tuned_ms"] != 123.5
+    lb.check(lb.lib().lb_destroy(g.h))
+    m, h = lb._Marshal([s]), ctypes.c_void_p()
+    lb.check(lb.lib().lb_create(m.params, 1, ctypes.byref(opt), ctypes.c_void_p(g.arena.data_ptr()),
+                                ctypes.c_size_t(g.arena.numel() - 256), ctypes.c_void_p(g.stream.cuda_stream),
+                                ctypes.byref(h)))
+    g.h = h
+    g.close()
+    with open(cache) as f:
+        assert len({line.split()[1] for line in f}) == 3
+
+
 def test_body_update_paths_agree():
     """Many patch tiles (here about a thousand) take the two-launch body update (nodes once, then
     the spreading tiles); a single simulation takes the one-launch form in which every tile block
