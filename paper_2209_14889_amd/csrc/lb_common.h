@@ -31,6 +31,18 @@ constexpr int tile_cap(int T, int halo) {
     return most;
 }
 
+// i / W in a tile's regions as i * ceil(2^16 / W) >> 16 (k_tile): exact for every width up to a tile's with
+// its widest halo and every site of the largest one (not beyond: 1115 / 62 is the first to fail)
+constexpr unsigned tile_div(unsigned i, unsigned W) { return (i * ((65536u + W - 1u) / W)) >> 16; }
+constexpr bool tile_div_exact(int T) {
+    const unsigned widest = (unsigned)tile_cols(T) + 8u, sites = (unsigned)tile_cap(T, 8);
+    for (unsigned W = 1; W <= widest; ++W)
+        for (unsigned i = 0; i < sites; ++i)
+            if (tile_div(i, W) != i / W) return false;
+    return true;
+}
+static_assert(tile_div_exact(64) && tile_div_exact(128) && tile_div_exact(256), "tile_div at every tile shape");
+
 // status bits raised by kernels, read by the host at synchronising calls
 constexpr int kStatusPatch = 1;     // a body outgrew its force/velocity patch
 constexpr int kStatusUnstable = 2;  // watchdog: non-finite or drifting mass

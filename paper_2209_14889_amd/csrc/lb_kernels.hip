@@ -1041,15 +1041,14 @@ __global__ __launch_bounds__(T, T == 64 ? 2 : 4) void k_tile(const SimDev *__res
     const __amdgpu_buffer_rsrc_t rHi = state_rsrc(S.h[cur]), rHo = state_rsrc(S.h[nxt]), rSi = state_rsrc(S.sig[cur]),
                                  rSo = state_rsrc(S.sig[nxt]), rPi = state_rsrc(S.P[cur]), rPo = state_rsrc(S.P[nxt]);
 
-    // site i of a region of width W that begins d sites before the tile: its coordinates in the region
-    // (i / W as i * ceil(2^16 / W) >> 16, exact for i < 2^11 and W <= 64) and its wrapped lattice site
-    // (the region reaches at most 4 sites beyond a lattice of at least 8)
+    // site i of a region of width W that begins d sites before the tile: its coordinates in the region and
+    // its wrapped lattice site (the region reaches at most 4 sites beyond a lattice of at least 8)
     struct Site {
         int X, Y, x, y;
     };
     auto site = [&](int i, int W, int d) {
         Site q;
-        q.Y = (int)(((unsigned)i * ((65536u + (unsigned)W - 1u) / (unsigned)W)) >> 16);
+        q.Y = (int)tile_div((unsigned)i, (unsigned)W);
         q.X = i - q.Y * W;
         q.x = wrap_near(wi.x0 - d + q.X, nx);
         q.y = wrap_near(wi.y0 - d + q.Y, ny);
