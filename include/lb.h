@@ -187,7 +187,8 @@ int lb_body_forces(lb_handle *h, double *host_out, size_t n_out);
  * order within each) into device_out, device memory of at least n_out doubles (LB_ERANGE if
  * n_out < 8 * total bodies): [0..1] the site-sum restoring force, [2..3] the centre of mass,
  * [4..5] the total node force, [6..7] the area-weighted restoring force (the same quantities as
- * lb_body_forces, without the external force, which the host computes).  Asynchronous. */
+ * lb_body_forces, without the external force, which the host computes; NaN for a body whose nodes span more
+ * than 16384 sites).  Asynchronous. */
 int lb_body_forces_device(lb_handle *h, double *device_out, size_t n_out);
 
 /* Bytes of stored state one site update reads and writes (populations, polymer stress and

@@ -1678,6 +1678,7 @@ __device__ __forceinline__ double lane_value(double v, int lane) {   // the same
 // one by one.  (Every site against every edge, with its divisions, in one wave a SIMD: 64 bodies of radius
 // 4 to 32 took 542 us, now 33; 32 of radius 4 to 16 took 91, now 21.)
 constexpr int kForceThreads = 1024;
+constexpr double kMaxSide = 16384.0;
 __global__ __launch_bounds__(kForceThreads) void k_body_force(const SimDev *__restrict__ sims,
                                                               const BodyDev *__restrict__ bodies, int body0, int cur,
                                                               double *__restrict__ out_all) {
@@ -1728,8 +1729,8 @@ __global__ __launch_bounds__(kForceThreads) void k_body_force(const SimDev *__re
     const int x0 = (int)floor(mnx + 0.5), x1 = (int)ceil(mxx - 0.5), y0 = (int)floor(mny + 0.5), y1 = (int)ceil(mxy - 0.5);
     const int ix0 = (int)ceil(mnx), ix1 = (int)floor(mxx), iy0 = (int)ceil(mny), iy1 = (int)floor(mxy);
     double ax = 0.0, ay = 0.0, bx = 0.0, by = 0.0;
-    // a body that has outgrown its patch (a status of its own reports it) has no sums
-    const bool whole = x1 >= x0 && y1 >= y0 && mxx - mnx < (double)B.ps && mxy - mny < (double)B.ps;
+    // nodes that span more than the largest lattice (or none that are numbers) have no sums: the loops end
+    const bool whole = x1 >= x0 && y1 >= y0 && mxx - mnx < kMaxSide && mxy - mny < kMaxSide;
     const int across = whole ? (x1 - x0) / 64 + 1 : 0, units = whole ? across * (y1 - y0 + 1) : 0;
     if (!whole) ax = ay = bx = by = __builtin_nan("");
     for (int u = wv; u < units; u += kWaves) {

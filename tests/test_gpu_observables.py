@@ -54,3 +54,28 @@ def test_observables_of_a_polygon(walls, radius, n, dent, turn):
         assert np.max(np.abs(got[b, 8:10] - r.body_force_area(b))) <= tol
         np.testing.assert_array_equal(per_body[b], np.concatenate([got[b, 0:2], got[b, 4:10]]))
     g.close()
+
+
+def test_observables_of_a_body_beyond_its_patch():
+    """A body that the flow has drawn out beyond its force patch, which the next synchronising call reports:
+    the device's observables are sums over its sites all the same."""
+    import oracle
+    nx, ny = 128, 64
+    s = wl.small_case(9, nx, ny, n_bodies=1, radius=10.0, pull=0.0).sims[0]
+    s.bodies[0].k_spring = s.bodies[0].eps_angle = 1e-12
+    s.params["Kx"] = (0.0, 0.0, 0.0, 0.0)     # nothing but viscosity holds the flow back
+    s.sigma0 = np.zeros((3, ny, nx))
+    s.sigma0[0] = 1e-3 * np.sin(2 * math.pi * np.arange(nx) / nx)
+    u = 0.12 * np.sin(2 * math.pi * (np.arange(ny)[:, None] - s.bodies[0].R[:, 1].mean()) / ny) * np.ones((ny, nx))
+    s.h0 = oracle.equilibrium(np.ones((ny, nx)), u, np.zeros((ny, nx)))
+    g = lb.Sim(s)
+    out = g._torch.full((8,), float("nan"), dtype=g._torch.float64, device="cuda")
+    g.step(500)
+    g.body_forces_device(out)
+    with pytest.raises(lb.LBError) as e:
+        g.sync()
+    assert e.value.code == lb.LB_ERANGE
+    v = out.cpu().numpy()
+    print("observables beyond the patch", v, flush=True)
+    assert np.all(np.isfinite(v)) and np.any(v[0:2] != 0.0) and np.any(v[6:8] != 0.0)
+    g.close()
