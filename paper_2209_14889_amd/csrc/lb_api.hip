@@ -648,14 +648,19 @@ int drain_timing(lb_handle *h) {
     return LB_OK;
 }
 
+// work-groups of T threads of the marching kernel resident on the device at once
+int fused_slots(const lb_handle *h, int T) {
+    return h->cus * fused_blocks_per_cu(T, h->opt.precision == 1, h->any_walls, h->any_pol, !h->plan.bodies.empty());
+}
+
 // the field pass of one step on the current items (fused kernels)
 hipError_t launch_field(lb_handle *h) {
     const bool fp16 = h->opt.precision == 1;
     if (h->tiles)
         return launch_tile(h->fused_T, fp16, h->any_walls, h->any_pol, h->stream, h->d_sims, h->d_bodies, h->d_tiles, h->n_items,
                            h->cur, h->d_t);
-    return launch_fused(h->fused_T, fp16, h->any_walls, h->any_pol, h->fused_grid, h->stream, h->d_sims, h->d_bodies, h->d_items,
-                        h->n_items, h->cur, h->d_t, h->cus);
+    return launch_fused(h->fused_T, fp16, h->any_walls, h->any_pol, !h->plan.bodies.empty(), h->fused_grid, h->stream, h->d_sims,
+                        h->d_bodies, h->d_items, h->n_items, h->cur, h->d_t, h->cus);
 }
 
 // launch one step's kernels (field pass + node update); parity flips
@@ -857,7 +862,7 @@ int upload_items(lb_handle *h, int T, int seg, int grid = 0) {
         return LB_OK;
     }
     if (items.size() > h->plan.items.size()) return fail(LB_EINVAL, "internal: work-item table overflow");
-    const int slots = h->cus * fused_blocks_per_cu(T, h->opt.precision == 1, h->any_walls, h->any_pol);
+    const int slots = fused_slots(h, T);
     if ((grid <= 0 || grid >= (int)items.size()) && !deal_by_work(items, h->cus, slots)) {
         const int rc = place_body_items(h, items);
         if (rc) return rc;
@@ -984,8 +989,7 @@ int choose_fused_config(lb_handle *h) {
         int T = 0, rows = 0;
         if (model_tiles(T, rows)) return upload_items(h, T, rows);
         T = model_T();
-        int seg = h->opt.seg ? h->opt.seg : model_seg(h->plan.sims, T, cus * fused_blocks_per_cu(T, fp16, h->any_walls, h->any_pol),
-                                                     h->plan.items.size());
+        int seg = h->opt.seg ? h->opt.seg : model_seg(h->plan.sims, T, fused_slots(h, T), h->plan.items.size());
         return upload_items(h, T, seg, h->opt.grid);
     }
     const uint64_t key = tune_key(h, h->params, dev);
@@ -1008,7 +1012,7 @@ int choose_fused_config(lb_handle *h) {
     }
     for (int T : {64, 128, 256}) {
         if (h->opt.threads && T != h->opt.threads) continue;
-        int slots = cus * fused_blocks_per_cu(T, fp16, h->any_walls, h->any_pol);
+        int slots = fused_slots(h, T);
         int m = model_seg(h->plan.sims, T, slots, h->plan.items.size());
         for (int seg : {m, std::max(4, m / 2), m * 2, m + 4, std::max(4, m - 4), 64}) {
             for (int grid : {0, (slots / 8) * 8}) {

@@ -554,7 +554,10 @@ __device__ __forceinline__ void inc_row(unsigned &r, unsigned ny) { r = (r + 1u 
 // POL = false: every simulation of the launch has P = 0, which the dynamics keep exactly (the
 // polarization right-hand side is proportional to P), so the Ericksen stress vanishes and C~ is
 // its isotropic value: the scalar model of Sec. II B.  That variant skips all P work.
-template <int T, typename HT, bool WALLS, bool POL>
+// ONE: items that one body touches keep it in registers (below).  A launch without bodies takes the
+// variant without: the registers and the branch a row cost every item (FP32 lattices without bodies,
+// us a step: 1024^2 34.7, with them 35.1; 2048^2 170.9, 171.4; 32 of 128^2 21.7, 22.0).
+template <int T, typename HT, bool WALLS, bool POL, bool ONE>
 __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 : 4) void k_fused(const SimDev *__restrict__ sims, const BodyDev *__restrict__ bodies,
                                              const WorkItem *__restrict__ items, int n_items, int cur,
                                              int *__restrict__ d_t, int cus) {
@@ -659,7 +662,7 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
             PT P0, P1;                     // P(f+1)
             float S0, S1, S2;              // sigma(f)
             typename Pop<HT>::Raw H[9];    // populations pulled into row f-1
-            float F0, F1;                  // the only body's spread force at row f-1 (kOneBody)
+            float F0, F1;                  // the only body's spread force at row f-1 (ONE)
         };
         // Values of this column handed from one iteration to the next: stage D's centre row
         // (the corrector's frozen inputs and the next predictor's south neighbours) and stage E's
@@ -672,7 +675,6 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
             float q0, q1, q2;
             PT qp0, qp1;
         };
-        constexpr bool kOneBody = !std::is_same<HT, __half>::value && !WALLS;
         Pre preA, preB;
         Carry carA, carB;
         // Row iterations 0 and 1 would only commit P rows f0 and f0+1 (their stress rows f0-1 and
@@ -699,7 +701,7 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
             preA.S1 = buf_ldf(rSi, b4, N4 + rS0);
             preA.S2 = buf_ldf(rSi, b4, 2u * N4 + rS0);
         }
-        if (kOneBody) preA.F0 = preA.F1 = preB.F0 = preB.F1 = 0.f;
+        if (ONE) preA.F0 = preA.F1 = preB.F0 = preB.F1 = 0.f;
         // Ericksen xy, yy of this column at rows f-1, f-2, f-3
         float exy1 = 0.f, eyy1 = 0.f, exy2 = 0.f, eyy2 = 0.f, exy3 = 0.f, eyy3 = 0.f;
 
@@ -710,7 +712,7 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
         // same for every row, the row's is scalar) and loads the spread force a row ahead.  The FP16 form
         // takes the list: at four waves a SIMD it would spill; so does the one with walls, which the extra
         // registers slow down (1400 x 1001 channel 46.1 -> 47.8 us).
-        const bool one = kOneBody && nib == 1;
+        const bool one = ONE && nib == 1;
         OneBody ob{0, 0, 0, rSi, rSi};
         unsigned bcol = kOutside;
         if (one) {
@@ -1832,17 +1834,22 @@ hipError_t launch_ib(bool advance, int nbodies, int ntiles, int nmax, hipStream_
     return hipGetLastError();
 }
 
-// the kernel for (work-group size, storage type, walls, polarization)
+// the kernel for (work-group size, storage type, walls, polarization, any body in the launch)
 typedef void (*FusedFn)(const SimDev *, const BodyDev *, const WorkItem *, int, int, int *, int);
-template <int T, typename HT>
-static FusedFn fused_fn_t(bool walls, bool pol) {
-    if (walls) return pol ? k_fused<T, HT, true, true> : k_fused<T, HT, true, false>;
-    return pol ? k_fused<T, HT, false, true> : k_fused<T, HT, false, false>;
+template <int T>
+static FusedFn fused_fn_t(bool fp16, bool walls, bool pol, bool any_body) {
+    if (fp16) {
+        if (walls) return pol ? k_fused<T, __half, true, true, false> : k_fused<T, __half, true, false, false>;
+        return pol ? k_fused<T, __half, false, true, false> : k_fused<T, __half, false, false, false>;
+    }
+    if (walls) return pol ? k_fused<T, float, true, true, false> : k_fused<T, float, true, false, false>;
+    if (any_body) return pol ? k_fused<T, float, false, true, true> : k_fused<T, float, false, false, true>;
+    return pol ? k_fused<T, float, false, true, false> : k_fused<T, float, false, false, false>;
 }
-static FusedFn fused_fn(int T, bool fp16, bool walls, bool pol) {
-    if (T == 64) return fp16 ? fused_fn_t<64, __half>(walls, pol) : fused_fn_t<64, float>(walls, pol);
-    if (T == 128) return fp16 ? fused_fn_t<128, __half>(walls, pol) : fused_fn_t<128, float>(walls, pol);
-    if (T == 256) return fp16 ? fused_fn_t<256, __half>(walls, pol) : fused_fn_t<256, float>(walls, pol);
+static FusedFn fused_fn(int T, bool fp16, bool walls, bool pol, bool any_body) {
+    if (T == 64) return fused_fn_t<64>(fp16, walls, pol, any_body);
+    if (T == 128) return fused_fn_t<128>(fp16, walls, pol, any_body);
+    if (T == 256) return fused_fn_t<256>(fp16, walls, pol, any_body);
     return nullptr;
 }
 
@@ -1867,16 +1874,16 @@ hipError_t launch_tile(int T, bool fp16, bool walls, bool pol, hipStream_t st, c
     return hipGetLastError();
 }
 
-hipError_t launch_fused(int T, bool fp16, bool walls, bool pol, int grid, hipStream_t st, const SimDev *sims,
+hipError_t launch_fused(int T, bool fp16, bool walls, bool pol, bool any_body, int grid, hipStream_t st, const SimDev *sims,
                         const BodyDev *bodies, const WorkItem *items, int n_items, int cur, int *d_t, int cus) {
-    FusedFn f = fused_fn(T, fp16, walls, pol);
+    FusedFn f = fused_fn(T, fp16, walls, pol, any_body);
     if (!f || cus < 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(f, dim3(grid), dim3(T), 0, st, sims, bodies, items, n_items, cur, d_t, cus);
     return hipGetLastError();
 }
 
-int fused_blocks_per_cu(int T, bool fp16, bool walls, bool pol) {
-    FusedFn f = fused_fn(T, fp16, walls, pol);
+int fused_blocks_per_cu(int T, bool fp16, bool walls, bool pol, bool any_body) {
+    FusedFn f = fused_fn(T, fp16, walls, pol, any_body);
     int n = 0;
     hipError_t e = f ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, T, 0) : hipErrorInvalidValue;
     return e == hipSuccess && n > 0 ? n : 1;

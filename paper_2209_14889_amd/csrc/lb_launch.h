@@ -14,14 +14,15 @@ hipError_t launch_ib(bool advance, int nbodies, int ntiles, int nmax, hipStream_
                      const int2 *blk, int cur, const int *d_t, int *d_status);
 // walls: the variant with wall handling (needed when any simulation of the launch has walls);
 // pol: the variant with the polarization field (needed unless P is zero in every simulation);
+// any_body: the variant for launches with bodies;
 // cus: the device's compute units (work-groups of the first round are dealt to them in turn)
-hipError_t launch_fused(int T, bool fp16, bool walls, bool pol, int grid, hipStream_t st, const SimDev *sims,
+hipError_t launch_fused(int T, bool fp16, bool walls, bool pol, bool any_body, int grid, hipStream_t st, const SimDev *sims,
                         const BodyDev *bodies, const WorkItem *items, int n_items, int cur, int *d_t, int cus);
 // the same step with short items as tiles, one work-group per item (T: 64, 128 or 256)
 hipError_t launch_tile(int T, bool fp16, bool walls, bool pol, hipStream_t st, const SimDev *sims, const BodyDev *bodies,
                        const WorkItem *items, int n_items, int cur, int *d_t);
 // resident fused work-groups per compute unit for work-group size T
-int fused_blocks_per_cu(int T, bool fp16, bool walls, bool pol);
+int fused_blocks_per_cu(int T, bool fp16, bool walls, bool pol, bool any_body);
 hipError_t launch_multipass(bool fp16, int nblocks, hipStream_t st, const SimDev *sims, const BodyDev *bodies,
                             const SiteBlock *blk, int cur, int *d_t);
 // the planes of `mask` (bits 0 .. 9 in the order of lb_read_fields), packed into out

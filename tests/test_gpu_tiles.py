@@ -101,3 +101,25 @@ def test_the_model_fits_the_item_table(nx, threads):
         np.testing.assert_array_equal(a[k], b[k], err_msg=k)
     one.close()
     g.close()
+
+
+@pytest.mark.parametrize("polar", [0, 1])
+@pytest.mark.parametrize("threads,nx", [(64, 64), (128, 100), (256, 300)])
+def test_a_lattice_without_bodies_beside_one_with(threads, nx, polar):
+    """A launch without bodies takes a variant of the marching kernel of its own; beside a lattice with a
+    body, the same lattice takes the other one.  The same bits."""
+    alone = wl.small_case(83, nx, 45).sims[0]
+    alone.bodies = []
+    other = wl.small_case(84, 70, 50, radius=6.0, pull=2e-4).sims[0]
+    if not polar:
+        for s in (alone, other):
+            s.P0 = np.zeros_like(s.P0)
+    opt = lb.make_options(fused_threads=threads, seg_rows=23)
+    a, b = lb.Sim([alone], opt), lb.Sim([alone, other], opt)
+    a.step(9)
+    b.step(9)
+    x, y = a.fields(), b.fields(0)
+    for k in lb.FIELDS:
+        np.testing.assert_array_equal(x[k], y[k], err_msg=k)
+    a.close()
+    b.close()
