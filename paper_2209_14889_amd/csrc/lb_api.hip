@@ -478,22 +478,6 @@ std::vector<WorkItem> build_items(const std::vector<SimPlan> &sims, int T, int s
     return items;
 }
 
-// Whether items of `rows` rows go as tiles.  A tile is a short chain (6.5-9 us for any lattice whose
-// tiles are all resident at once, where marching items take 17-23), but computes more halo: with more tiles
-// a compute unit, items marching down their rows win.  The line, steps with one body a lattice, tiles
-// against the best marching shape: FP32, 640^2, 6.25 tiles a unit, 29.7 against 30.0 us; 680^2, 7.3, 31.8 against
-// 30.4.  Lattices of up to 128 columns march without halo columns, so earlier: 20 of 128^2, 5 a unit, 28.0
-// against 28.1; 24 of them, 6 a unit, 30.1 against 28.8; 96 of 64^2, 6 a unit, 37.3 against 36.6.  FP16 tiles
-// are resident eight to a unit: 28 of 128^2, 7 a unit, 30.5 against 32.1; 700^2, 7.6, 28.8 against 28.9; 720^2,
-// 8.1, 32.8 against 28.8.
-bool tiles_pay(const std::vector<SimPlan> &sims, int T, int rows, int cus, bool fp16) {
-    if (rows < kTileMinRows || rows > tile_rows(T)) return false;
-    int widest = 0;
-    for (const SimPlan &sp : sims) widest = std::max(widest, sp.nx);
-    const size_t halves = fp16 ? 16 : widest <= 128 ? 11 : 13;   // of a tile a unit
-    return 2 * count_tiles(sims, T, rows) <= halves * (size_t)cus;
-}
-
 std::vector<WorkItem> build_tiles(const std::vector<SimPlan> &sims, int T, int rows) {
     std::vector<WorkItem> items;
     for (size_t s = 0; s < sims.size(); ++s) {
@@ -506,26 +490,6 @@ std::vector<WorkItem> build_tiles(const std::vector<SimPlan> &sims, int T, int r
             }
     }
     return items;
-}
-
-// cost model of one fused launch: work items run in rounds of `slots` resident work-groups and
-// an item of seg rows takes seg + 8 row iterations (the pipeline fill).  From three rows on: where they
-// still fit in one round they beat four (700^2 33.1 -> 30.8 us a step); two rows gain nothing more.  The item
-// table (`room`) is sized for four: narrow strips of three rows may not fit.
-int model_seg(const std::vector<SimPlan> &sims, int T, int slots, size_t room) {
-    int best = 8;
-    double best_cost = 1e300;
-    for (int seg = 3; seg <= 128; ++seg) {
-        size_t items = build_items(sims, T, seg).size();
-        if (items > room) continue;
-        double rounds = std::ceil((double)items / slots);
-        double cost = rounds * (seg + 8) + 1e-3 * seg;   // ties: shorter segments
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = seg;
-        }
-    }
-    return best;
 }
 
 }  // namespace
@@ -651,6 +615,53 @@ int drain_timing(lb_handle *h) {
 // work-groups of T threads of the marching kernel resident on the device at once
 int fused_slots(const lb_handle *h, int T) {
     return h->cus * fused_blocks_per_cu(T, h->opt.precision == 1, h->any_walls, h->any_pol, !h->plan.bodies.empty());
+}
+
+// Whether items of `rows` rows go as tiles.  A tile is a short chain (6.5-9 us for any lattice whose
+// tiles are all resident at once, where marching items take 17-23), but computes more halo: with more tiles
+// a compute unit, items marching down their rows win.  The line, steps with one body a lattice, tiles
+// against the best marching shape: FP32, 640^2, 6.25 tiles a unit, 29.7 against 30.0 us; 680^2, 7.3, 31.8 against
+// 30.4.  Lattices of up to 128 columns march without halo columns, so earlier: 20 of 128^2, 5 a unit, 28.0
+// against 28.1; 24 of them, 6 a unit, 30.1 against 28.8; 96 of 64^2, 6 a unit, 37.3 against 36.6.  FP16 tiles
+// are resident eight to a unit: 28 of 128^2, 7 a unit, 30.5 against 32.1; 700^2, 7.6, 28.8 against 28.9; 720^2,
+// 8.1, 32.8 against 28.8.
+// Without bodies, whose items are the slowest and gain most by the shorter chain, earlier: FP32, 250^2 six times,
+// 6 a unit, 20.4 against 20.8; 620^2, 6.1, 21.1 against 20.7; FP16, 24 of 128^2, 6 a unit, 18.0 against 18.3; 26
+// of them, 6.5, 19.5 against 18.8; 250^2 eight times, 8, 21.5 against 19.7.
+bool tiles_pay(const lb_handle *h, int T, int rows) {
+    if (rows < kTileMinRows || rows > tile_rows(T)) return false;
+    const bool fp16 = h->opt.precision == 1, bodies = !h->plan.bodies.empty();
+    int widest = 0;
+    for (const SimPlan &sp : h->plan.sims) widest = std::max(widest, sp.nx);
+    const size_t halves = fp16 ? (bodies ? 16 : 12) : widest <= 128 ? 11 : bodies ? 13 : 12;   // of a tile a unit
+    return 2 * count_tiles(h->plan.sims, T, rows) <= halves * (size_t)h->cus;
+}
+
+// cost model of one fused launch: work items run in rounds of `slots` resident work-groups and
+// an item of seg rows takes seg + 8 row iterations (the pipeline fill).  From three rows on: where they
+// still fit in one round they beat four (one body, 700^2 33.1 -> 30.8 us a step; 96 of 64^2 41.2 -> 40.9, 104 of
+// them 43.6 -> 41.8); two rows gain nothing more.  Without bodies, whose items last longest, the work counts
+// and not an item's length: there only where no SIMD takes a further wave (700^2 24.5 -> 22.3; 30 of 128^2
+// instead 21.2 -> 22.0, 128 of 64^2 21.9 -> 30.2).  The item table (`room`) is sized for four: narrow strips of
+// three rows may not fit.
+int model_seg(const lb_handle *h, int T) {
+    const std::vector<SimPlan> &sims = h->plan.sims;
+    const int slots = fused_slots(h, T), simds = 4 * h->cus;
+    auto waves = [&](size_t items) { return (items * (size_t)(T / 64) + simds - 1) / simds; };   // of a SIMD
+    int best = 8;
+    double best_cost = 1e300;
+    for (int seg = 3; seg <= 128; ++seg) {
+        size_t items = build_items(sims, T, seg).size();
+        if (items > h->plan.items.size()) continue;
+        if (seg == 3 && h->plan.bodies.empty() && waves(items) > waves(build_items(sims, T, 4).size())) continue;
+        double rounds = std::ceil((double)items / slots);
+        double cost = rounds * (seg + 8) + 1e-3 * seg;   // ties: shorter segments
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = seg;
+        }
+    }
+    return best;
 }
 
 // the field pass of one step on the current items (fused kernels)
@@ -850,7 +861,7 @@ int place_body_items(lb_handle *h, std::vector<WorkItem> &items) {
 // grid: 0 = one work-group per item; > 0 = persistent grid of that many work-groups (a multiple
 // of 8, so each XCD keeps a contiguous run of items) looping over the item table
 int upload_items(lb_handle *h, int T, int seg, int grid = 0) {
-    h->tiles = grid <= 0 && h->d_tiles && tiles_pay(h->plan.sims, T, seg, h->cus, h->opt.precision == 1);
+    h->tiles = grid <= 0 && h->d_tiles && tiles_pay(h, T, seg);
     if (h->tiles && count_tiles(h->plan.sims, T, seg) > h->plan.max_tiles) h->tiles = false;
     std::vector<WorkItem> items = h->tiles ? build_tiles(h->plan.sims, T, seg) : build_items(h->plan.sims, T, seg);
     if (h->tiles) {
@@ -880,12 +891,12 @@ int upload_items(lb_handle *h, int T, int seg, int grid = 0) {
 
 // What a shape (threads, rows, grid) stands for, raised with every change of the field kernels or of the
 // rules that pick one of them for a shape, so that shapes timed with other kernels are tuned again:
-// 2: short items as tiles where they pay.
-constexpr uint64_t kShapeMeaning = 2;
+// 3: short items as tiles where they pay, for lattices with bodies and without.
+constexpr uint64_t kShapeMeaning = 3;
 
 // FNV-1a over everything the tuned shape depends on: the lattices (sizes, walls, P or not), the
-// storage precision, the field kernel, a forced work-group size, the GPU (model, CUs), what a shape means
-// and whether there is a table for tiles (without one the same shape marches)
+// storage precision, the field kernel, a forced work-group size, the GPU (model, CUs), what a shape means,
+// whether there is a table for tiles (without one the same shape marches) and whether there are bodies
 uint64_t tune_key(const lb_handle *h, const std::vector<lb_sim_params> &sims, int dev) {
     uint64_t k = 1469598103934665603ull;
     auto mix = [&](uint64_t v) {
@@ -904,6 +915,7 @@ uint64_t tune_key(const lb_handle *h, const std::vector<lb_sim_params> &sims, in
     mix((uint64_t)h->opt.threads);
     mix(kShapeMeaning);
     mix((uint64_t)(h->d_tiles != nullptr));
+    mix((uint64_t)!h->plan.bodies.empty());
     mix((uint64_t)sims.size());
     for (const auto &p : sims) {
         mix((uint64_t)p.nx);
@@ -959,7 +971,6 @@ int choose_fused_config(lb_handle *h) {
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     h->cus = std::max(1, cus);
     if (h->opt.kernel != 0) return LB_OK;
-    const bool fp16 = h->opt.precision == 1;
     // work-group width: lattices no wider than 64 or 128 run as full-width strips of that many
     // lanes (no halo lanes and no idle waves); wider ones as 248-column strips of 256 lanes
     auto model_T = [&]() {
@@ -979,17 +990,17 @@ int choose_fused_config(lb_handle *h) {
         T = model_T();
         if (!h->opt.threads && sites > 2048) T = std::max(T, 128);
         rows = kTileMinRows;
-        if (count_tiles(h->plan.sims, T, rows) * (size_t)(T / 64) <= 8 * (size_t)cus && tiles_pay(h->plan.sims, T, rows, h->cus, fp16))
+        if (count_tiles(h->plan.sims, T, rows) * (size_t)(T / 64) <= 8 * (size_t)cus && tiles_pay(h, T, rows))
             return true;
         T = h->opt.threads ? T : 256;
         rows = 8;
-        return tiles_pay(h->plan.sims, T, rows, h->cus, fp16);
+        return tiles_pay(h, T, rows);
     };
     if (!h->opt.autotune) {
         int T = 0, rows = 0;
         if (model_tiles(T, rows)) return upload_items(h, T, rows);
         T = model_T();
-        int seg = h->opt.seg ? h->opt.seg : model_seg(h->plan.sims, T, fused_slots(h, T), h->plan.items.size());
+        int seg = h->opt.seg ? h->opt.seg : model_seg(h, T);
         return upload_items(h, T, seg, h->opt.grid);
     }
     const uint64_t key = tune_key(h, h->params, dev);
@@ -1013,7 +1024,7 @@ int choose_fused_config(lb_handle *h) {
     for (int T : {64, 128, 256}) {
         if (h->opt.threads && T != h->opt.threads) continue;
         int slots = fused_slots(h, T);
-        int m = model_seg(h->plan.sims, T, slots, h->plan.items.size());
+        int m = model_seg(h, T);
         for (int seg : {m, std::max(4, m / 2), m * 2, m + 4, std::max(4, m - 4), 64}) {
             for (int grid : {0, (slots / 8) * 8}) {
                 Cand c{T, seg, grid};

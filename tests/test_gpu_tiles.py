@@ -123,3 +123,21 @@ def test_a_lattice_without_bodies_beside_one_with(threads, nx, polar):
         np.testing.assert_array_equal(x[k], y[k], err_msg=k)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("nx,ny,k,precision,polar,tiles,rows", [
+    (64, 64, 128, 0, 1, 0, 4), (100, 100, 40, 0, 0, 0, 4), (128, 128, 30, 0, 1, 0, 4), (640, 640, 1, 0, 1, 0, 4),
+    (250, 250, 8, 1, 1, 0, 4), (128, 128, 30, 1, 0, 0, 4), (700, 700, 1, 0, 1, 0, 3), (250, 250, 6, 0, 1, 1, 8)])
+def test_launch_model_without_bodies(nx, ny, k, precision, polar, tiles, rows):
+    """Lattices without bodies on 256 compute units: tiles up to six a unit, and three marching rows only
+    where they do not put a further wave on a SIMD.  The lattices beyond were slower than in four rows."""
+    s = wl.small_case(85, nx, ny, n_bodies=0, random_dirs=False).sims[0]
+    if not polar:
+        s.P0 = np.zeros_like(s.P0)
+    g = lb.Sim([s] * k, lb.make_options(precision=precision))
+    if g._torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are those of 256 compute units")
+    shape = g.launch_shape()
+    across = -(-nx // 32) if tiles else 1 if nx <= 256 else -(-nx // 248)
+    assert shape["seg_rows"] == rows and shape["n_items"] == k * across * -(-ny // rows), shape
+    g.close()
