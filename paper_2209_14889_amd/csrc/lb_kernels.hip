@@ -78,6 +78,8 @@ __device__ __forceinline__ Schedule schedule(const BodyDev &B, double t) {
     return q;
 }
 
+typedef float Float4 __attribute__((ext_vector_type(4)));     // 16 bytes each, for loads from global memory
+typedef double Double2 __attribute__((ext_vector_type(2)));
 // four consecutive floats at any 4-byte boundary (one 16-byte load)
 typedef float Row4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -329,73 +331,101 @@ struct TileNodes {
     int cnt[kIbThreads / 64];
 };
 
-// f_IB at tile site (lx, ly): the listed nodes' f_a phi(x) phi(y), of the entries with an even number (h 0),
-// an odd one (h 1) or of both apart (s[0], s[1]), each in order.  The wave's sites are [x0, x1] x [y0, y1]: its
+// what entry e of the list adds at tile site (lx, ly), e's values in o, wx, wy and f
+__device__ __forceinline__ void gather_one(int lx, int ly, int2 o, float4 wx, float4 wy, double2 f, double2 &s) {
+    const int i = lx - o.x, j = ly - o.y;
+    if ((unsigned)i < 4u && (unsigned)j < 4u) {
+        const float wxs = i == 0 ? wx.x : i == 1 ? wx.y : i == 2 ? wx.z : wx.w;
+        const float wys = j == 0 ? wy.x : j == 1 ? wy.y : j == 2 ? wy.z : wy.w;
+        const double w = (double)wxs * (double)wys;
+        s.x += f.x * w;
+        s.y += f.y * w;
+    }
+}
+
+// f_IB at tile site (lx, ly): the listed nodes' f_a phi(x) phi(y), of the entries with an even number (h 0) or
+// an odd one (h 1), in order.  The wave's sites are [x0, x1] x [y0, y1]: its
 // lanes first look at 64 entries at once, and only those that reach them are read and weighed, the LDS
 // reads of four entries before any of them is used.  An entry costs some forty instructions of the chain, and
 // of the nodes of an arc across the tile about half reach a wave's 8 x 4 sites (whole rows of the tile, 16 x 2,
 // gain nothing from an arc along them: 512^2 22.2 us a step, with 8 x 4 21.6, every entry 21.7; 64^2 14.1, 14.1
 // and 14.6; 32 pulled bodies 32.3, 32.2 and 32.8).
-template <bool BOTH>
-__device__ __forceinline__ void gather(const TileNodes &L, int cnt, int lx, int ly, int x0, int y0, int x1, int y1, int h, double2 s[2]) {
+__device__ __forceinline__ double2 gather_half(const TileNodes &L, int cnt, int lx, int ly, int x0, int y0, int x1, int y1, int h) {
     constexpr unsigned long long kEven = 0x5555555555555555ull;
     const int lane = threadIdx.x & 63;
+    double2 s = make_double2(0.0, 0.0);
 #pragma unroll 1
     for (int base = 0; base < cnt; base += 64) {
         const int2 at = L.o[min(base + lane, kMaxCand - 1)];
         const unsigned long long near =
             __ballot(base + lane < cnt && at.y <= y1 && at.y + 4 > y0 && at.x <= x1 && at.x + 4 > x0);
-#pragma unroll
-        for (int p = 0; p < (BOTH ? 2 : 1); ++p) {
-            unsigned long long m = near & ((BOTH ? p : h) ? kEven << 1 : kEven);
+        unsigned long long m = near & (h ? kEven << 1 : kEven);
 #pragma unroll 1
-            for (int left = max(__popcll(near & kEven), __popcll(near & (kEven << 1))); left > 0; left -= 4) {
-                int2 o[4];
-                float4 wx[4], wy[4];
-                double2 f[4];
-                bool have[4];
+        for (int left = max(__popcll(near & kEven), __popcll(near & (kEven << 1))); left > 0; left -= 4) {
+            int2 o[4];
+            float4 wx[4], wy[4];
+            double2 f[4];
+            bool have[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    have[u] = m != 0;
-                    const int e = base + (have[u] ? __builtin_ctzll(m) : 0);
-                    m &= m - 1;
-                    o[u] = L.o[e];
-                    wx[u] = L.w[e][0];
-                    wy[u] = L.w[e][1];
-                    f[u] = L.f[e];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = lx - o[u].x, j = ly - o[u].y;
-                    if (have[u] && (unsigned)i < 4u && (unsigned)j < 4u) {
-                        const float wxs = i == 0 ? wx[u].x : i == 1 ? wx[u].y : i == 2 ? wx[u].z : wx[u].w;
-                        const float wys = j == 0 ? wy[u].x : j == 1 ? wy[u].y : j == 2 ? wy[u].z : wy[u].w;
-                        const double w = (double)wxs * (double)wys;
-                        s[p].x += f[u].x * w;
-                        s[p].y += f[u].y * w;
-                    }
-                }
+            for (int u = 0; u < 4; ++u) {
+                have[u] = m != 0;
+                const int e = base + (have[u] ? __builtin_ctzll(m) : 0);
+                m &= m - 1;
+                o[u] = L.o[e];
+                wx[u] = L.w[e][0];
+                wy[u] = L.w[e][1];
+                f[u] = L.f[e];
             }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (have[u]) gather_one(lx, ly, o[u], wx[u], wy[u], f[u], s);
         }
     }
+    return s;
 }
 
-// the listed nodes' forces on the 16 x 16 sites of tile (tx, ty) of a body's patch, by 256 threads (8 x 8 sites
-// to a wave), or 512 (8 x 4) with a pair of lanes per site (lane h then stores component h).  The even and the odd entries are
-// summed apart and then added, so both give the same bits.
+// The same of all entries, the even and the odd ones apart (s[0], s[1]).  This launch has hundreds of tiles, several
+// to a unit: instructions count and not the chain, and looking for the entries that reach a wave costs more than it
+// spares (k_ib_spread of 96 bodies of radius 12, 1536 tiles, 11.9 us that way and 9.7 this way; of 200, 19.2 and 15.5).
+__device__ __forceinline__ void gather_all(const TileNodes &L, int cnt, int lx, int ly, double2 s[2]) {
+    int e = 0;
+    for (; e + 4 <= cnt; e += 4) {
+        int2 o[4];
+        float4 wx[4], wy[4];
+        double2 f[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            o[u] = L.o[e + u];
+            wx[u] = L.w[e + u][0];
+            wy[u] = L.w[e + u][1];
+            f[u] = L.f[e + u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) gather_one(lx, ly, o[u], wx[u], wy[u], f[u], s[u & 1]);
+    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+        if (e + u < cnt) gather_one(lx, ly, L.o[e + u], L.w[e + u][0], L.w[e + u][1], L.f[e + u], s[u & 1]);
+}
+
+// the listed nodes' forces on the 16 x 16 sites of tile (tx, ty) of a body's patch, by 256 threads (rows of sites),
+// or 512 (8 x 4 to a wave) with a pair of lanes per site (lane h then stores component h).  The even and the odd
+// entries are summed apart and then added, so both give the same bits.
 template <int THREADS>
 __device__ __forceinline__ void spread_tile(const BodyDev &B, const TileNodes &L, int cnt, int tx, int ty) {
     constexpr bool pair = THREADS == 2 * kPatchTile * kPatchTile;
-    const int s = pair ? threadIdx.x >> 1 : threadIdx.x, h = pair ? threadIdx.x & 1 : 0;
-    constexpr int kRows = pair ? 4 : 8;   // of a wave's sites
-    const int wv = uniform((int)(threadIdx.x >> 6)), x0 = (wv & 1) * 8, y0 = (wv >> 1) * kRows;
-    const int lx = x0 + s % 8, ly = y0 + s / 8 % kRows, px = tx * kPatchTile + lx, py = ty * kPatchTile + ly;
+    const int tid = threadIdx.x, h = pair ? tid & 1 : 0;
+    const int wv = uniform(tid >> 6), x0 = (wv & 1) * 8, y0 = (wv >> 1) * 4;   // of a wave's sites (pairs)
+    const int lx = pair ? x0 + (tid >> 1) % 8 : tid % kPatchTile, ly = pair ? y0 + (tid >> 1) / 8 % 4 : tid / kPatchTile;
+    const int px = tx * kPatchTile + lx, py = ty * kPatchTile + ly;
     double2 part[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
-    gather<!pair>(L, cnt, lx, ly, x0, y0, x0 + 7, y0 + kRows - 1, h, part);
-    double2 a = part[0], b = part[1];
-    if (pair) b = make_double2(__shfl_xor(a.x, 1), __shfl_xor(a.y, 1));
-    a.x += b.x;
-    a.y += b.y;
+    if (pair) {
+        part[0] = gather_half(L, cnt, lx, ly, x0, y0, x0 + 7, y0 + 3, h);
+        part[1] = make_double2(__shfl_xor(part[0].x, 1), __shfl_xor(part[0].y, 1));
+    } else {
+        gather_all(L, cnt, lx, ly, part);
+    }
+    const double2 a = make_double2(part[0].x + part[1].x, part[0].y + part[1].y);
     if (px < B.ps && py < B.ps) {
         const unsigned i = (unsigned)(py * B.ps + px), plane = (unsigned)(B.ps * B.ps);
         if (pair) {
@@ -426,9 +456,14 @@ __global__ __launch_bounds__(kSpreadThreads) void k_ib_spread(const BodyDev *__r
         const int a = base + tid;
         bool flag = false;
         int ix = 0, iy = 0;
-        if (a < n) {
-            ix = B.nix[2 * a];
-            iy = B.nix[2 * a + 1];
+        Float4 w0{}, w1{};
+        Double2 f{};
+        if (a < n) {   // all of a node at once, not one after the other as they are stored (10.7 us -> 9.7)
+            ix = gptr(B.nix)[2 * a];
+            iy = gptr(B.nix)[2 * a + 1];
+            w0 = ((const LBK_GLOBAL Float4 *)gptr(B.nw))[2 * a];
+            w1 = ((const LBK_GLOBAL Float4 *)gptr(B.nw))[2 * a + 1];
+            f = ((const LBK_GLOBAL Double2 *)gptr(B.fnode))[a];
             flag = ix > X0 - 4 && ix < X0 + kPatchTile && iy > Y0 - 4 && iy < Y0 + kPatchTile;
         }
         const unsigned long long m = __ballot(flag);
@@ -442,11 +477,10 @@ __global__ __launch_bounds__(kSpreadThreads) void k_ib_spread(const BodyDev *__r
         }
         if (flag) {
             if (q < kMaxCand) {
-                const float4 *w = reinterpret_cast<const float4 *>(B.nw) + 2 * a;
                 L.o[q] = make_int2(ix - X0, iy - Y0);
-                L.w[q][0] = w[0];
-                L.w[q][1] = w[1];
-                L.f[q] = reinterpret_cast<const double2 *>(B.fnode)[a];
+                L.w[q][0] = make_float4(w0.x, w0.y, w0.z, w0.w);
+                L.w[q][1] = make_float4(w1.x, w1.y, w1.z, w1.w);
+                L.f[q] = make_double2(f.x, f.y);
             } else {
                 bad = true;
             }
