@@ -34,8 +34,10 @@ __device__ __forceinline__ bf16x4 bf16_rne4(f32x4 v) {
 enum Epi { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_TANH = 2, EPI_TANH_GRAD = 3 };
 
 constexpr int TM = 64, TN = 64, TK = 64;
-constexpr int LDK = TK + 8;   // LDS row stride in BF16 values: 36 words, so the 16 rows of an operand
-                              // read start at 16 different multiples of four banks
+constexpr int lds_row(int KT) { return KT + 8; }   // LDS row stride in BF16 values: 36 words for 64 of k, so the
+                                                   // 16 rows of an operand read start at 16 different
+                                                   // multiples of four banks
+constexpr int LDK = lds_row(TK);
 
 // Loads through a buffer resource return zero for an offset beyond its range, so what lies outside an
 // operand is loaded with kOut as its offset instead of being branched around: the loads of a trip
@@ -51,10 +53,10 @@ __device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, unsigned off) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
 
-// One thread's share of a 64 x 64 operand tile, as the four float4 it loads.  KC: the operand is
-// contiguous along k (element (r, k) at p[r * ld + k]) and the thread takes k4 .. k4+3 of rows
-// r0, r0+16, r0+32, r0+48.  Otherwise it is contiguous along the rows (element at p[k * ld + r]) and
-// the thread takes the 4 x 4 block of rows r0 .. r0+3 and k4 .. k4+3, v[i] holding k4 + i.
+// One thread's share of a 64 x KT operand tile (KT 64, or 16 with KC), as the KT / 16 float4 it loads.  KC: the
+// operand is contiguous along k (element (r, k) at p[r * ld + k]) and the thread takes k4 .. k4+3 of rows
+// r0, r0+16, r0+32, r0+48 (one row of 64 for KT 16).  Otherwise it is contiguous along the rows (element at
+// p[k * ld + r]) and the thread takes the 4 x 4 block of rows r0 .. r0+3 and k4 .. k4+3, v[i] holding k4 + i.
 // VEC: p and ld, and with ld the extent along the contiguous direction, are multiples of four
 // floats.  Values outside R x K are zero.
 // Buffer offsets are taken from the tile's corner and hold 63 rows (or k) of up to kLongRow floats: any
@@ -62,15 +64,17 @@ __device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, unsigned off) {
 // addresses and a branch around what lies outside.
 constexpr long kLongRow = 1l << 23;
 static_assert(4 * (63 * kLongRow + 64) <= 0x7fffffff, "a tile's offsets stay within its buffer resource");
-template <bool KC, bool VEC, bool LONG>
-__device__ __forceinline__ void tile_load(f32x4 v[4], const float *__restrict__ p, long ld, int R, int K, int row, int k0) {
+template <bool KC, bool VEC, bool LONG, int KT>
+__device__ __forceinline__ void tile_load(f32x4 v[KT / 16], const float *__restrict__ p, long ld, int R, int K, int row, int k0) {
+    static_assert(KC || KT == 64, "a short tile is contiguous along k");
+    constexpr int Q = KT / 4, ROWS = 256 / Q;   // float4 of a row's k, rows of one load of the block
     const int t = threadIdx.x;
     const __amdgpu_buffer_rsrc_t src = operand_rsrc(KC ? p + (long)row * ld + k0 : p + (long)k0 * ld + row);
     const unsigned l = (unsigned)ld;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = KC ? (t >> 4) + 16 * i : (t & 15) * 4;
-        const int k = KC ? (t & 15) * 4 : (t >> 4) * 4 + i;
+    for (int i = 0; i < KT / 16; ++i) {
+        const int r = KC ? t / Q + ROWS * i : (t & 15) * 4;
+        const int k = KC ? t % Q * 4 : (t >> 4) * 4 + i;
         const int n = KC ? (row + r < R ? K - k0 - k : 0) : (k0 + k < K ? R - row - r : 0);   // values left
         if (LONG) {
             const float *q = p + (KC ? (long)(row + r) * ld + k0 + k : (long)(k0 + k) * ld + row + r);
@@ -93,11 +97,12 @@ __device__ __forceinline__ void tile_load(f32x4 v[4], const float *__restrict__ 
         }
     }
 }
-template <bool KC> __device__ __forceinline__ void tile_store(short (*S)[LDK], const f32x4 v[4]) {
+template <bool KC, int KT> __device__ __forceinline__ void tile_store(short (*S)[lds_row(KT)], const f32x4 v[KT / 16]) {
+    constexpr int Q = KT / 4, ROWS = 256 / Q;
     const int t = threadIdx.x;
     if (KC) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *reinterpret_cast<bf16x4 *>(&S[(t >> 4) + 16 * i][(t & 15) * 4]) = bf16_rne4(v[i]);
+        for (int i = 0; i < KT / 16; ++i) *reinterpret_cast<bf16x4 *>(&S[t / Q + ROWS * i][t % Q * 4]) = bf16_rne4(v[i]);
     } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -106,8 +111,8 @@ template <bool KC> __device__ __forceinline__ void tile_store(short (*S)[LDK], c
     }
 }
 
-struct Stage {   // the two LDS buffers of both operands' tiles
-    short a[2][TM][LDK], b[2][TN][LDK];
+template <int KT> struct Stage {   // the two LDS buffers of both operands' tiles
+    short a[2][TM][lds_row(KT)], b[2][TN][lds_row(KT)];
 };
 
 // acc = this wave's 32 x 32 part of the 64 x 64 tile at (m0, n0) of sum_k A(m, k) B(k, n), operands
@@ -121,31 +126,34 @@ struct Stage {   // the two LDS buffers of both operands' tiles
 // trip of 16 of k with scalar loads and two barriers, same results bit for bit: the four products of
 // a 512-row forward pass of the 256-wide network 104 -> 31 us, one of 1000 x 1000 x 1000 78-152 -> about
 // 30 us.
-template <bool AK, bool BK, bool VEC, bool LONG>
-__device__ __forceinline__ void product_tile(Stage &S, f32x4 acc[2][2], const float *__restrict__ A, long lda,
+// KT 16: products of K <= 16 (a network's few inputs), whose tile of 64 would be mostly zeros to convert and
+// store, and leave room for four blocks a unit instead of eight: 65 536 x 512 x 5
+// 58.5 -> 31.0 us (34.5 in trips of 16 with scalar loads), 262 144 rows of 2-16-16-2 53.0 -> 30.2 (44.0).
+template <bool AK, bool BK, bool VEC, bool LONG, int KT>
+__device__ __forceinline__ void product_tile(Stage<KT> &S, f32x4 acc[2][2], const float *__restrict__ A, long lda,
                                              const float *__restrict__ B, long ldb, int M, int N, int K, int m0,
                                              int n0) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 va[4], vb[4];
-    tile_load<AK, VEC, LONG>(va, A, lda, M, K, m0, 0);
-    tile_load<BK, VEC, LONG>(vb, B, ldb, N, K, n0, 0);
-    for (int k0 = 0, s = 0; k0 < K; k0 += TK, s ^= 1) {
+    f32x4 va[KT / 16], vb[KT / 16];
+    tile_load<AK, VEC, LONG, KT>(va, A, lda, M, K, m0, 0);
+    tile_load<BK, VEC, LONG, KT>(vb, B, ldb, N, K, n0, 0);
+    for (int k0 = 0, s = 0; k0 < K; k0 += KT, s ^= 1) {
         // buffer s was last read two trips ago, before the previous trip's barrier
-        tile_store<AK>(S.a[s], va);
-        tile_store<BK>(S.b[s], vb);
+        tile_store<AK, KT>(S.a[s], va);
+        tile_store<BK, KT>(S.b[s], vb);
         __syncthreads();
-        if (k0 + TK < K) {
-            tile_load<AK, VEC, LONG>(va, A, lda, M, K, m0, k0 + TK);
-            tile_load<BK, VEC, LONG>(vb, B, ldb, N, K, n0, k0 + TK);
+        if (k0 + KT < K) {
+            tile_load<AK, VEC, LONG, KT>(va, A, lda, M, K, m0, k0 + KT);
+            tile_load<BK, VEC, LONG, KT>(vb, B, ldb, N, K, n0, k0 + KT);
         }
         // operand layout of the 16x16x16 BF16 MFMA: lane l holds A(l%16, 4*(l/16)+0..3) and
         // B(4*(l/16)+0..3, l%16)
         const int r = lane & 15, kq = (lane >> 4) * 4;
 #pragma unroll
-        for (int kk = 0; kk < TK; kk += 16) {
+        for (int kk = 0; kk < KT; kk += 16) {
             if (k0 + kk >= K) break;
             bf16x4 a[2], b[2];
             for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x4 *>(&S.a[s][wm + 16 * i + r][kk + kq]);
@@ -159,14 +167,14 @@ __device__ __forceinline__ void product_tile(Stage &S, f32x4 acc[2][2], const fl
 
 // D(m, n) = epilogue(product).  Epilogues: + bias[n]; tanh(+ bias); times (1 - aux(m, n)^2) with aux
 // row-major M x N (the tanh derivative from stored activations).
-template <int EPI, bool AK, bool BK, bool VEC, bool LONG = false>
+template <int EPI, bool AK, bool BK, bool VEC, bool LONG = false, int KT = TK>
 __global__ __launch_bounds__(256) void k_gemm(const float *__restrict__ A, long lda, const float *__restrict__ B, long ldb,
                                               float *__restrict__ D, int M, int N, int K,
                                               const float *__restrict__ bias, const float *__restrict__ aux) {
-    __shared__ __align__(16) Stage S;
+    __shared__ __align__(16) Stage<KT> S;
     const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
     f32x4 acc[2][2];
-    product_tile<AK, BK, VEC, LONG>(S, acc, A, lda, B, ldb, M, N, K, m0, n0);
+    product_tile<AK, BK, VEC, LONG, KT>(S, acc, A, lda, B, ldb, M, N, K, m0, n0);
     // result layout: lane l holds D(4*(l/16)+q, l%16), q = 0..3
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int c = n0 + (wv & 1) * 32 + (lane & 15), rq = m0 + (wv >> 1) * 32 + (lane >> 4) * 4;
@@ -814,6 +822,14 @@ hipError_t gemm(const float *A, long lda, const float *B, long ldb, float *D, in
                 k_gemm<EPI, AK, BK, true, true><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
             else
                 k_gemm<EPI, AK, BK, false, true><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
+            return hipGetLastError();
+        }
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_TANH)
+        if (K <= 16) {
+            if (vec(A, lda) && vec(B, ldb))
+                k_gemm<EPI, AK, BK, true, false, 16><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
+            else
+                k_gemm<EPI, AK, BK, false, false, 16><<<grid, 256, 0, st>>>(A, lda, B, ldb, D, M, N, K, bias, aux);
             return hipGetLastError();
         }
     if (vec(A, lda) && vec(B, ldb))

@@ -103,6 +103,28 @@ def test_gemm_bf16_rows_beyond_a_tiles_buffer_range(M, N, K):
     assert torch.equal(mlp.gemm_bf16(A, B), want)
 
 
+@pytest.mark.parametrize("K", [1, 4, 5, 8, 15, 16, 17])
+@pytest.mark.parametrize("batch,offset", [(1, 0), (64, 0), (65, 1), (130, 0)])
+def test_layer_of_few_inputs(K, batch, offset):
+    """One layer of up to and just beyond 16 inputs, too wide for the one-launch form, from inputs on a 16-byte
+    boundary and 4 bytes past one, element by element against the layer of the rounded operands."""
+    import torch
+    from paper_2209_14889_amd import mlp
+    N = 516
+    rng = np.random.default_rng(100 * K + batch)
+    X = rng.uniform(-1, 1, (batch, K)).astype(np.float32)
+    W, b = rng.uniform(-1, 1, (N, K)).astype(np.float32), rng.uniform(-1, 1, N).astype(np.float32)
+    buf = torch.empty(X.size + offset, dtype=torch.float32, device="cuda")
+    x = buf[offset:].view(batch, K)
+    x.copy_(torch.from_numpy(X))
+    net = mlp.MLP([K, N], batch)
+    net.set_params(np.concatenate([W.ravel(), b]))
+    Y = net.forward(x).cpu().numpy().astype(np.float64)
+    z, ez = mb.layer_bound(X.astype(np.float64), np.zeros(X.shape), W.astype(np.float64), b.astype(np.float64))
+    assert np.all(np.abs(Y - z) <= ez)
+    net.close()
+
+
 @pytest.mark.parametrize("widths,batch", [
     ([5, 256, 256, 256, 64], 1), ([5, 256, 256, 256, 64], 17), ([5, 256, 256, 256, 64], 4097),
     ([5, 256, 256, 256, 64], 8193 + 15), ([3, 512, 20, 512, 1], 33), ([130, 4], 5), ([7, 300, 100, 65], 70),
