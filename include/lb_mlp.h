@@ -72,9 +72,9 @@ int lb_mlp_destroy(lb_mlp *m);
  * the library in each GPU's memory (2^20 floats, 4 MiB, held until the process ends; its address
  * is looked up on the first call on a device): batch x (widest hidden layer) must not exceed
  * 2^19 (LB_ERANGE otherwise).  Calls that may overlap on one GPU (different streams, threads) race for
- * that array; calls in order on one stream are safe.  A call leaves the array alone, with the same limit, only
- * where the compute units hold the activations: all widths at most 512, every hidden width a multiple of 4,
- * params on a 16-byte boundary, and Y overlapping neither X nor params (a last layer alone needs no array).
+ * that array; calls in order on one stream are safe.  (Where the compute units can hold the activations the
+ * array is not used, with the same limit; which calls do so depends on sizes and addresses, and none is
+ * promised to.)
  * Same products and results as lb_mlp_forward.  Asynchronous on hip_stream. */
 int lb_mlp_forward_noalloc(const lb_mlp_config *cfg, const float *params, const float *X, int32_t batch,
                            float *Y, void *hip_stream);

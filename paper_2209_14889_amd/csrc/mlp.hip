@@ -846,10 +846,14 @@ hipError_t layer_forward(bool last, const float *in, const float *W, const float
                 : gemm<EPI_BIAS_TANH, true, true>(in, K, W, K, out, B, N, K, b, nullptr, st);
 }
 
-// The network as the narrow kernels take it; false if it is not one for them: a layer too wide, or
-// rows of a weight matrix after the first that do not start on 16 bytes.
+// The network as the narrow kernels take it; false if it is not one for them: a layer too wide; rows of a
+// weight matrix after the first that do not start on 16 bytes; one layer, which is one launch anyway; or a
+// first layer, whose weights come in single loads, of more than 32 768 of them.  Forward passes layer by layer and
+// in one launch, us: 256 rows of 64-256-256-64 26 and 18, of 128-256-256-64 26.3 and 26.0, of 256-256-256-256 26 and
+// 40, of 384-384-384 20 and 75; widths up to the limit of LDS, 1000 rows of 16-384-384-16 26 and 16, of
+// 5-512-512-512-64 44 and 31, 65 536 of them 450 and 308 (one row 28 and 29).
 bool narrow_net(int L, const int *w, const float *P, Net &net) {
-    if (*std::max_element(w, w + L + 1) > kNarrow) return false;
+    if (*std::max_element(w, w + L + 1) > kNarrow || L < 2 || w[0] * w[1] > 32768) return false;
     int o = 0;
     net.L = L;
     for (int l = 0; l < L; ++l) {
@@ -868,6 +872,21 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb) {
     return x < y + nb && y < x + na;
 }
 
+// Whether a forward pass of B rows goes in one launch.  A net of up to 64 columns leaves most of a block's 16
+// waves idle, so over many rows the layers win: 5-16-16-8, 16 384 rows 10.4 us in one launch, 13.0 by layers,
+// 24 576 rows 18.2 and 13.8; 5-64-64-8, 32 768 rows 20.1 and 20.7, 49 152 rows 31 and 25.
+bool narrow_forward(const Net &net, int B) {
+    const int widest = *std::max_element(net.w, net.w + net.L + 1);
+    return widest > 64 || B <= std::min(std::max(1024 * widest, 16384), 32768);
+}
+
+// Whether gradients of B rows go through k_forward and k_backward, 16 rows a block.  Each block reads every weight, so
+// beyond a block or two a unit the layers win, the earlier the wider: a training step of 8192 rows of 5-256-256-256-64
+// 211 us, 224 by layers, of 16 384 rows 406 and 401; of 5-512-512-512-64, 2000 rows 112 and 121, 4100 rows 223 and 180.
+bool narrow_gradients(const Net &net, int B) {
+    return B <= (*std::max_element(net.w, net.w + net.L + 1) <= 256 ? 8192 : 4096);
+}
+
 template <int RT> size_t narrow_lds(const Net &net) {
     return (2 * (16 * RT) * (size_t)net.stride + kWaves * 16 * row_stride(kPanel)) * sizeof(short);
 }
@@ -877,7 +896,7 @@ template <int RT> hipError_t forward_narrow(const Net &net, const float *P, cons
 }
 
 // Y = network(X) in one launch.  Rows per block: 16 while the blocks are at most one per compute
-// unit (each block reads every weight, so fewer rows a block only help while units are idle), then 32
+// unit of the whole device, 256 (each block reads every weight, so fewer rows a block only help while units are idle), then 32
 // and, where 64 rows' activations fit the 160 KB of LDS, 64, which halve and quarter the weight
 // traffic: 4096 rows take 14 us with 16 rows a block, 8192 rows 18 with 32 (22 with 64), 65 536 rows
 // 90 with 64 (124 with 32).
@@ -913,15 +932,16 @@ int scratch_on_current_device(float **out) {
     return LB_OK;
 }
 
-// forward into the activation buffers, a launch per layer
-int forward(lb_mlp *m, const float *X, int B) {
+// forward into the activation buffers, a launch per layer, the last layer into `out`
+int forward(lb_mlp *m, const float *X, int B, float *out) {
     const Layout &lo = m->lo;
     const float *in = X;
     for (int l = 0; l < lo.L; ++l) {
         const int K = lo.w[l], N = lo.w[l + 1];
         const float *W = m->P() + lo.oW[l], *b = m->P() + lo.oB[l];
-        HIPCHK(layer_forward(l + 1 == lo.L, in, W, b, m->act(l), B, N, K, m->stream));
-        in = m->act(l);
+        float *Z = l + 1 == lo.L ? out : m->act(l);
+        HIPCHK(layer_forward(l + 1 == lo.L, in, W, b, Z, B, N, K, m->stream));
+        in = Z;
     }
     return LB_OK;
 }
@@ -947,7 +967,7 @@ int gradients(lb_mlp *m, const float *X, const float *Y, int B, const Adam *adam
     Net net;
     Grads g{};
     if (m->room) {
-        if (narrow_net(L, lo.w.data(), m->P(), net)) {
+        if (narrow_net(L, lo.w.data(), m->P(), net) && narrow_gradients(net, B)) {
             Kept kept{};
             Chain ch{};
             for (int l = 0; l < L; ++l) {
@@ -961,7 +981,7 @@ int gradients(lb_mlp *m, const float *X, const float *Y, int B, const Adam *adam
             k_backward<<<(B + 15) / 16, 64 * kWaves, narrow_lds<1>(net), m->stream>>>(net, ch, m->P(), Y, B, m->rows());
             HIPCHK(hipGetLastError());
         } else {
-            int rc = forward(m, X, B);
+            int rc = forward(m, X, B, m->act(L - 1));
             if (rc) return rc;
             k_rel_loss<<<B, 64, 0, m->stream>>>(m->act(L - 1), Y, B, NL, m->dz(L - 1), m->rows());
             HIPCHK(hipGetLastError());
@@ -980,7 +1000,7 @@ int gradients(lb_mlp *m, const float *X, const float *Y, int B, const Adam *adam
         HIPCHK(hipGetLastError());
         return LB_OK;
     }
-    int rc = forward(m, X, B);
+    int rc = forward(m, X, B, m->act(L - 1));
     if (rc) return rc;
     float *dA = m->grad(0), *dZ = m->grad(1);
     k_rel_loss<<<B, 64, 0, m->stream>>>(m->act(L - 1), Y, B, NL, dZ, m->rows());
@@ -1078,14 +1098,16 @@ int lb_mlp_forward(lb_mlp *m, const float *X, int32_t batch, float *Y) {
     if (batch < 1 || batch > m->cfg.max_batch) return fail(LB_ERANGE, "batch out of range");
     const int NL = m->lo.w[m->lo.L];
     Net net;
-    // (overlapping X and Y: the layers' own buffers keep Y unwritten until X has been read)
-    if (narrow_net(m->lo.L, m->lo.w.data(), m->P(), net) &&
-        !overlap(X, 4 * (size_t)batch * m->lo.w[0], Y, 4 * (size_t)batch * NL)) {
+    // overlapping X and Y: layer by layer, where X has been read when the last layer is written (a single
+    // layer goes through its own buffer)
+    const bool apart = !overlap(X, 4 * (size_t)batch * m->lo.w[0], Y, 4 * (size_t)batch * NL);
+    if (apart && narrow_net(m->lo.L, m->lo.w.data(), m->P(), net) && narrow_forward(net, batch)) {
         HIPCHK(forward_narrow(net, m->P(), X, batch, Y, m->stream));
         return LB_OK;
     }
-    int rc = forward(m, X, batch);
-    if (rc) return rc;
+    const bool direct = apart || m->lo.L > 1;
+    int rc = forward(m, X, batch, direct ? Y : m->act(m->lo.L - 1));
+    if (rc || direct) return rc;
     HIPCHK(hipMemcpyAsync(Y, m->act(m->lo.L - 1), 4 * (size_t)batch * NL, hipMemcpyDeviceToDevice, m->stream));
     return LB_OK;
 }
@@ -1138,7 +1160,7 @@ int lb_mlp_forward_noalloc(const lb_mlp_config *cfg, const float *params, const 
     size_t n_params = 0;
     for (int l = 0; l < L; ++l) n_params += (size_t)cfg->widths[l + 1] * (cfg->widths[l] + 1);
     const size_t nY = 4 * (size_t)batch * cfg->widths[L];
-    if (narrow_net(L, cfg->widths, params, net) && !overlap(X, 4 * (size_t)batch * cfg->widths[0], Y, nY) &&
+    if (narrow_net(L, cfg->widths, params, net) && narrow_forward(net, batch) && !overlap(X, 4 * (size_t)batch * cfg->widths[0], Y, nY) &&
         !overlap(params, 4 * n_params, Y, nY)) {
         HIPCHK(forward_narrow(net, params, X, batch, Y, st));
         return LB_OK;

@@ -329,6 +329,30 @@ def test_gradients_in_three_launches_and_layer_by_layer(widths, batch):
     assert abs(out[0][0] - loss) < 2e-3 * loss
 
 
+@pytest.mark.parametrize("widths,batch", [
+    ([5, 16, 16, 8], 16385), ([3, 8, 8, 2], 16400), ([5, 64, 64, 8], 32769), ([4, 100, 8], 32800), ([6, 40], 300)])
+def test_forward_of_many_rows_is_the_forward_of_few(widths, batch):
+    """Just beyond the rows that thin networks take in one launch (and, for the last two, with no such limit,
+    and with one layer): the same bits as the same rows a thousand at a time."""
+    import torch
+    from paper_2209_14889_amd import mlp
+    rng = np.random.default_rng(batch)
+    X = torch.from_numpy(rng.uniform(-1, 1, (batch, widths[0])).astype(np.float32)).cuda()
+    net = mlp.MLP(widths, batch)
+    net.set_params(mlp.init_params(widths, 33))
+    Y = net.forward(X)
+    parts = torch.cat([net.forward(X[i:i + 1000]) for i in range(0, batch, 1000)])
+    assert torch.equal(Y, parts)
+    net.close()
+
+
+@pytest.mark.parametrize("widths,batch", [([5, 64, 64, 64, 8], 8192), ([5, 64, 64, 64, 8], 8193), ([5, 384, 384, 384, 8], 4096),
+                                          ([5, 384, 384, 384, 8], 4097), ([200, 200, 200, 200, 8], 300), ([6, 40], 70)])
+def test_gradients_on_either_side_of_the_one_launch_form(widths, batch):
+    """The most rows that gradients take in three launches, one more, and networks that never do."""
+    test_gradients_in_three_launches_and_layer_by_layer(widths, batch)
+
+
 def test_first_adam_step_follows_its_definition():
     import torch
     from paper_2209_14889_amd import mlp
