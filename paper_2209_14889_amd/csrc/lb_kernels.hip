@@ -1712,7 +1712,9 @@ __device__ __forceinline__ double lane_value(double v, int lane) {   // the same
 // Bound by the chain of one wave's FP64 instructions.  A wave takes 64 sites of a row at a time; its lanes
 // first look at 64 edges at once and work out those few that touch the row, which then go round the wave
 // one by one.  (Every site against every edge, with its divisions, in one wave a SIMD: 64 bodies of radius
-// 4 to 32 took 542 us, now 33; 32 of radius 4 to 16 took 91, now 21.)
+// 4 to 32 took 542 us, now 27; 32 of radius 4 to 16 took 80, now 15.)  Waves without nodes or without sites skip the
+// reductions, which are a small body's time: radius 1.2, 13.7 us with all 16 waves in them, 6.6 without (the start's
+// 256 threads 9.5); 300 bodies of radius 4 28.5 and 14.2 (19.1).
 constexpr int kForceThreads = 1024;
 constexpr double kMaxSide = 16384.0;
 __global__ __launch_bounds__(kForceThreads) void k_body_force(const SimDev *__restrict__ sims,
@@ -1741,16 +1743,19 @@ __global__ __launch_bounds__(kForceThreads) void k_body_force(const SimDev *__re
         fy += f.y;
         ar += q.x * r.y - r.x * q.y;
     }
-    double v9[9] = {wave_min(mnx), wave_min(mny), wave_max(mxx), wave_max(mxy),
-                    wave_sum(cx),  wave_sum(cy),  wave_sum(fx),  wave_sum(fy), wave_sum(ar)};
-    if (lane == 0)
-        for (int k = 0; k < 9; ++k) sh[k][wv] = v9[k];
+    const int nodeWaves = min(kWaves, (n + 63) / 64);   // the others have nothing to reduce
+    if (wv < nodeWaves) {
+        double v9[9] = {wave_min(mnx), wave_min(mny), wave_max(mxx), wave_max(mxy),
+                        wave_sum(cx),  wave_sum(cy),  wave_sum(fx),  wave_sum(fy), wave_sum(ar)};
+        if (lane == 0)
+            for (int k = 0; k < 9; ++k) sh[k][wv] = v9[k];
+    }
     __syncthreads();
     double all[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) all[k] = sh[k][0];
 #pragma unroll 1
-    for (int w = 1; w < kWaves; ++w)
+    for (int w = 1; w < nodeWaves; ++w)
 #pragma unroll
         for (int k = 0; k < 9; ++k) all[k] = k < 2 ? fmin(all[k], sh[k][w]) : k < 4 ? fmax(all[k], sh[k][w]) : all[k] + sh[k][w];
     mnx = all[0];
@@ -1804,13 +1809,16 @@ __global__ __launch_bounds__(kForceThreads) void k_body_force(const SimDev *__re
             by += w * dy;
         }
     }
-    double red[4] = {wave_sum(ax), wave_sum(ay), wave_sum(bx), wave_sum(by)};
-    if (lane == 0)
-        for (int k = 0; k < 4; ++k) sh[k][wv] = red[k];
+    const int unitWaves = min(kWaves, max(units, 1));
+    if (wv < unitWaves) {
+        double red[4] = {wave_sum(ax), wave_sum(ay), wave_sum(bx), wave_sum(by)};
+        if (lane == 0)
+            for (int k = 0; k < 4; ++k) sh[k][wv] = red[k];
+    }
     __syncthreads();
     if (tid < 4) {
         double v = 0.0;
-        for (int w = 0; w < kWaves; ++w) v += sh[tid][w];
+        for (int w = 0; w < unitWaves; ++w) v += sh[tid][w];
         out[tid < 2 ? tid : tid + 4] = v;
     } else if (tid == 4) {
         out[2] = all[4] / n;
