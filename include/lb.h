@@ -122,7 +122,7 @@ typedef struct {
 
 /* Bytes of device memory lb_create needs for these simulations (arena for all state, tables,
  * patches and scratch).  sims: n_sims parameter sets; opt may be NULL (defaults).  The figure includes
- * the table of the tile items (at most 256 KiB, the last part of the arena). */
+ * the table of the tile items (at most 64 KiB, the last part of the arena). */
 int lb_query_arena_bytes(const lb_sim_params *sims, int32_t n_sims, const lb_options *opt,
                          size_t *bytes);
 

@@ -343,7 +343,7 @@ int pick_threads(const lb_sim_params *sims, int n_sims, const Opt &o) {
 // Items of kTileMinRows .. tile_rows(T) rows are tiles (k_tile): the columns of a lattice are cut evenly
 // into as few of at most tile_width(T, rows) as it takes.
 constexpr int kTileMinRows = 4;
-constexpr size_t kMaxTiles = 8192;   // more never pay (tiles_pay)
+constexpr size_t kMaxTiles = 2048;   // of the table: eight for each of 256 compute units, the most that pay (tiles_pay)
 int tiles_across(int nx, int T, int rows) { return (nx + tile_width(T, rows) - 1) / tile_width(T, rows); }
 
 size_t count_tiles(const std::vector<SimPlan> &sims, int T, int rows) {
@@ -861,8 +861,8 @@ int place_body_items(lb_handle *h, std::vector<WorkItem> &items) {
 // grid: 0 = one work-group per item; > 0 = persistent grid of that many work-groups (a multiple
 // of 8, so each XCD keeps a contiguous run of items) looping over the item table
 int upload_items(lb_handle *h, int T, int seg, int grid = 0) {
-    h->tiles = grid <= 0 && h->d_tiles && tiles_pay(h, T, seg);
-    if (h->tiles && count_tiles(h->plan.sims, T, seg) > h->plan.max_tiles) h->tiles = false;
+    // (the table holds every launch that pays on 256 compute units; a device of more may ask for a longer one)
+    h->tiles = grid <= 0 && h->d_tiles && tiles_pay(h, T, seg) && count_tiles(h->plan.sims, T, seg) <= h->plan.max_tiles;
     std::vector<WorkItem> items = h->tiles ? build_tiles(h->plan.sims, T, seg) : build_items(h->plan.sims, T, seg);
     if (h->tiles) {
         HIPCHK(hipMemcpyAsync(h->d_tiles, items.data(), sizeof(WorkItem) * items.size(), hipMemcpyHostToDevice, h->stream));
