@@ -982,7 +982,8 @@ int choose_fused_config(lb_handle *h) {
     // A lattice small enough to be tiles: 4-row tiles of that width's work-group while they give a SIMD at
     // most two waves (more and shorter chains: 64^2 6.4 us with 128 lanes and 4 rows, 7.5 with 8), else
     // 256 lanes and 8 rows, which compute less halo.  Beyond 2048 sites at least 128 lanes (64^2 takes 8.2
-    // us with 64, whose one wave does everything; below, narrow lattices keep the documented width).
+    // us with 64, whose one wave does everything).  Below, narrow lattices keep the documented width, which costs
+    // them half a microsecond: 64 x 24 9.5 us between events against 8.9 with 128 lanes, 16^2 9.5 and 8.9.
     auto model_tiles = [&](int &T, int &rows) {
         if (h->opt.seg || h->opt.grid || !h->d_tiles) return false;
         size_t sites = 0;

@@ -142,6 +142,29 @@ def test_autotune_cache(tmp_path):
     assert len(lines()) == 3
 
 
+@pytest.mark.timeout(300)
+def test_full_ensemble_dealt_by_work():
+    """The 256-member ensemble in the shape that the tuner takes now, 256-thread items of 128 rows dealt by
+    their work in one round, against the 128-thread items of 17 rows that are checked against the oracle
+    above: the same bits."""
+    sims = wl.c4().sims
+    fields = None
+    pick = [0, 37, 100, 128, 255]
+    for threads, rows in ((128, 17), (256, 128)):
+        say(f"case full ensemble, {threads} threads x {rows} rows, 60 steps")
+        ens = lb.Sim(sims, lb.make_options(fused_threads=threads, seg_rows=rows, graph_chunk=20))
+        shape = ens.launch_shape()
+        assert (shape["threads"], shape["seg_rows"]) == (threads, rows)
+        ens.step(60)
+        got = [(ens.fields(i), ens.nodes(i)[0]) for i in pick]
+        fields = got if fields is None else fields
+        for i, (f, R), (f0, R0) in zip(pick, got, fields):
+            for k in lb.FIELDS:
+                np.testing.assert_array_equal(f[k], f0[k], err_msg=f"{i} {k}")
+            np.testing.assert_array_equal(R, R0)
+        ens.close()
+
+
 def _former_tune_key(sim, precision, threads):
     """The autotune file's key of one simulation as it was when every shape marched."""
     import torch
