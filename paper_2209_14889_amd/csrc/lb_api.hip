@@ -617,8 +617,8 @@ int fused_slots(const lb_handle *h, int T) {
     return h->cus * fused_blocks_per_cu(T, h->opt.precision == 1, h->any_walls, h->any_pol, !h->plan.bodies.empty());
 }
 
-// Whether items of `rows` rows go as tiles.  A tile is a short chain (6.5-9 us for any lattice whose
-// tiles are all resident at once, where marching items take 17-23), but computes more halo: with more tiles
+// Whether items of `rows` rows go as tiles.  A tile is a short chain (7-9 us for a lattice whose
+// waves have a SIMD to themselves, where marching items take 17-23), but computes more halo: with more tiles
 // a compute unit, items marching down their rows win.  The line, steps with one body a lattice, tiles
 // against the best marching shape: FP32, 640^2, 6.25 tiles a unit, 29.7 against 30.0 us; 680^2, 7.3, 31.8 against
 // 30.4.  Lattices of up to 128 columns march without halo columns, so earlier: 20 of 128^2, 5 a unit, 28.0
@@ -980,10 +980,10 @@ int choose_fused_config(lb_handle *h) {
         return mx <= 64 ? 64 : mx <= 128 ? 128 : 256;
     };
     // A lattice small enough to be tiles: 4-row tiles of that width's work-group while they give a SIMD at
-    // most two waves (more and shorter chains: 64^2 6.4 us with 128 lanes and 4 rows, 7.5 with 8), else
-    // 256 lanes and 8 rows, which compute less halo.  Beyond 2048 sites at least 128 lanes (64^2 takes 8.2
-    // us with 64, whose one wave does everything).  Below, narrow lattices keep the documented width, which costs
-    // them half a microsecond: 64 x 24 9.5 us between events against 8.9 with 128 lanes, 16^2 9.5 and 8.9.
+    // most two waves (more and shorter chains: 64^2 10.2 us between events with 64 lanes and 4 rows, 11.6 with 8), else
+    // 256 lanes and 8 rows, which compute less halo.  Beyond 2048 sites at least 128 lanes (64^2 9.6 us; with 64
+    // one wave does everything).  Below, narrow lattices keep the documented width, which costs them half a
+    // microsecond: 64 x 24 9.5 us against 8.9 with 128 lanes, 16^2 9.5 and 8.9.
     auto model_tiles = [&](int &T, int &rows) {
         if (h->opt.seg || h->opt.grid || !h->d_tiles) return false;
         size_t sites = 0;

@@ -167,9 +167,12 @@ __device__ __forceinline__ double2 block_com(const double2 *sR, int n, double (*
 // is computed once (a spring and an angle belong to one node and reach its neighbours through LDS), the
 // second velocity interpolation reuses the first one's values, pairs of lanes share a node's
 // interpolation and a site's gather, the extent is reduced in whole sites, and the drive's schedule is
-// one wave's work beside the others' nodes.  One launch, before -> after (the same bits): 64^2, 40
-// nodes 9.3 -> 7.4 us; 2048^2, 8 bodies of 75-150 nodes 10.1 -> 8.3; the 250^2 box with its trap 11.8 ->
-// 9.1; 32 pulled bodies 12.4 -> 9.5.
+// one wave's work beside the others' nodes.  One launch, before -> after: 64^2, 40 nodes 9.3 -> 6.3 us;
+// 2048^2, 8 bodies of 75-150 nodes 10.1 -> 7.8; the 250^2 box with its trap 11.8 -> 8.1.
+// The forces of a site are summed in another order than node by node (the even and the odd entries apart), and so
+// are a node's pull and trap: FP64 sums that may differ in their last bit, which the rounding of the patch to FP32
+// hides nearly always, not by construction (250^2 box, 800 trapped bodies: one force in 2.4 million steps, and with
+// it velocities 1e-6 apart a thousand steps later).  One order, used by both forms: the result does not vary by run.
 constexpr int kIbThreads = 512;
 
 // LDS of the nodes, sized by the launch for its largest body: position, then spring to the next
@@ -1033,11 +1036,11 @@ __global__ __launch_bounds__(T, (WALLS || !std::is_same<HT, __half>::value) ? 3 
 // stage over the whole tile at once, with its halo: P on (w + 8) x (l + 8) sites, the Ericksen stress on
 // (w + 6) x (l + 6), the collision on (w + 4) x (l + 4), the predictor on (w + 2) x (l + 2), the
 // corrector on w x l, with one barrier between stages.  It computes more halo sites per lattice site
-// (16 x 16: 1.9, 1.6, 1.3 times the sites in the first three stages) in a chain about a tenth as
-// long.  The arithmetic of a site is k_fused's, so the results are the same bits.
-// Field pass, FP32, marching -> tiles: 64^2 18.8 -> 6.4 us, 250^2 closed box 21.9 -> 8.8, 512^2 22.9 ->
-// 14.1, of which about 1.6 are the launch itself and 2 the loads; at 4 tiles a unit a tile costs a unit
-// 2.2 us, two thirds of it VALU issue and the rest LDS.
+// (32 x 8, the larger lattices' tile: 2.1, 1.7, 1.3 times the sites in the first three stages) in a chain about a
+// tenth as long.  The arithmetic of a site is k_fused's, so the results are the same bits.
+// Field pass, FP32, one body, marching -> tiles: 64^2 18.8 -> 7.2 us, 250^2 closed box 21.9 -> 9.0, 512^2 22.9 ->
+// 15.8, of which about 1.6 are the launch itself and 2 the loads.  VALU issue is a thirtieth of the first, where a
+// wave is alone on its SIMD, 0.45 of the second and 0.6 of the third, at four tiles a unit.
 template <int T, typename HT, bool WALLS, bool POL>
 __global__ __launch_bounds__(T, T == 64 ? 2 : 4) void k_tile(const SimDev *__restrict__ sims, const BodyDev *__restrict__ bodies,
                                                const WorkItem *__restrict__ items, int n_items, int cur,

@@ -231,8 +231,8 @@ __device__ __forceinline__ void adam_update(const Adam &o, float gi, float &p, f
 // turn the last bit of a sum that cancels into a step of either sign).
 // Bounded by the chain of loads over the batch and the fetch of its code: hence one small tile a wave
 // (a 64 x 64 tile's 16 values a lane cost 15 KB of unrolled update), and more blocks than units.
-// A training step of 256 rows of the 256-wide network: 134 us in 19 launches -> 39 us in three
-// (k_forward 15, k_backward 13, this 9).
+// A training step of 256 rows of the 256-wide network: 390 us in 19 launches -> 39 us in three
+// (k_forward 16.2, k_backward 14.5, this 8.2).
 constexpr int WT = 32;
 template <bool STEP>
 __global__ __launch_bounds__(256) void k_weights(Grads gr, int batch, float *__restrict__ G, Adam adam,
@@ -402,8 +402,8 @@ struct Net {
 // What bounds it: at a few hundred rows a chain of dependent steps (one round of loads per panel, some
 // eight cycles for each instruction of a wave; deeper unrolled forms were slower, 16-27 us for 512 rows
 // against 13), at tens of thousands the vector instructions, most of them the tanh (about 30 a value: 50
-// of the 97 us for 65 536 rows, the products 16).
-// 512 rows of 5-256-256-256-64: 31 -> 12.5 us against a launch per layer; 65 536 rows 210 -> 97 us.
+// of the 94 us for 65 536 rows, the products 16).
+// 512 rows of 5-256-256-256-64: 31 -> 12.9 us against a launch per layer; 65 536 rows 172 -> 94 us.
 // KEEP: every hidden layer's activations are also stored, in FP32, for the backward pass.
 struct Kept {
     float *act[8];
@@ -898,8 +898,8 @@ template <int RT> hipError_t forward_narrow(const Net &net, const float *P, cons
 // Y = network(X) in one launch.  Rows per block: 16 while the blocks are at most one per compute
 // unit of the whole device, 256 (each block reads every weight, so fewer rows a block only help while units are idle), then 32
 // and, where 64 rows' activations fit the 160 KB of LDS, 64, which halve and quarter the weight
-// traffic: 4096 rows take 14 us with 16 rows a block, 8192 rows 18 with 32 (22 with 64), 65 536 rows
-// 90 with 64 (124 with 32).
+// traffic: 4096 rows take 14.5 us with 16 rows a block, 8192 rows 19 with 32 (22 with 64), 65 536 rows
+// 94 with 64 (124 with 32).
 hipError_t forward_narrow(const Net &net, const float *P, const float *X, int B, float *Y, hipStream_t st) {
     if (B <= 16 * 256) return forward_narrow<1>(net, P, X, B, Y, st);
     if (B <= 32 * 256 || narrow_lds<4>(net) > 160 * 1024) return forward_narrow<2>(net, P, X, B, Y, st);
